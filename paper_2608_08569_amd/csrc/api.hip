@@ -485,15 +485,13 @@ int voxzip_evict_compact_ragged(void* k_cache, void* v_cache, float* score, int3
 
 size_t vz_decode_ws_bytes(int32_t L, int32_t Hq, int32_t Hkv, int32_t d, int64_t plane, int32_t n_seqs) {
     (void)d;
-    const size_t gen = vz_decode_generic_ws_bytes(L, Hq, plane, n_seqs);
-    const size_t fused = vz_decode_fused_ws_bytes(L, Hq, plane, n_seqs);
+    const size_t rows = vz_decode_fused_ws_bytes(L, Hq, plane, n_seqs);  // the chunked and the general path
     const size_t range = Hkv > 0 && Hq % Hkv == 0 ? vz_decode_range_ws_bytes(L, Hq, Hkv, plane, n_seqs) : 0;
-    return std::max(std::max(gen, fused), range);
+    return std::max(rows, range);
 }
 
 hipError_t vz_launch_decode(const VzDecodeArgs& a, hipStream_t stream) {
     const int64_t plane = a.rag.n > 0 ? a.rag.total : a.cap;
     if (vz_decode_fused_ok(a.dtype, a.d, a.Hq, a.Hkv, a.L, plane, a.rag.n)) return vz_launch_decode_fused(a, stream);
-    if (!vz_decode_generic_ok(plane, a.rag.n)) return hipErrorInvalidValue;
     return vz_launch_decode_generic(a, stream);
 }

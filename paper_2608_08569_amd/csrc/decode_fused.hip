@@ -72,68 +72,15 @@ struct PartialsT {
 using Partials = PartialsT<uint8_t>;
 using ConstPartials = PartialsT<const uint8_t>;
 
-// Chunks of sequence s in a ragged call (0 when it cannot be served).
-__device__ __forceinline__ int ragged_chunks(const VzRagged& r, int s) {
-    return vz::ragged_decode_status(r, s) == VZ_OK ? (r.len[s] + CHUNK) / CHUNK : 0;
-}
-
-// The sequence a work item belongs to, resolved at the top of every kernel.
-struct SeqItem {
-    int s;           // sequence (0 for a single-sequence call)
-    int len, next_pos;
-    int n_chunks;    // chunks of the sequence
-    int first;       // its first chunk row in the partials
-    int64_t base;    // its first slot in the planes
-};
-
-// Flat chunk f of a ragged call, found by a whole wave: each lane loads one
-// sequence's values (64 sequences per round), a wave scan of their chunk
-// counts finds the owner of f, and the owner's values are forwarded from the
-// lane that loaded them, so the kernel waits for one round of loads.  False
-// when f lies past the call's chunks (or past the nc_max rows).
-__device__ __forceinline__ bool locate_ragged_chunk(const FusedArgs& a, int f, SeqItem& it, int& c) {
-    const VzRagged& r = a.rag;
-    const int lane = threadIdx.x % vz::kWave;
-    int run = 0;
-    for (int s0 = 0; s0 < r.n && run <= a.nc_max; s0 += vz::kWave) {
-        const int su = min(s0 + lane, r.n - 1);  // load for every lane, mask after
-        const int64_t b = r.base[su];
-        const int cp = r.cap[su], ln = r.len[su], np = r.next_pos[su];
-        const bool ok = s0 + lane < r.n && vz::decode_status_of(b, cp, ln, np, r.total) == VZ_OK;
-        const int n = ok ? (ln + CHUNK) / CHUNK : 0;
-        int incl = n;
-#pragma unroll
-        for (int o = 1; o < vz::kWave; o <<= 1) {
-            const int t = __shfl_up(incl, o, vz::kWave);
-            if (lane >= o) incl += t;
-        }
-        const unsigned long long hit = __ballot(run + incl > f);
-        if (hit) {
-            const int src = __builtin_ctzll(hit);
-            const int nc = __builtin_amdgcn_readfirstlane(__shfl(n, src, vz::kWave));
-            const int first = __builtin_amdgcn_readfirstlane(run + __shfl(incl, src, vz::kWave) - nc);
-            if (first + nc > a.nc_max) return false;
-            it.s = s0 + src;
-            it.len = __builtin_amdgcn_readfirstlane(__shfl(ln, src, vz::kWave));
-            it.next_pos = __builtin_amdgcn_readfirstlane(__shfl(np, src, vz::kWave));
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b), src, vz::kWave));
-            const uint32_t hi = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b >> 32), src, vz::kWave));
-            it.base = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-            it.n_chunks = nc;
-            it.first = first;
-            c = f - first;
-            return true;
-        }
-        run += __builtin_amdgcn_readfirstlane(__shfl(incl, vz::kWave - 1, vz::kWave));
-    }
-    return false;
-}
+using vz::SeqItem;
+using vz::ragged_chunks;
+static_assert(CHUNK == vz::kChunk, "one chunk size");
 
 // Flat chunk f of a call: false when it holds no work.
 template <bool RAG>
 __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem& it, int& c) {
     if constexpr (RAG) {
-        return locate_ragged_chunk(a, f, it, c);
+        return vz::locate_ragged_chunk(a.rag, a.nc_max, f, it, c);
     } else {
         if (f >= a.n_chunks) return false;
         it.s = 0;
@@ -784,14 +731,6 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
     if (t < CHUNK && t < nk) *sc = fmaf(a.gamma, a_old, acc);
 }
 
-// Chunk rows of the partials per layer: ceil(plane / CHUNK) for a single
-// sequence; for a ragged call ceil(plane / CHUNK) + n_seqs, a bound on the
-// sum of ceil((len[s] + 1) / CHUNK) over sequences that lie inside the planes
-// without overlapping.
-int64_t chunk_rows(int64_t plane, int32_t n_seqs) {
-    return (plane + CHUNK - 1) / CHUNK + (n_seqs > 0 ? n_seqs : 0);
-}
-
 template <int NW, bool RAG>
 hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
     FusedArgs a{};
@@ -813,7 +752,7 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
     int seqs = 1;
     if (RAG) {
         a.plane = v.rag.total;
-        a.nc_max = static_cast<int32_t>(chunk_rows(a.plane, v.rag.n));
+        a.nc_max = static_cast<int32_t>(vz_decode_chunk_rows(a.plane, v.rag.n));
         a.n_chunks = a.nc_max;  // grid extent per layer
         seqs = v.rag.n;
     } else {
@@ -821,7 +760,7 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
         a.len = v.len;
         a.next_pos = v.next_pos;
         a.n_chunks = static_cast<int32_t>((static_cast<int64_t>(v.len) + CHUNK) / CHUNK);  // of len + 1 keys
-        a.nc_max = static_cast<int32_t>(chunk_rows(a.plane, 0));
+        a.nc_max = static_cast<int32_t>(vz_decode_chunk_rows(a.plane, 0));
     }
     if (vz_decode_range_ok(a.L, NW, RAG ? v.rag.n : 0)) {
         if (!RAG) {
@@ -859,6 +798,14 @@ hipError_t launch_decode_fused_any(const VzDecodeArgs& v, hipStream_t stream) {
 }  // namespace
 
 // ---- sizing shared with the host API ----
+// Chunk rows of the partials per layer: ceil(plane / CHUNK) for a single
+// sequence; for a ragged call ceil(plane / CHUNK) + n_seqs, a bound on the
+// sum of ceil((len[s] + 1) / CHUNK) over sequences that lie inside the planes
+// without overlapping.
+int64_t vz_decode_chunk_rows(int64_t plane, int32_t n_seqs) {
+    return (plane + CHUNK - 1) / CHUNK + (n_seqs > 0 ? n_seqs : 0);
+}
+
 size_t vz_decode_hdr_bytes(int32_t L) {
     return kHeaderBytes + (static_cast<size_t>(L) * sizeof(uint64_t) + 255) / 256 * 256;
 }
@@ -876,11 +823,11 @@ bool vz_decode_fused_ok(int32_t dtype, int32_t d, int32_t Hq, int32_t Hkv, int32
     if (!(Hkv == 1 || Hkv == 2 || Hkv == 4 || Hkv == 8)) return false;
     if (Hq % Hkv != 0 || Hq / Hkv > GMAX) return false;
     // 32-bit chunk-row indexes of the partials (the attend grid is smaller)
-    return static_cast<int64_t>(L) * chunk_rows(plane, n_seqs) * Hq < (int64_t(1) << 31);
+    return static_cast<int64_t>(L) * vz_decode_chunk_rows(plane, n_seqs) * Hq < (int64_t(1) << 31);
 }
 
 size_t vz_decode_fused_ws_bytes(int32_t L, int32_t Hq, int64_t plane, int32_t n_seqs) {
-    const int64_t rows = chunk_rows(plane, n_seqs);
+    const int64_t rows = vz_decode_chunk_rows(plane, n_seqs);
     const int32_t seqs = n_seqs > 0 ? n_seqs : 1;
     return vz_decode_hdr_bytes(L) + static_cast<size_t>(L) * rows * Hq * (sizeof(float2) + sizeof(uint16_t) * (D + CHUNK)) +
            static_cast<size_t>(seqs) * L * Hq * sizeof(float2);

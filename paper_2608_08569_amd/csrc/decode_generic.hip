@@ -1,27 +1,57 @@
 // Decode step (Sec. 3.1 Eq. 1-2, Sec. 3.2.2 Eq. 6), general path: any group
-// size up to 16, float32 or bfloat16, d in {64, 128}.  Three launches:
+// size up to 16, float32 or bfloat16, d in {64, 128}.  It serves float32
+// caches, head size 64 and the head groups that the bfloat16 d = 128 paths do
+// not take.  Logits, probabilities and every sum are float32 in both element
+// types; keys are handled in chunks of 128 as on the chunked path.
 //
-//   logits   one thread per key: s[l][h][j] = scale * q_h . K[g][j] for the
-//            heads of every KV group (queries staged in LDS); the thread that
-//            owns slot len appends k_new / v_new / next_pos first (it reads the
-//            new key from k_new, so no other thread depends on that write);
-//   combine  one block per (layer, head): max and sum of exp over the logits,
-//            then o = sum_j exp(s_j - m) V[g][j] / sum with D channels x
-//            (256 / D) key lanes;
-//   fold     one thread per key: A[j] = gamma * A[j] + sum_h exp(s_hj - m_h) / l_h.
+//   logits   one workgroup per (layer, KV head, chunk), four waves of 32 keys:
+//            S^T = K Q^T on the matrix cores (16 keys x 16 query heads), the
+//            logits to the workspace, the chunk's max and sum of exp per head;
+//            the workgroup whose chunk holds slot len appends the new row
+//            first and reads it from k_new;
+//   values   one workgroup per (layer, KV head, run of chunks): the sequence's
+//            softmax statistics from the chunks' pairs, p from the logits,
+//            O^T = V^T P^T on the matrix cores and each key's sum over the
+//            group's heads of p, which takes the place of the logits it was
+//            formed from; so does the run's output when there are several;
+//   finish   Eq. (6) from the key sums of the KV heads, and the output rows
+//            from the runs' outputs (not launched when the values kernel has
+//            done both: one KV head and one run).
 //
-// The logits live in the workspace between launches.  This path is the one
-// float32 caches use; bfloat16 caches with d = 128 take the fused MFMA path.
+// Both products stream their rows straight from the cache into the MFMA
+// operand layouts, with no trip through LDS: float32 rows (and float32 p) take
+// v_mfma_f32_16x16x4_f32, bfloat16 keys v_mfma_f32_16x16x32_bf16 (products of
+// bfloat16 are exact in float32); bfloat16 values are widened first, so that p
+// keeps its 24 bits.  At 16 heads the float32 instruction needs about a
+// quarter of its rate to keep up with HBM, so large calls are bound by memory
+// and small ones by the launches and the round trips inside each.  Measured
+// (kernel times, before: one thread per key for the logits, one workgroup per
+// (layer, head) for softmax and P V, one thread per key for the scores):
+//   16 layers, 16Q/4KV, d = 128, float32, 2049 keys   365 -> 39 us (3.5 TB/s)
+//   24 layers, 14Q/2KV, d = 64, bfloat16, 4001 keys   345 -> 27 us (1.8 TB/s)
+//   1 layer, 4Q/1KV, d = 64, float32, 129 keys        22.4 -> 9.4 us
 #include <math.h>
+
+#include <type_traits>
 
 #include "vz_internal.h"
 
 namespace {
 
-constexpr int kThreads = 256;
+using vz::SeqItem;
+using vz::kChunk;
 
-// Arguments shared by the three launches (see the fused path: a
-// single-sequence call has rag.n == 0).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / vz::kWave;
+constexpr int kKeysPerWave = kChunk / kWaves;  // 32: two 16-key tiles
+constexpr int kHeads = 16;                     // head columns of a matrix instruction, and the largest group
+constexpr int kMaxRuns = 64;                   // runs of chunks per sequence
+constexpr int kStatChunks = 128;               // chunks whose pairs the values kernel merges itself
+
+// Arguments of the launches (a single-sequence call has rag.n == 0).
 struct GenericArgs {
     const void* q;
     const void* k_new;
@@ -31,199 +61,452 @@ struct GenericArgs {
     int32_t* pos;
     float* score;
     void* out;
-    float* S;    // logits [L][Hq][plane]
-    float* ml;   // [seqs][L][Hq][2] max and sum of exp per head
-    int32_t len, next_pos;  // single sequence
-    int32_t n_blocks;       // key blocks per layer (grid extent)
+    float* S;        // logits [L][nc_max][Hq][kChunk], then key sums and run outputs in their place
+    float2* ml;      // max and sum of exp per (layer, chunk row, head) [L][nc_max][Hq]
+    float2* layer;   // the same per (sequence, layer, head), for planes of more than kStatChunks chunks
+    int32_t len, next_pos, n_chunks;  // single sequence
+    int32_t nc_max;                   // chunk rows per layer
     int32_t Hq, Hkv, L;
     int64_t plane;
     float scale, gamma;
     VzRagged rag;
 };
 
-__device__ __forceinline__ int ragged_blocks(const VzRagged& r, int s) {
-    return vz::ragged_decode_status(r, s) == VZ_OK ? (r.len[s] + kThreads) / kThreads : 0;
-}
-
-struct SeqKeys {
-    int s, len, next_pos;
-    int64_t base;
-};
-
-// Key block f of a layer: false when it holds no work; c = block inside the sequence.
+// Flat chunk f of a layer: false when it holds no work; c = chunk inside the sequence.
 template <bool RAG>
-__device__ __forceinline__ bool resolve_block(const GenericArgs& a, int f, SeqKeys& it, int& c) {
+__device__ __forceinline__ bool resolve_chunk(const GenericArgs& a, int f, SeqItem& it, int& c) {
     if constexpr (RAG) {
-        int first = 0, nb = 0;
-        const int s = vz::ragged_locate(f, a.rag.n, a.n_blocks, [&](int t) { return ragged_blocks(a.rag, t); },
-                                        first, nb);
-        if (s < 0 || first + nb > a.n_blocks) return false;
-        it.s = s;
-        it.len = a.rag.len[s];
-        it.next_pos = a.rag.next_pos[s];
-        it.base = a.rag.base[s];
-        c = f - first;
+        return vz::locate_ragged_chunk(a.rag, a.nc_max, f, it, c);
     } else {
-        it.s = 0;
-        it.len = a.len;
-        it.next_pos = a.next_pos;
-        it.base = 0;
+        it = SeqItem{0, a.len, a.next_pos, a.n_chunks, 0, 0};
         c = f;
+        return f < a.n_chunks;
     }
-    return true;
 }
+
+// Runs of a sequence of nc chunks: runs of `step` chunks, the last one taking
+// the remainder as well.  A run's output replaces logits of the run's first
+// two chunks, so runs have at least two chunks; with one head per KV head
+// there is no room beside the key sums, and a sequence is one run.
+// (Function of the sequence and the group size alone: a ragged call gives the
+// bits of a single-sequence call.)
+struct Runs {
+    int n, step;
+};
+__host__ __device__ inline Runs runs_of(int nc, int G) {
+    Runs r;
+    r.step = max(2, (nc + kMaxRuns - 1) / kMaxRuns);
+    r.n = G == 1 ? 1 : max(1, nc / r.step);
+    return r;
+}
+
+// Row (layer, chunk row, head) of the workspace arrays.
+__device__ __forceinline__ size_t ws_row(const GenericArgs& a, int l, int chunk_row, int h) {
+    return (static_cast<size_t>(l) * a.nc_max + chunk_row) * a.Hq + h;
+}
+// Run output of head hg of KV head g (first chunk row `row` of the run): heads
+// 1 .. in their own rows of that chunk, head 0 in row 1 of the next one (rows
+// 0 hold the key sums).
+__device__ __forceinline__ float* run_out(const GenericArgs& a, int l, int row, int g, int G, int hg) {
+    return a.S + (hg > 0 ? ws_row(a, l, row, g * G + hg) : ws_row(a, l, row + 1, g * G + 1)) * kChunk;
+}
+
+// Max and sum over the 16 lanes of a DPP row, in every lane (rotations by 8,
+// 4, 2 and 1; each step adds the same two values in both lanes of a pair).
+template <int ROR>
+__device__ __forceinline__ float ror16(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float row16_max(float v) {
+    v = fmaxf(v, ror16<8>(v));
+    v = fmaxf(v, ror16<4>(v));
+    v = fmaxf(v, ror16<2>(v));
+    return fmaxf(v, ror16<1>(v));
+}
+__device__ __forceinline__ float row16_sum(float v) {
+    v += ror16<8>(v);
+    v += ror16<4>(v);
+    v += ror16<2>(v);
+    return v + ror16<1>(v);
+}
+// exp(x - m), 0 for an absent x (-inf, also when m is -inf).
+__device__ __forceinline__ float exp_rel(float x, float m) { return x == -INFINITY ? 0.f : expf(x - m); }
 
 template <int DT, int D, bool RAG>
 __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
     constexpr int PER = E::kPer16B;
-    __shared__ float qs[16 * D];
-    const int l = blockIdx.y;
-    SeqKeys it;
+    constexpr int NV = D / (4 * PER);  // 16-byte pieces of a row per lane: channels 4 PER s + PER q4 ..
+    __shared__ float s_m[kWaves][kHeads], s_l[kWaves][kHeads];
+    const int l = blockIdx.y, g = blockIdx.z;
+    SeqItem it;
     int c;
-    if (!resolve_block<RAG>(a, blockIdx.x, it, c)) return;
-    const int len = it.len;
-    const int T_keys = len + 1;
-    const int j = c * kThreads + threadIdx.x;
-    const int Hq = a.Hq, Hkv = a.Hkv;
-    const int G = Hq / Hkv;
+    if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid / vz::kWave), lane = tid % vz::kWave;
+    const int q4 = lane >> 4, r16 = lane & 15;
+    const int Hq = a.Hq, G = Hq / a.Hkv, len = it.len;
     const size_t row_sl = static_cast<size_t>(it.s) * a.L + l;
-    const T* q = static_cast<const T*>(a.q);
-    const T* k_new = static_cast<const T*>(a.k_new);
-    const T* v_new = static_cast<const T*>(a.v_new);
-    T* k_cache = static_cast<T*>(a.k_cache);
-    T* v_cache = static_cast<T*>(a.v_cache);
+    const size_t head = (static_cast<size_t>(l) * a.Hkv + g) * a.plane + it.base;
+    T* const K = static_cast<T*>(a.k_cache) + head * D;
+    T* const V = static_cast<T*>(a.v_cache) + head * D;
+    const T* const kn = static_cast<const T*>(a.k_new) + (row_sl * a.Hkv + g) * D;
+    const T* const vn = static_cast<const T*>(a.v_new) + (row_sl * a.Hkv + g) * D;
 
-    for (int g = 0; g < Hkv; ++g) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < G * D; i += kThreads)
-            qs[i] = E::load(q, (row_sl * Hq + static_cast<size_t>(g) * G) * D + i);
-        __syncthreads();
-        if (j < T_keys) {
-            const T* krow = (j < len) ? k_cache + ((static_cast<size_t>(l) * Hkv + g) * a.plane + it.base + j) * D
-                                      : k_new + (row_sl * Hkv + g) * D;
-            float acc[16];
+    // rows of the wave's two tiles (past the new one: the new row again, masked)
+    const int k0 = c * kChunk + kKeysPerWave * w;
+    uint4 kr[2][NV], qr[NV];
 #pragma unroll
-            for (int hh = 0; hh < 16; ++hh) acc[hh] = 0.f;
-            for (int c0 = 0; c0 < D; c0 += PER) {
-                float f[PER];
-                vz::unpack16<DT>(*reinterpret_cast<const uint4*>(krow + c0), f);
+    for (int ti = 0; ti < 2; ++ti) {
+        const int key = k0 + 16 * ti + r16;
+        const T* row = key < len ? K + static_cast<size_t>(key) * D : kn;
 #pragma unroll
-                for (int hh = 0; hh < 16; ++hh) {
-                    if (hh < G) {
-#pragma unroll
-                        for (int i = 0; i < PER; ++i) acc[hh] += qs[hh * D + c0 + i] * f[i];
-                    }
-                }
-            }
-#pragma unroll
-            for (int hh = 0; hh < 16; ++hh)
-                if (hh < G) a.S[(static_cast<size_t>(l) * Hq + g * G + hh) * a.plane + it.base + j] = acc[hh] * a.scale;
-        }
+        for (int s = 0; s < NV; ++s) kr[ti][s] = *reinterpret_cast<const uint4*>(row + PER * (4 * s + q4));
     }
-    if (j == len) {  // Eq. (1): append the new row to every KV head of this layer
-        for (int g = 0; g < Hkv; ++g) {
-            const size_t src = (row_sl * Hkv + g) * D;
-            const size_t dst = ((static_cast<size_t>(l) * Hkv + g) * a.plane + it.base + len) * D;
-            for (int c0 = 0; c0 < D; c0 += PER) {
-                *reinterpret_cast<uint4*>(k_cache + dst + c0) = *reinterpret_cast<const uint4*>(k_new + src + c0);
-                *reinterpret_cast<uint4*>(v_cache + dst + c0) = *reinterpret_cast<const uint4*>(v_new + src + c0);
+    {
+        const T* row = static_cast<const T*>(a.q) + (row_sl * Hq + g * G + min(r16, G - 1)) * D;
+#pragma unroll
+        for (int s = 0; s < NV; ++s) __builtin_memcpy(&qr[s], row + PER * (4 * s + q4), 16);  // any element alignment
+    }
+    // Eq. (1): the new row, after this workgroup's loads of the chunk
+    if (c == len / kChunk) {
+        constexpr int CH = D / PER;
+        if (tid < 2 * CH) {
+            const int o = PER * (tid % CH);
+            T* dst = (tid < CH ? K : V) + static_cast<size_t>(len) * D + o;
+            *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>((tid < CH ? kn : vn) + o);
+        }
+        if (g == 0 && tid == 2 * CH) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
+    }
+    if (r16 >= G) {  // unused head columns
+#pragma unroll
+        for (int s = 0; s < NV; ++s) qr[s] = make_uint4(0, 0, 0, 0);
+    }
+    float* const S = a.S + ws_row(a, l, it.first + c, g * G + r16) * kChunk + kKeysPerWave * w;
+    float sv[2][4], m_w = -INFINITY;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NV; ++s) {
+            if constexpr (DT == VZ_F32) {
+                const float kf[4] = {__uint_as_float(kr[ti][s].x), __uint_as_float(kr[ti][s].y),
+                                     __uint_as_float(kr[ti][s].z), __uint_as_float(kr[ti][s].w)};
+                const float qf[4] = {__uint_as_float(qr[s].x), __uint_as_float(qr[s].y), __uint_as_float(qr[s].z),
+                                     __uint_as_float(qr[s].w)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[i], acc, 0, 0, 0);
+            } else {
+                bf16x8_t kf, qf;
+                __builtin_memcpy(&kf, &kr[ti][s], 16);
+                __builtin_memcpy(&qf, &qr[s], 16);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf, acc, 0, 0, 0);
             }
         }
-        a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
+        // lane: head r16, keys 16 ti + 4 q4 + i
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sv[ti][i] = k0 + 16 * ti + 4 * q4 + i <= len ? acc[i] * a.scale : -INFINITY;
+            m_w = fmaxf(m_w, sv[ti][i]);
+        }
+        if (r16 < G)
+            *reinterpret_cast<float4*>(S + 16 * ti + 4 * q4) = make_float4(sv[ti][0], sv[ti][1], sv[ti][2], sv[ti][3]);
+    }
+    m_w = fmaxf(m_w, __shfl_xor(m_w, 16, vz::kWave));
+    m_w = fmaxf(m_w, __shfl_xor(m_w, 32, vz::kWave));
+    float l_w = 0.f;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l_w += exp_rel(sv[ti][i], m_w);
+    l_w += __shfl_xor(l_w, 16, vz::kWave);
+    l_w += __shfl_xor(l_w, 32, vz::kWave);
+    if (q4 == 0) {
+        s_m[w][r16] = m_w;
+        s_l[w][r16] = l_w;
+    }
+    __syncthreads();
+    if (tid < G) {
+        float m = s_m[0][tid], z = 0.f;
+#pragma unroll
+        for (int v = 1; v < kWaves; ++v) m = fmaxf(m, s_m[v][tid]);
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v) z = fmaf(s_l[v][tid], exp_rel(s_m[v][tid], m), z);
+        a.ml[ws_row(a, l, it.first + c, g * G + tid)] = make_float2(m, z);
     }
 }
 
-__device__ float block_reduce(float v, bool is_max, float* red) {
-    v = is_max ? vz::wave_max(v) : vz::wave_sum(v);
-    const int w = threadIdx.x / vz::kWave;
-    __syncthreads();
-    if ((threadIdx.x % vz::kWave) == 0) red[w] = v;
-    __syncthreads();
-    float r = red[0];
-    for (int i = 1; i < kThreads / vz::kWave; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
-    return r;
+// Max and sum of exp of one head over nc chunks, by 16 neighbouring lanes
+// (lane i takes chunks i, i + 16, ...): ml points at the head's pair of chunk
+// 0.  Up to kStatChunks chunks: eight pairs per lane, all loaded (indexes
+// clamped) before any is used.
+constexpr int kStatPairs = kStatChunks / 16;
+__device__ __forceinline__ void load_pairs(const float2* ml, int nc, int Hq, int c0, float2 (&p)[kStatPairs]) {
+#pragma unroll
+    for (int k = 0; k < kStatPairs; ++k) p[k] = ml[static_cast<size_t>(min(c0 + 16 * k, nc - 1)) * Hq];
+}
+__device__ __forceinline__ float2 merge_pairs(float2 (&p)[kStatPairs], int nc, int i) {
+    float m = -INFINITY, z = 0.f;
+#pragma unroll
+    for (int k = 0; k < kStatPairs; ++k) {
+        p[k].x = i + 16 * k < nc ? p[k].x : -INFINITY;
+        m = fmaxf(m, p[k].x);
+    }
+    m = row16_max(m);
+#pragma unroll
+    for (int k = 0; k < kStatPairs; ++k) z = fmaf(p[k].x == -INFINITY ? 0.f : p[k].y, exp_rel(p[k].x, m), z);
+    return make_float2(m, row16_sum(z));
+}
+// Any number of chunks (the same order of additions).
+__device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int Hq, int i) {
+    float2 p[kStatPairs];
+    float m = -INFINITY, z = 0.f;
+    for (int c0 = i; c0 - i < nc; c0 += kStatChunks) {
+        load_pairs(ml, nc, Hq, c0, p);
+#pragma unroll
+        for (int k = 0; k < kStatPairs; ++k) m = fmaxf(m, p[k].x);  // a clamped pair is one of the head's own
+    }
+    m = row16_max(m);
+    for (int c0 = i; c0 - i < nc; c0 += kStatChunks) {
+        load_pairs(ml, nc, Hq, c0, p);
+#pragma unroll
+        for (int k = 0; k < kStatPairs; ++k) z = fmaf(c0 + 16 * k < nc ? p[k].y : 0.f, exp_rel(p[k].x, m), z);
+    }
+    return make_float2(m, row16_sum(z));
 }
 
-// One block per (head, layer, sequence); in a ragged call also stores the
-// sequence's status.
-template <int DT, int D, bool RAG>
-__global__ __launch_bounds__(kThreads) void combine_kernel(const GenericArgs a) {
-    using E = vz::Elem<DT>;
-    constexpr int JL = kThreads / D;
-    __shared__ float red[kThreads / vz::kWave];
-    __shared__ float part[kThreads];
-    const int h = blockIdx.x, l = blockIdx.y;
-    int s = 0, len = a.len;
-    int64_t base = 0;
+// Statistics of every head of a (sequence, layer), once, for calls whose
+// planes hold more than kStatChunks chunks (where merging them in every
+// workgroup of the values kernel would read chunks x runs pairs).
+template <bool RAG>
+__global__ __launch_bounds__(kThreads) void stats_kernel(const GenericArgs a) {
+    const int l = blockIdx.y, s = blockIdx.z;
+    int first = 0, nc = a.n_chunks;
     if constexpr (RAG) {
-        s = blockIdx.z;
-        const int st = vz::ragged_decode_status(a.rag, s);
-        int ok = st == VZ_OK;
-        if (ok) {
-            const int first = vz::ragged_first(s, a.n_blocks, [&](int t) { return ragged_blocks(a.rag, t); });
-            ok = first >= 0 && first + ragged_blocks(a.rag, s) <= a.n_blocks;
+        nc = vz::ragged_chunks(a.rag, s);
+        first = vz::ragged_first(s, a.nc_max, [&](int u) { return vz::ragged_chunks(a.rag, u); });
+        if (nc == 0 || first < 0 || first + nc > a.nc_max) return;
+    }
+    const int h = blockIdx.x * (kThreads / 16) + threadIdx.x / 16, i = threadIdx.x % 16;
+    const float2 st = merge_all(a.ml + ws_row(a, l, first, min(h, a.Hq - 1)), nc, a.Hq, i);
+    if (i == 0 && h < a.Hq) a.layer[(static_cast<size_t>(s) * a.L + l) * a.Hq + h] = st;
+}
+
+// Values of a row piece (four or eight channels of one key) as floats.
+template <int DT, int PER>
+__device__ __forceinline__ void widen(const uint32_t* x, float* f) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if constexpr (DT == VZ_F32) f[i] = __uint_as_float(x[i]);
+        else f[i] = __uint_as_float((i & 1) ? x[i / 2] & 0xFFFF0000u : x[i / 2] << 16);
+    }
+}
+
+template <int DT, int D, bool RAG>
+__global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
+    using E = vz::Elem<DT>;
+    using T = typename E::T;
+    // Lane (q4, r16) loads channels PER r16 .. + PER - 1 (of each of NP
+    // pieces of a row) of keys 4 q4 + i: component e of piece j is row r16 of
+    // the A operand of output tile PER j + e, key 4 q4 + i its column q4.
+    constexpr int PER = DT == VZ_F32 ? 4 : D / 16;
+    constexpr int NP = D / (16 * PER);
+    constexpr int NT = D / 16;                          // output tiles
+    constexpr int WORDS = PER * sizeof(T) / 4;
+    constexpr int DEPTH = NP * WORDS >= 8 ? 2 : 4;      // tiles in flight per wave (32 or 16 registers each, or 8)
+    __shared__ float s_o[kWaves][kHeads][D + 4];
+    __shared__ float2 s_stat[kHeads];
+    const int l = blockIdx.y, g = blockIdx.z;
+    const int Hq = a.Hq, G = Hq / a.Hkv;
+    SeqItem it;
+    int c0, run;
+    Runs rn;
+    if constexpr (RAG) {
+        // grid over chunk rows: the first chunk of each run works
+        if (!resolve_chunk<true>(a, blockIdx.x, it, c0)) return;
+        rn = runs_of(it.n_chunks, G);
+        run = c0 / rn.step;
+        if (run >= rn.n || c0 != run * rn.step) return;
+    } else {
+        resolve_chunk<false>(a, 0, it, c0);
+        rn = runs_of(it.n_chunks, G);
+        run = blockIdx.x;
+        c0 = run * rn.step;
+    }
+    const int nch = (run == rn.n - 1 ? it.n_chunks : c0 + rn.step) - c0;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid / vz::kWave), lane = tid % vz::kWave;
+    const int q4 = lane >> 4, r16 = lane & 15;
+    const int len = it.len;
+    const size_t row_sl = static_cast<size_t>(it.s) * a.L + l;
+    const T* const V =
+        static_cast<const T*>(a.v_cache) + ((static_cast<size_t>(l) * a.Hkv + g) * a.plane + it.base) * D;
+    float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base;
+    const bool fold = a.Hkv == 1;  // one KV head: its key sums are the whole of Eq. (6)'s
+
+    // 16-key tile x of the wave: keys 32 w + 16 (x % 2) .. of chunk c0 + x / 2
+    struct Tile {
+        float4 s;
+        uint32_t v[4][NP][WORDS];
+        float a;  // the old score of key 4 q4 + r16 (r16 < 4), for the fold
+    };
+    auto tile_key = [&](int x) { return (c0 + x / 2) * kChunk + kKeysPerWave * w + 16 * (x % 2); };
+    const int v_off = 4 * q4 * D + PER * r16;                    // lane offsets inside a tile
+    const int s_off = min(r16, G - 1) * kChunk + 4 * q4;
+    auto load = [&](int x, Tile& t) {
+        const int k0 = tile_key(x);
+        const float* sr = a.S + ws_row(a, l, it.first + c0 + x / 2, g * G) * kChunk + k0 % kChunk;
+        t.s = *reinterpret_cast<const float4*>(sr + s_off);
+        if (k0 + 15 <= len) {  // wave-uniform
+            const T* vr = V + static_cast<size_t>(k0) * D;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < NP; ++j) __builtin_memcpy(t.v[i][j], vr + v_off + i * D + 16 * PER * j, WORDS * 4);
+            t.a = sc[k0 + 4 * q4 + (r16 & 3)];
+        } else {  // rows past the new one: that row again, masked later
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T* vr = V + static_cast<size_t>(min(k0 + 4 * q4 + i, len)) * D + PER * r16;
+#pragma unroll
+                for (int j = 0; j < NP; ++j) __builtin_memcpy(t.v[i][j], vr + 16 * PER * j, WORDS * 4);
+            }
+            t.a = sc[min(k0 + 4 * q4 + (r16 & 3), len)];
         }
-        if (a.rag.status && h == 0 && l == 0 && threadIdx.x == 0)
+    };
+    const int n_tiles = 2 * nch;
+    Tile tile[DEPTH];
+    // the statistics' loads first, then the first tiles (behind them, so that
+    // the statistics do not wait for the tiles)
+    const bool own_stats = (a.plane + kChunk - 1) / kChunk <= kStatChunks;
+    const int hs = min(tid / 16, G - 1);  // 16 lanes per head
+    float2 pr[kStatPairs];
+    if (own_stats) load_pairs(a.ml + ws_row(a, l, it.first, g * G + hs), it.n_chunks, Hq, tid % 16, pr);
+    else pr[0] = a.layer[row_sl * Hq + g * G + hs];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u)
+        load(min(u, n_tiles - 1), tile[u]);
+    __builtin_amdgcn_sched_barrier(0);
+
+    {
+        const float2 st = own_stats ? merge_pairs(pr, it.n_chunks, tid % 16) : pr[0];
+        if (tid % 16 == 0) s_stat[tid / 16] = st;
+    }
+    __syncthreads();
+    const float M = s_stat[r16].x, inv_Z = 1.0f / s_stat[r16].y;
+
+    f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto use = [&](int x, const Tile& cur, auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;  // keys past the new one: no p, and no value times a p of 0
+        const int k0 = tile_key(x);
+        float e[4] = {cur.s.x, cur.s.y, cur.s.z, cur.s.w};
+        float ks[4];
+        bool on[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            on[i] = !TAIL || k0 + 4 * q4 + i <= len;
+            e[i] = r16 < G && on[i] ? expf(e[i] - M) : 0.f;
+            ks[i] = e[i] * inv_Z;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                float f[PER];
+                widen<DT, PER>(cur.v[i][j], f);
+#pragma unroll
+                for (int k = 0; k < PER; ++k)
+                    acc[PER * j + k] =
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(on[i] ? f[k] : 0.f, e[i], acc[PER * j + k], 0, 0, 0);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ks[i] = row16_sum(ks[i]);
+        if (r16 < 4) {
+            const float sum = r16 == 0 ? ks[0] : r16 == 1 ? ks[1] : r16 == 2 ? ks[2] : ks[3];
+            const int key = k0 + 4 * q4 + r16;
+            if (fold) {
+                if (key <= len) sc[key] = fmaf(a.gamma, key < len ? cur.a : 0.f, sum);
+            } else {
+                // (the logits of these keys are in registers: only this wave reads them)
+                a.S[ws_row(a, l, it.first + c0 + x / 2, g * G) * kChunk + key % kChunk] = sum;
+            }
+        }
+    };
+    for (int x = 0; x < n_tiles; x += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            if (x + u < n_tiles) {
+                if (tile_key(x + u) + 15 <= len) use(x + u, tile[u], std::false_type{});
+                else if (tile_key(x + u) <= len) use(x + u, tile[u], std::true_type{});
+            }
+            if (x + u + DEPTH < n_tiles) load(x + u + DEPTH, tile[u]);
+        }
+    }
+    // ---- the four waves' outputs, added in wave order ----
+    // row 4 q4 + i of tile PER j + k: channel 16 PER j + PER (4 q4 + i) + k
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            s_o[w][r16][16 * PER * (t / PER) + PER * (4 * q4 + i) + t % PER] = acc[t][i];
+    __syncthreads();  // ... and every logit of the run has been read
+    for (int x = tid; x < G * D; x += kThreads) {
+        const int h = x / D, ch = x % D;
+        float o = s_o[0][h][ch];
+#pragma unroll
+        for (int v = 1; v < kWaves; ++v) o += s_o[v][h][ch];
+        o /= s_stat[h].y;
+        if (rn.n == 1)
+            static_cast<T*>(a.out)[(row_sl * Hq + g * G + h) * D + ch] = E::from_f32(o);
+        else
+            run_out(a, l, it.first + c0, g, G, h)[ch] = o;
+    }
+}
+
+// Fold blocks [0, fold_blocks) of a layer: one chunk's scores, thread = key.
+// The blocks after them: one (head, sequence)'s output row from its runs, and
+// in a ragged call the sequence's status.
+template <int DT, int D, bool RAG>
+__global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int fold_blocks) {
+    using E = vz::Elem<DT>;
+    const int l = blockIdx.y, t = threadIdx.x;
+    const int Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
+    SeqItem it;
+    if (static_cast<int>(blockIdx.x) < fold_blocks) {
+        int c;
+        if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
+        const int key = c * kChunk + t;
+        if (key > it.len) return;
+        float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base + key;
+        const float old = *sc;
+        float sum = 0.f;
+#pragma unroll 4
+        for (int g = 0; g < Hkv; ++g) sum += a.S[ws_row(a, l, it.first + c, g * G) * kChunk + t];
+        *sc = fmaf(a.gamma, key < it.len ? old : 0.f, sum);  // zero pad of Eq. (6) for the new slot
+        return;
+    }
+    const int ob = static_cast<int>(blockIdx.x) - fold_blocks, h = ob % Hq, s = ob / Hq;
+    int first = 0, nc = a.n_chunks;
+    if constexpr (RAG) {
+        const int st = vz::ragged_decode_status(a.rag, s);
+        nc = vz::ragged_chunks(a.rag, s);
+        first = vz::ragged_first(s, a.nc_max, [&](int u) { return vz::ragged_chunks(a.rag, u); });
+        const bool ok = st == VZ_OK && first >= 0 && first + nc <= a.nc_max;
+        if (a.rag.status && h == 0 && l == 0 && t == 0)
             a.rag.status[s] = ok ? VZ_OK : (st != VZ_OK ? st : VZ_ERR_CAPACITY);
         if (!ok) return;
-        len = a.rag.len[s];
-        base = a.rag.base[s];
     }
-    const int Hq = a.Hq;
-    const int T_keys = len + 1;
-    const int g = h / (Hq / a.Hkv);
-    const float* sv = a.S + (static_cast<size_t>(l) * Hq + h) * a.plane + base;
-    const size_t row_sl = static_cast<size_t>(s) * a.L + l;
-
-    float m = -INFINITY;
-    for (int j = threadIdx.x; j < T_keys; j += kThreads) m = fmaxf(m, sv[j]);
-    m = block_reduce(m, true, red);
-    float z = 0.f;
-    for (int j = threadIdx.x; j < T_keys; j += kThreads) z += expf(sv[j] - m);
-    z = block_reduce(z, false, red);
-    if (threadIdx.x == 0) {
-        a.ml[(row_sl * Hq + h) * 2] = m;
-        a.ml[(row_sl * Hq + h) * 2 + 1] = z;
-    }
-    const int c = threadIdx.x % D, jl = threadIdx.x / D;
-    const typename E::T* V =
-        static_cast<const typename E::T*>(a.v_cache) + ((static_cast<size_t>(l) * a.Hkv + g) * a.plane + base) * D;
-    float acc = 0.f;
-    for (int j = jl; j < T_keys; j += JL) acc += expf(sv[j] - m) * E::load(V, static_cast<size_t>(j) * D + c);
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    if (jl == 0) {
-        float t = part[c];
-        for (int i = 1; i < JL; ++i) t += part[i * D + c];
-        static_cast<typename E::T*>(a.out)[(row_sl * Hq + h) * D + c] = E::from_f32(t / z);
-    }
-}
-
-template <bool RAG>
-__global__ __launch_bounds__(kThreads) void fold_kernel(const GenericArgs a) {
-    __shared__ float mls[2 * 256];
-    const int l = blockIdx.y;
-    SeqKeys it;
-    int c;
-    if (!resolve_block<RAG>(a, blockIdx.x, it, c)) return;
-    const int Hq = a.Hq;
-    const size_t row_sl = static_cast<size_t>(it.s) * a.L + l;
-    for (int i = threadIdx.x; i < 2 * Hq; i += kThreads) mls[i] = a.ml[row_sl * Hq * 2 + i];
-    __syncthreads();
-    const int len = it.len;
-    const int j = c * kThreads + threadIdx.x;
-    if (j > len) return;
-    float* sc = a.score + static_cast<size_t>(l) * a.plane + it.base;
-    float acc = (j < len) ? a.gamma * sc[j] : 0.f;
-    for (int h = 0; h < Hq; ++h)
-        acc += expf(a.S[(static_cast<size_t>(l) * Hq + h) * a.plane + it.base + j] - mls[2 * h]) / mls[2 * h + 1];
-    sc[j] = acc;
-}
-
-int64_t key_blocks(int64_t plane, int32_t n_seqs) {
-    return n_seqs > 0 ? (plane + kThreads - 1) / kThreads + n_seqs : (plane + kThreads - 1) / kThreads;
+    const Runs rn = runs_of(nc, G);
+    if (rn.n == 1 || t >= D) return;
+    const int g = h / G, hg = h % G;
+    float o = 0.f;
+#pragma unroll 8
+    for (int r = 0; r < rn.n; ++r) o += run_out(a, l, first + r * rn.step, g, G, hg)[t];
+    static_cast<typename E::T*>(a.out)[((static_cast<size_t>(s) * a.L + l) * Hq + h) * D + t] = E::from_f32(o);
 }
 
 template <int DT, int D, bool RAG>
@@ -241,28 +524,37 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
     a.Hkv = v.Hkv;
     a.L = v.L;
     a.plane = RAG ? v.rag.total : v.cap;
+    a.nc_max = static_cast<int32_t>(vz_decode_chunk_rows(a.plane, v.rag.n));
+    const size_t rows = static_cast<size_t>(v.L) * a.nc_max * v.Hq;
     a.S = reinterpret_cast<float*>(static_cast<uint8_t*>(v.ws) + vz_decode_hdr_bytes(v.L));
-    a.ml = a.S + static_cast<size_t>(v.L) * v.Hq * a.plane;
+    a.ml = reinterpret_cast<float2*>(a.S + rows * kChunk);
+    a.layer = a.ml + rows;
     a.scale = v.sm_scale > 0.f ? v.sm_scale : 1.0f / sqrtf(static_cast<float>(D));
     a.gamma = v.gamma;
     a.rag = v.rag;
-    int seqs = 1;
-    if (RAG) {
-        a.n_blocks = static_cast<int32_t>(key_blocks(v.rag.total, v.rag.n));
-        seqs = v.rag.n;
-    } else {
+    const int G = v.Hq / v.Hkv, seqs = RAG ? v.rag.n : 1;
+    int chunks = a.nc_max, runs = a.nc_max;  // grid extents per layer and KV head
+    if (!RAG) {
         a.len = v.len;
         a.next_pos = v.next_pos;
-        a.n_blocks = (v.len + kThreads) / kThreads;
+        a.n_chunks = chunks = v.len / kChunk + 1;  // of len + 1 keys
+        runs = runs_of(chunks, G).n;
     }
-    dim3 gk(a.n_blocks, a.L);
-    hipLaunchKernelGGL((logits_kernel<DT, D, RAG>), gk, dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((logits_kernel<DT, D, RAG>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((combine_kernel<DT, D, RAG>), dim3(a.Hq, a.L, seqs), dim3(kThreads), 0, stream, a);
+    if ((a.plane + kChunk - 1) / kChunk > kStatChunks) {
+        hipLaunchKernelGGL((stats_kernel<RAG>), dim3((a.Hq + 15) / 16, a.L, seqs), dim3(kThreads), 0, stream, a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((values_kernel<DT, D, RAG>), dim3(runs, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fold_kernel<RAG>), gk, dim3(kThreads), 0, stream, a);
+    const int folds = a.Hkv > 1 ? chunks : 0;  // one KV head: folded by the values kernel
+    const int outs = RAG || runs > 1 ? a.Hq * seqs : 0;
+    if (folds + outs == 0) return hipSuccess;
+    hipLaunchKernelGGL((finish_kernel<DT, D, RAG>), dim3(folds + outs, a.L), dim3(kChunk), 0, stream, a, folds);
     return hipGetLastError();
 }
 
@@ -272,16 +564,6 @@ hipError_t launch_any(const VzDecodeArgs& v, hipStream_t stream) {
 }
 
 }  // namespace
-
-bool vz_decode_generic_ok(int64_t plane, int32_t n_seqs) {
-    return key_blocks(plane, n_seqs) < (int64_t(1) << 31);  // grid x
-}
-
-size_t vz_decode_generic_ws_bytes(int32_t L, int32_t Hq, int64_t plane, int32_t n_seqs) {
-    const int32_t seqs = n_seqs > 0 ? n_seqs : 1;
-    return vz_decode_hdr_bytes(L) +
-           (static_cast<size_t>(L) * Hq * plane + static_cast<size_t>(seqs) * L * Hq * 2) * sizeof(float);
-}
 
 hipError_t vz_launch_decode_generic(const VzDecodeArgs& a, hipStream_t stream) {
     if (a.dtype == VZ_BF16 && a.d == 128) return launch_any<VZ_BF16, 128>(a, stream);

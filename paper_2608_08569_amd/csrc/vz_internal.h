@@ -151,19 +151,38 @@ __device__ __forceinline__ int ragged_decode_status(const VzRagged& r, int s) {
     return decode_status_of(r.base[s], r.cap[s], r.len[s], r.next_pos[s], r.total);
 }
 
-// Flat work items of a ragged batch: sequence s contributes count(s) >= 0
-// consecutive items, in sequence order.  Called by a whole wave (every lane
-// gets the same result, wave-uniform).  Returns the sequence holding flat item
-// f, with its first flat item and its item count, or -1 when f lies past
-// `limit` items or past the last one.  count() must return at most 2^24.
-template <class Count>
-__device__ int ragged_locate(int f, int n_seqs, int limit, Count count, int& first, int& nc) {
+// Keys are handled in chunks of kChunk by the decode paths that keep per-chunk
+// results in the workspace.
+constexpr int kChunk = 128;
+
+// Chunks of sequence s in a ragged call (0 when it cannot be served).
+__device__ __forceinline__ int ragged_chunks(const VzRagged& r, int s) {
+    return ragged_decode_status(r, s) == VZ_OK ? (r.len[s] + kChunk) / kChunk : 0;
+}
+
+// The sequence a work item belongs to, resolved at the top of every kernel.
+struct SeqItem {
+    int s;           // sequence (0 for a single-sequence call)
+    int len, next_pos;
+    int n_chunks;    // chunks of the sequence
+    int first;       // its first chunk row in the workspace
+    int64_t base;    // its first slot in the planes
+};
+
+// Flat chunk f of a ragged call, found by a whole wave: each lane loads one
+// sequence's values (64 sequences per round), a wave scan of their chunk
+// counts finds the owner of f, and the owner's values are forwarded from the
+// lane that loaded them, so the kernel waits for one round of loads.  False
+// when f lies past the call's chunks (or past the nc_max rows).
+__device__ __forceinline__ bool locate_ragged_chunk(const VzRagged& r, int nc_max, int f, SeqItem& it, int& c) {
     const int lane = threadIdx.x % kWave;
     int run = 0;
-    for (int s0 = 0; s0 < n_seqs && run <= limit; s0 += kWave) {
-        const int s = s0 + lane;
-        const int n0 = count(s < n_seqs ? s : n_seqs - 1);  // load for every lane, mask after
-        const int n = s < n_seqs ? n0 : 0;
+    for (int s0 = 0; s0 < r.n && run <= nc_max; s0 += kWave) {
+        const int su = min(s0 + lane, r.n - 1);  // load for every lane, mask after
+        const int64_t b = r.base[su];
+        const int cp = r.cap[su], ln = r.len[su], np = r.next_pos[su];
+        const bool ok = s0 + lane < r.n && decode_status_of(b, cp, ln, np, r.total) == VZ_OK;
+        const int n = ok ? (ln + kChunk) / kChunk : 0;
         int incl = n;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -173,17 +192,28 @@ __device__ int ragged_locate(int f, int n_seqs, int limit, Count count, int& fir
         const unsigned long long hit = __ballot(run + incl > f);
         if (hit) {
             const int src = __builtin_ctzll(hit);
-            nc = __builtin_amdgcn_readfirstlane(__shfl(n, src, kWave));
-            first = __builtin_amdgcn_readfirstlane(run + __shfl(incl, src, kWave) - nc);
-            return __builtin_amdgcn_readfirstlane(s0 + src);
+            const int nc = __builtin_amdgcn_readfirstlane(__shfl(n, src, kWave));
+            const int first = __builtin_amdgcn_readfirstlane(run + __shfl(incl, src, kWave) - nc);
+            if (first + nc > nc_max) return false;
+            it.s = s0 + src;
+            it.len = __builtin_amdgcn_readfirstlane(__shfl(ln, src, kWave));
+            it.next_pos = __builtin_amdgcn_readfirstlane(__shfl(np, src, kWave));
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b), src, kWave));
+            const uint32_t hi = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b >> 32), src, kWave));
+            it.base = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+            it.n_chunks = nc;
+            it.first = first;
+            c = f - first;
+            return true;
         }
-        run += __shfl(incl, kWave - 1, kWave);
+        run += __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
     }
-    return -1;
+    return false;
 }
 
-// First flat item of sequence t (items as in ragged_locate), or -1 when it
-// lies past `limit`.  Called by a whole wave.
+// First flat item of sequence t when sequence s contributes count(s) >= 0
+// consecutive items, in sequence order, or -1 when it lies past `limit`.
+// Called by a whole wave (every lane gets the same result).
 template <class Count>
 __device__ int ragged_first(int t, int limit, Count count) {
     const int lane = threadIdx.x % kWave;
@@ -257,10 +287,12 @@ size_t vz_decode_ws_bytes(int32_t L, int32_t Hq, int32_t Hkv, int32_t d, int64_t
 // path-specific scratch
 size_t vz_decode_hdr_bytes(int32_t L);
 bool vz_decode_fused_ok(int32_t dtype, int32_t d, int32_t Hq, int32_t Hkv, int32_t L, int64_t plane, int32_t n_seqs);
+// Workspace of the chunked path and of the general path (the same layout of
+// rows: per (layer, chunk row, query head) one float2 and 512 bytes).
 size_t vz_decode_fused_ws_bytes(int32_t L, int32_t Hq, int64_t plane, int32_t n_seqs);
+// Chunk rows per layer of either path's workspace.
+int64_t vz_decode_chunk_rows(int64_t plane, int32_t n_seqs);
 hipError_t vz_launch_decode_fused(const VzDecodeArgs& a, hipStream_t stream);
-bool vz_decode_generic_ok(int64_t plane, int32_t n_seqs);
-size_t vz_decode_generic_ws_bytes(int32_t L, int32_t Hq, int64_t plane, int32_t n_seqs);
 hipError_t vz_launch_decode_generic(const VzDecodeArgs& a, hipStream_t stream);
 hipError_t vz_launch_decode(const VzDecodeArgs& a, hipStream_t stream);
 // Whole-range decode path (single sequence): whether a call takes it.
