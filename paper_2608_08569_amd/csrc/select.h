@@ -10,8 +10,12 @@
 //      them are evicted: the E smallest keys.
 //   2. The E-th smallest key is found either by E rounds of a block-wide
 //      minimum over keys above the previous one (small E, the steady state of
-//      one eviction per step), or by an MSB-first radix select with 8-bit
-//      digits and an LDS histogram (large E, e.g. the first eviction).
+//      one eviction per step), or by an MSB-first radix select with 11-bit
+//      digits and an LDS histogram (large E, e.g. the first eviction): the
+//      first digit then holds a score's exponent and three bits of its
+//      mantissa, so scores of any spread reach many bins (8-bit digits put
+//      most of a layer into a handful of bins, whose LDS atomics serialise),
+//      and two or three digits settle the threshold.
 //   3. Evicted slots below `budget` are holes; kept slots at or above it are
 //      movers.  The k-th mover fills the k-th hole, both in slot order.
 //      Sources and destinations are disjoint, so the moves need no ordering
@@ -31,6 +35,8 @@ constexpr int kSmallE = 8;          // up to this many evictions: rounds of bloc
 constexpr int kInlineRows = 256;    // up to this many moved slots: K/V copied by the select block
 constexpr int kBitmapWords = 8192;  // kept-position bitmap: 2^18 positions
 constexpr uint64_t kNoKey = ~0ull;  // LDS key of a slot that does not compete
+constexpr int kDigit = 11;          // bits per digit of the radix select
+constexpr int kBins = 1 << kDigit;
 
 // Block-shared state of a selection by NT threads.  NKEYS > 0: the rank keys
 // of up to NKEYS slots live in LDS (kNoKey for sinks and recent slots), and
@@ -44,7 +50,7 @@ struct SelShared {
     uint64_t red64[NT / vz::kWave];
     int red_a[NT / vz::kWave];
     int red_b[NT / vz::kWave];
-    uint32_t hist[256];
+    uint32_t hist[kBins];
     uint64_t prefix;
     int krem;
     int cnt;
@@ -140,8 +146,10 @@ struct SelJob {
     int32_t first_best_j;
 };
 
-// LK: this layer's keys are kept in LDS (needs sh.keys and len <= kLdsSlots
-// and inline_kv).  READY: the caller has already filled sh.keys (and passed a
+// LK: this layer's keys are kept in LDS (needs sh.keys and len <= SH::kKeys).
+// inline_kv (at most kInlineRows evictions): the move lists are in LDS too
+// (with LK) and the K/V rows move here; otherwise the lists go to src_g and
+// dst_g for the copy kernel.  READY: the caller has already filled sh.keys (and passed a
 // barrier) and passes each thread's smallest key; only with LK.  With one
 // eviction the keys are never read back, so such a caller may leave them out.
 // move_fn(n_moves, src, dst), when given, may perform the moves itself (and
@@ -207,6 +215,31 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
         k = vz::rank_key(A[j], p);
         return true;
     };
+    // fn(slot, key) for every competing slot of this thread (tid, tid + NT,
+    // ...).  From memory: eight slots' loads at once (indexes clamped).
+    auto for_keys = [&](auto fn) {
+        if constexpr (LK) {
+            for (int j = tid; j < len; j += NT) {
+                const uint64_t k = s_keys[j];
+                if (k != kNoKey) fn(j, k);
+            }
+        } else {
+            constexpr int B = 8;
+            for (int j0 = tid; j0 < len; j0 += B * NT) {
+                int32_t pv[B];
+                float av[B];
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const int j = min(j0 + b * NT, len - 1);
+                    pv[b] = P[j];
+                    av[b] = A[j];
+                }
+#pragma unroll
+                for (int b = 0; b < B; ++b)
+                    if (j0 + b * NT < len && is_mid(pv[b])) fn(j0 + b * NT, vz::rank_key(av[b], pv[b]));
+            }
+        }
+    };
 
     // ---- threshold: evict middle slots whose key >> shift <= thr >> shift ----
     uint64_t thr = 0;
@@ -221,14 +254,12 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
                 best = job.first_best;
                 best_j = job.first_best_j;
             } else {
-                for (int j = tid; j < len; j += NT) {
-                    uint64_t k;
-                    if (!key_at(j, k)) continue;
+                for_keys([&](int j, uint64_t k) {
                     if (k > tau && k < best) {
                         best = k;
                         best_j = j;
                     }
-                }
+                });
             }
             tau = block_min_u64<NT>(best, sh);
             if (tau == ~0ull) break;  // fewer middle slots than E
@@ -281,56 +312,51 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
             lds_barrier();
         }
     } else if (E > kSmallE) {
+        constexpr int BPT = kBins / NT;  // bins per thread
+        static_assert(BPT * NT == kBins, "whole bins per thread");
         uint64_t prefix = 0;
         int krem = E;
-        for (int s = 56;; s -= 8) {
-            if (tid < 256) sh.hist[tid] = 0;
+        for (int top = 64;;) {  // bits [top, 64) are settled
+            const int s = top > kDigit ? top - kDigit : 0;
+#pragma unroll
+            for (int i = 0; i < BPT; ++i) sh.hist[tid * BPT + i] = 0;
             __syncthreads();
-            for (int j = tid; j < len; j += NT) {
-                uint64_t k;
-                if (!key_at(j, k)) continue;
-                if (s == 56 || (k >> (s + 8)) == (prefix >> (s + 8)))
-                    atomicAdd(&sh.hist[(k >> s) & 255u], 1u);
+            const uint32_t mask = (1u << (top - s)) - 1;
+            for_keys([&](int, uint64_t k) {
+                if (top == 64 || (k >> top) == (prefix >> top))
+                    atomicAdd(&sh.hist[static_cast<uint32_t>(k >> s) & mask], 1u);
+            });
+            __syncthreads();
+            // the bin holding the krem-th smallest candidate: one thread's run of bins
+            int c[BPT], sum = 0;
+#pragma unroll
+            for (int i = 0; i < BPT; ++i) {
+                c[i] = static_cast<int>(sh.hist[tid * BPT + i]);
+                sum += c[i];
             }
-            __syncthreads();
-            if (tid < vz::kWave) {  // wave 0 finds the bin holding the krem-th smallest candidate
-                int c4[4], sum = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    c4[i] = static_cast<int>(sh.hist[tid * 4 + i]);
-                    sum += c4[i];
+            int excl, unused, total, unused_total;
+            block_scan2<NT>(sum, 0, excl, unused, total, unused_total, sh);
+            if (total < krem) {  // fewer candidates than E: take everything
+                if (tid == 0) {
+                    sh.prefix = prefix | (static_cast<uint64_t>(mask) << s);
+                    sh.krem = 0;
+                    sh.cnt = 0;
                 }
-                const int incl = wave_incl_scan(sum);
-                const int excl = incl - sum;
-                const bool hit = excl < krem && incl >= krem;
-                const unsigned long long mask = __ballot(hit);
-                if (mask == 0ull) {  // fewer candidates than E: take everything
-                    if (tid == 0) {
-                        sh.prefix = prefix | (255ull << s);
-                        sh.krem = 0;
-                        sh.cnt = 0;
-                    }
-                } else if (hit) {
-                    // the first of the lane's 4 bins where the count reaches krem
-                    // (fixed indexes only: no private array in scratch memory)
-                    int cum = excl, b = -1, cum_b = 0, cnt_b = 0;
+            } else if (excl < krem && excl + sum >= krem) {
+                // the first of the thread's bins where the count reaches krem
+                // (fixed indexes only: no private array in scratch memory)
+                int cum = excl, bin = -1, cum_b = 0, cnt_b = 0;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bool take = b < 0 && cum + c4[i] >= krem;
-                        b = take ? i : b;
-                        cum_b = take ? cum : cum_b;
-                        cnt_b = take ? c4[i] : cnt_b;
-                        cum += c4[i];
-                    }
-                    if (b < 0) {  // not reached: the lane holds the krem-th candidate
-                        b = 3;
-                        cum_b = cum;
-                        cnt_b = c4[3];
-                    }
-                    sh.prefix = prefix | (static_cast<uint64_t>(tid * 4 + b) << s);
-                    sh.krem = krem - cum_b;
-                    sh.cnt = cnt_b;
+                for (int i = 0; i < BPT; ++i) {
+                    const bool take = bin < 0 && cum + c[i] >= krem;
+                    bin = take ? i : bin;
+                    cum_b = take ? cum : cum_b;
+                    cnt_b = take ? c[i] : cnt_b;
+                    cum += c[i];
                 }
+                sh.prefix = prefix | (static_cast<uint64_t>(tid * BPT + bin) << s);
+                sh.krem = krem - cum_b;
+                sh.cnt = cnt_b;
             }
             __syncthreads();
             prefix = sh.prefix;
@@ -341,18 +367,23 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
                 shift = s;
                 break;
             }
+            top = s;
         }
     }
 
     // ---- holes (evicted, slot < budget) and movers (kept, slot >= budget) ----
-    int32_t* src = LK ? s_src : job.src_g;
-    int32_t* dst = LK ? s_dst : job.dst_g;
+    // (lists in LDS with LK: of at most kInlineRows entries beside the keys,
+    // longer ones in place of the keys, which the classification leaves behind
+    // as one bit per slot; the copy kernel's lists in memory otherwise)
+    int32_t* src = !LK ? job.src_g : job.inline_kv ? s_src : reinterpret_cast<int32_t*>(s_keys);
+    int32_t* dst = !LK ? job.dst_g : job.inline_kv ? s_dst : reinterpret_cast<int32_t*>(s_keys) + SH::kKeys;
     int n_moves = 0;
     if (LK && E > 0 && E <= kSmallE) {
         n_moves = sh.nm;  // paired above
     } else {
         const int per = (len + NT - 1) / NT;
         const int j0 = min(tid * per, len), j1 = min(j0 + per, len);
+        static_assert(!LK || SH::kKeys / NT <= 32, "a bit per slot of a thread");
         auto evicted = [&](int j) -> bool {
             if (E == 0) return false;
             uint64_t k;
@@ -360,15 +391,17 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
             return (k >> shift) <= (thr >> shift);
         };
         int nh = 0, nm = 0;
+        uint32_t bits = 0;
         for (int j = j0; j < j1; ++j) {
             const bool ev = evicted(j);
+            if (LK) bits |= static_cast<uint32_t>(ev) << (j - j0);
             if (j < budget) nh += ev ? 1 : 0;
             else nm += ev ? 0 : 1;
         }
         int hx, mx, ht, mt;
         block_scan2<NT>(nh, nm, hx, mx, ht, mt, sh);
         for (int j = j0; j < j1; ++j) {
-            const bool ev = evicted(j);
+            const bool ev = LK ? (bits >> (j - j0)) & 1u : evicted(j);
             if (j < budget) {
                 if (ev) dst[hx++] = j;
             } else if (!ev) {
@@ -377,6 +410,11 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
         }
         n_moves = min(ht, mt);
         __syncthreads();
+        if (LK && !job.inline_kv)
+            for (int r = tid; r < n_moves; r += NT) {
+                job.src_g[r] = src[r];
+                job.dst_g[r] = dst[r];
+            }
     }
 
     bool moved = false;
@@ -387,8 +425,8 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
             A[d] = A[s];
             P[d] = P[s];
         }
-    if (tid == 0) *job.n_out = (LK || job.inline_kv) ? 0 : n_moves;
-    if (!moved && (LK || job.inline_kv)) {
+    if (tid == 0) *job.n_out = job.inline_kv ? 0 : n_moves;
+    if (!moved && job.inline_kv) {
         const int total = n_moves * Hkv * 2 * CH;
         for (int i = tid; i < total; i += NT) {
             const int c = i % CH;

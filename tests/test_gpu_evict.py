@@ -250,3 +250,33 @@ def test_empty_cache_with_kept_output():
     # sequence 1: sink {0}, recent {5}, middle {4, 1, 3, 2} by score: pos 3 (0.6) kept
     assert (kr[:, :2] == -1).all() and (kr[:, 2:5] == [0, 3, 5]).all()
     assert (from_dev(p)[:, :2] == -7).all()
+
+
+@pytest.mark.parametrize("length,budget,tie_levels", [
+    (1024, 767, 0),        # 257 evictions: the first size whose move lists leave the small arrays
+    (1023, 600, 1),        # one score for all: the threshold lies in the position digits
+    (16384, 16000, 3),     # the last length with its keys in LDS, more evictions than inline moves
+    (16384, 90, 0), (16385, 3000, 0), (20000, 19900, 5), (24577, 24568, 0)])
+def test_large_selections(length, budget, tie_levels):
+    """Many moved rows and the radix select's digits on both sides of the
+    16384-slot limit of the LDS keys (whole numbers and copies: exact)."""
+    _check_evict(1, 2, 64, length + 1, length, budget, synth.DT_BF16, next_pos=length + 77, tie_levels=tie_levels,
+                 seed=3)
+
+
+def test_selection_of_scores_of_any_size():
+    """Zeros, subnormals, values next to each other and the largest finite
+    ones: every bit of a score counts."""
+    import torch
+    L, Hkv, d, length, budget = 1, 1, 64, 3000, 1500
+    k, v, s, p = synth.random_state(9, L, Hkv, d, length, length, synth.DT_F32, next_pos=length + 5)
+    bits = (synth.uniform01(synth.stream_key(9, "bits"), 0, length) * 0x7F7FFFFF).astype(np.uint32)
+    bits[:200] = np.arange(200) // 2              # zeros and subnormals, in pairs
+    bits[200:900] = 0x3C000000 + np.arange(700)   # neighbours
+    s[0] = bits[np.argsort(synth.uniform01(synth.stream_key(9, "mix"), 0, length))].view(np.float32)
+    g = GpuCache(L, 1, Hkv, d, length, synth.DT_F32)
+    g.load(k, v, s, p, length, length + 5)
+    keep, nl = oracle.evict_select(s.astype(np.float64), p, length, budget, 4, -1, length + 5)
+    kept = torch.full((L, budget), -1, dtype=torch.int32, device="cuda")
+    assert g.evict(budget, kept=kept) == nl == budget
+    assert np.array_equal(from_dev(kept)[0], p[0][keep[0]])
