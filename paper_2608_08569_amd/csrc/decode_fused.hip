@@ -31,6 +31,7 @@
 // partials, and the layer's (max, sum) of the head.  Fold kernel: per (chunk,
 // layer), the chunk's scores A[j] = gamma A[j] + sum_h p_hj from p~ and one
 // factor per head.
+#include <algorithm>
 #include <atomic>
 #include <random>
 #include <type_traits>
@@ -48,7 +49,8 @@ using namespace vz_mfma;
 constexpr size_t kHeaderBytes = 256;
 
 // Per-chunk partial results in the workspace, after the header:
-//   ml [L][nc_max][Hq]        float2     chunk max m_c and sum l_c of exp2, per head
+//   ml [L][Hq][nc_max]        float2     chunk max m_c and sum l_c of exp2, per head (a head's chunks
+//                                        side by side: the finishing kernels read them 16 lanes at a time)
 //   o  [L][nc_max][Hq][D]     bfloat16   O_c relative to m_c
 //   p  [L][nc_max][Hq][CHUNK] bfloat16   p~ = exp2(s - m_c) per key of the chunk
 //   layer [S][L][Hq]          float2     the layer's max M and 1 / sum S, per head
@@ -76,6 +78,16 @@ using vz::SeqItem;
 using vz::ragged_chunks;
 static_assert(CHUNK == vz::kChunk, "one chunk size");
 
+struct Exp2Rel {
+    __device__ __forceinline__ float operator()(float x, float m) const { return x == -INFINITY ? 0.f : exp2f(x - m); }
+};
+// The weights of the chunks in a head's sums, where the chunk of the max has
+// weight 1 and a sum of exp of at least 1: the instruction alone, whose flush
+// of weights below 2^-126 is far below the sums' last bit.
+struct Exp2Weight {
+    __device__ __forceinline__ float operator()(float x, float m) const { return __builtin_amdgcn_exp2f(x - m); }
+};
+
 // Flat chunk f of a call: false when it holds no work.
 template <bool RAG>
 __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem& it, int& c) {
@@ -98,18 +110,22 @@ __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem
 // waves in which wave w owns keys [VT w, VT w + VT) of the chunk.  Each wave
 // requests its query rows and its K and V tile (16 KB) before anything else,
 // so a chunk costs one memory round trip, and a one-layer call over 8k keys
-// spreads its 16 MB over 260 workgroups.  The waves agree on the chunk's max per head through
-// LDS, then sum their exp2 sums and partial outputs in wave order; the
-// partial results of (chunk, query head) go to the workspace for the
-// finishing kernels.  (Launch bounds: four workgroups per CU, 128 registers
-// per lane; the MFMA accumulators then live in ordinary vector registers.)
+// spreads its 16 MB over 260 workgroups.  Both tiles come in the MFMA operand
+// layouts and stay in registers: the softmax is relative to the wave's own max
+// until the waves meet once, at the end, where their outputs are rescaled to
+// the chunk's max and summed in wave order.  A one-layer call is a launch
+// (1.7 us), its 16.8 MB (3.8 us for a kernel of the same loads and nothing
+// else) and this arithmetic behind the last loads, 1.9 us with the stores: per
+// layer of a 48-layer graph at 8,200 keys, with the finishing launch and a
+// caller's kernel, 14.9 -> 13.8 us (V through LDS, three barriers and the
+// sequence search by shuffles before).
+// (Launch bounds: four workgroups per CU, 128 registers per lane; the MFMA
+// accumulators then live in ordinary vector registers.)
 constexpr int SPLIT_W = CHUNK / VT;  // waves per chunk: one 32-key tile each
 template <int NW, bool RAG>
 __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const FusedArgs a) {
     constexpr int OS = D + 4;  // padded LDS row of a wave's partial output (floats)
-    static_assert(SPLIT_W * GMAX * OS * 4 <= SPLIT_W * TILE_BYTES, "the partial outputs fit in the tile buffers");
-    __shared__ __attribute__((aligned(16))) uint8_t s_tile[SPLIT_W][TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) uint16_t s_p[GMAX][CHUNK];  // p~ of the chunk, per head
+    __shared__ __attribute__((aligned(16))) float s_o[SPLIT_W][GMAX][OS];
     __shared__ float s_m[SPLIT_W][GMAX], s_l[SPLIT_W][GMAX];
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -117,18 +133,21 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     const int hi = r16 >> 3, hh = r16 & 7;
     const int Hq = a.Hq, nc_max = a.nc_max;
     const int G = Hq / NW;
-    // item = (chunk item, KV head), KV head fastest; chunk items are ordered
-    // as in the attend kernel (a single sequence's full chunks of every layer
-    // first, its short remainders last)
+    // item = (chunk item, KV head), KV head fastest; a ragged call's layers
+    // are on grid y; a single sequence's chunk items are its full chunks of
+    // every layer first, then the short remainders
     const int g = static_cast<int>(blockIdx.x) % NW;
     const int ci = static_cast<int>(blockIdx.x) / NW;
     int l, f;
     if constexpr (RAG) {
-        l = ci / nc_max;
-        f = ci - l * nc_max;
+        l = blockIdx.y;
+        f = ci;
     } else {
         const int n_full = (a.len + 1) / CHUNK;
-        if (ci < a.L * n_full) {
+        if (a.L == 1) {
+            l = 0;
+            f = ci;
+        } else if (ci < a.L * n_full) {
             l = ci / n_full;
             f = ci - l * n_full;
         } else {
@@ -184,13 +203,14 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     }
 
     // both tiles requested at once; rows past the chunk read as zero without
-    // touching memory (bounded scalar descriptors).  The V tile comes whole
-    // rows at a time (instruction m: rows 4 m .. 4 m + 3) for its trip through
-    // LDS; the K tile straight in the MFMA A-operand layout (register m =
-    // 4 ti + s: row 16 ti + r16, bytes 16 (q4 + 4 s) .. + 15), used from
-    // registers.
-    const int lane_off = q4 * (D * 2) + 16 * r16;
+    // touching memory (bounded scalar descriptors).  K in the MFMA A-operand
+    // layout: register m = 4 ti + s holds bytes 16 (q4 + 4 s) .. + 15 of row
+    // 16 ti + r16.  V whole rows at a time, 16 bytes of four rows per lane and
+    // tile half: register m = 4 ti + i holds channels 8 r16 .. + 7 of row
+    // 16 ti + 4 q4 + i, which are the lane's share of eight A operands (V^T,
+    // channel slot r16 of output tile e: channel 8 r16 + e) for those keys.
     const int lane_off_k = r16 * (D * 2) + 16 * q4;
+    const int lane_off_v = 4 * q4 * (D * 2) + 16 * r16;
     uint4 kt[8], vt[8];
     {
         // (the byte bound taken through readfirstlane keeps the descriptors in
@@ -209,14 +229,12 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         }
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rv, lane_off + 4 * m * (D * 2), 0, 0);
+            const auto v =
+                __builtin_amdgcn_raw_buffer_load_b128(rv, lane_off_v + (16 * (m >> 2) + (m & 3)) * (D * 2), 0, 0);
             __builtin_memcpy(&vt[m], &v, 16);
         }
     }
     __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first wait
-    uint8_t* const buf = s_tile[w];
-    uint8_t* const vwp = buf + q4 * VSTRIDE + 16 * r16;
-    const uint8_t* const vr = buf + (4 * q4 + (r16 >> 2)) * VSTRIDE + 16 * ((r16 & 3) >> 1) + 8 * (r16 & 1);
 
     if (writer && r16 == (rr & 15)) {  // the new K row: row 16 ti + r16 of registers 4 ti .. 4 ti + 3
 #pragma unroll
@@ -236,6 +254,8 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
             acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kt[4 * ti + s]), as_bf16x8(qv[s]), acc[ti], 0,
                                                               0, 0);
     }
+    // packed: head column r16 < 8 keeps the even half's logits, column r16 =
+    // 8 + hh takes the odd half's of head hh
     float sp[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -244,345 +264,325 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         const int key = VT * w + 16 * hi + 4 * q4 + i;  // within the chunk
         sp[i] = (key < nk) ? v * a.scale_log2 : -INFINITY;
     }
+    // ---- p relative to the wave's max, per head ----
     float m_w = fmaxf(fmaxf(sp[0], sp[1]), fmaxf(sp[2], sp[3]));
-    m_w = fmaxf(m_w, __shfl_xor(m_w, 16, 64));
-    m_w = fmaxf(m_w, __shfl_xor(m_w, 32, 64));
+    m_w = vz::rows_max(m_w);
     m_w = fmaxf(m_w, ror8(m_w));
-    if (q4 == 0 && hi == 0) s_m[w][hh] = m_w;
+    const float m_ref = m_w == -INFINITY ? 0.f : m_w;  // a wave past the chunk's keys
+    float l_w = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sp[i] = exp2f(sp[i] - m_ref);
+        l_w += sp[i];
+    }
+    l_w = vz::rows_sum(l_w);
+    l_w += ror8(l_w);
+    if (q4 == 0 && hi == 0) {
+        s_m[w][hh] = m_w;
+        s_l[w][hh] = l_w;
+    }
+    // B operand P^T: columns 0..7 the even half's keys, then the odd half's
+    // (columns 8..15 hold the halves the other way round: outputs not used)
+    const uint32_t p01 = pack_bf16x2(sp[0], sp[1]), p23 = pack_bf16x2(sp[2], sp[3]);
+    const bf16x8_t pb = as_bf16x8(make_uint4(p01, p23, ror8_u32(p01), ror8_u32(p23)));
+
     if (writer) {
-        if (q4 == (rr & 3)) {  // the new V row: row 4 m + q4 of register m
+        if (q4 == ((rr >> 2) & 3)) {  // the new V row: row 16 ti + 4 q4 + i of register 4 ti + i
 #pragma unroll
             for (int m = 0; m < 8; ++m)
-                if (m == rr >> 2) vt[m] = vn_row;
+                if (m == 4 * (rr >> 4) + (rr & 3)) vt[m] = vn_row;
         }
         // the new rows into the cache, after every load of the wave
         if (r16 == (rr & 15)) {
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) *reinterpret_cast<uint4*>(Kh + len * D + 8 * (q4 + 4 * s)) = kn_row[s];
         }
-        if (q4 == (rr & 3)) *reinterpret_cast<uint4*>(Vh + len * D + 8 * r16) = vn_row;
+        if (q4 == ((rr >> 2) & 3)) *reinterpret_cast<uint4*>(Vh + len * D + 8 * r16) = vn_row;
         if (g == 0 && lane == 0) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
     }
-#pragma unroll
-    for (int m = 0; m < 8; ++m) *reinterpret_cast<uint4*>(vwp + 4 * VSTRIDE * m) = vt[m];
-    __syncthreads();
-
-    // ---- the chunk's max per head, p~ against it ----
-    float m_c = s_m[0][hh];
-#pragma unroll
-    for (int v = 1; v < SPLIT_W; ++v) m_c = fmaxf(m_c, s_m[v][hh]);
-    float l_w = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        sp[i] = exp2f(sp[i] - m_c);
-        l_w += sp[i];
-    }
-    l_w += __shfl_xor(l_w, 16, 64);
-    l_w += __shfl_xor(l_w, 32, 64);
-    l_w += ror8(l_w);
-    if (q4 == 0 && hi == 0) s_l[w][hh] = l_w;
-    const uint32_t p01 = pack_bf16x2(sp[0], sp[1]), p23 = pack_bf16x2(sp[2], sp[3]);
-    if (hh < G) *reinterpret_cast<uint2*>(&s_p[hh][VT * w + 16 * hi + 4 * q4]) = make_uint2(p01, p23);
 
     // ---- O^T = V^T P^T over the wave's keys ----
-    float ev[4], od[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float x = sp[i];
-        const float y = ror8(x);
-        ev[i] = hi ? y : x;
-        od[i] = hi ? x : y;
-    }
-    const uint4 pw = make_uint4(pack_bf16x2(ev[0], ev[1]), pack_bf16x2(ev[2], ev[3]), pack_bf16x2(od[0], od[1]),
-                                pack_bf16x2(od[2], od[3]));
-    const bf16x8_t pa = as_bf16x8(pw);
+    // Output tile e takes channel 8 slot + e of each of the 16 channel slots:
+    // its A operand is element e of the lane's eight V pieces (keys 4 q4 + i,
+    // then 16 + 4 q4 + i, as in pb), gathered by byte permutes.
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 oacc[DTILES];
 #pragma unroll
-    for (int n = 0; n < DTILES; ++n) {
-        s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vr + 32 * n));
-        s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4*)(vr + 16 * VSTRIDE + 32 * n));
-        uint4 bw;
-        __builtin_memcpy(&bw.x, &b0, 8);
-        __builtin_memcpy(&bw.z, &b1, 8);
-        oacc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bw), pa, zero, 0, 0, 0);
+    for (int e = 0; e < DTILES; ++e) {
+        uint32_t x[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const uint32_t words[4] = {vt[m].x, vt[m].y, vt[m].z, vt[m].w};
+            x[m] = words[e / 2];
+        }
+        constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;  // halves of (second, first) word
+        uint32_t av[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) av[y] = __builtin_amdgcn_perm(x[2 * y + 1], x[2 * y], (e & 1) ? kHigh : kLow);
+        oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(av[0], av[1], av[2], av[3])), pb, zero,
+                                                          0, 0, 0);
     }
-    __syncthreads();  // every wave's V reads are done: the tiles take the partial outputs
-    float* const s_o = reinterpret_cast<float*>(&s_tile[0][0]);  // [SPLIT_W][GMAX][OS]
+    // lane: head r16, channels 8 (4 q4 + i) + e
     if (r16 < G) {
 #pragma unroll
-        for (int n = 0; n < DTILES; ++n)
-            *reinterpret_cast<f32x4*>(s_o + (w * GMAX + r16) * OS + 16 * n + 4 * q4) = oacc[n];
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < DTILES; e += 4)
+                *reinterpret_cast<float4*>(&s_o[w][r16][8 * (4 * q4 + i) + e]) =
+                    make_float4(oacc[e][i], oacc[e + 1][i], oacc[e + 2][i], oacc[e + 3][i]);
     }
     __syncthreads();
 
     // ---- partial results of (chunk, head): (m_c, l_c), O_c and p~ ----
     Partials part(a.ws, a.hdr_bytes, a.L, nc_max, Hq);
     const int pbase = (l * nc_max + it.first + c) * Hq + g * G;  // < 2^31 (checked on the host)
-    if (tid < G) {
-        float lc = 0.f;
-#pragma unroll
-        for (int v = 0; v < SPLIT_W; ++v) lc += s_l[v][tid];
-        float mc = s_m[0][tid];
-#pragma unroll
-        for (int v = 1; v < SPLIT_W; ++v) mc = fmaxf(mc, s_m[v][tid]);
-        part.ml[pbase + tid] = make_float2(mc, lc);
+    auto chunk_max = [&](int h) { return fmaxf(fmaxf(s_m[0][h], s_m[1][h]), fmaxf(s_m[2][h], s_m[3][h])); };
+    static_assert(SPLIT_W == 4, "four waves' maxima");
+    {
+        // p~ = p rescaled to the chunk's max, 4 keys of a head per lane
+        const float f = exp2f(m_w - chunk_max(hh));
+        if (hh < G)
+            *reinterpret_cast<uint2*>(part.p + static_cast<size_t>(pbase + hh) * CHUNK + VT * w + 16 * hi + 4 * q4) =
+                make_uint2(pack_bf16x2(sp[0] * f, sp[1] * f), pack_bf16x2(sp[2] * f, sp[3] * f));
     }
     {
-        // 4 channels (outputs) or 4 keys (p~) per thread, whole rows per head
+        // 4 channels per thread, whole output rows per head
         const int h = tid >> 5, c4 = 4 * (tid & 31);
         if (h < G) {
-            float o[4];
+            const float m_c = chunk_max(h);
+            float o[4] = {0.f, 0.f, 0.f, 0.f}, lc = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float x = 0.f;
-#pragma unroll
-                for (int v = 0; v < SPLIT_W; ++v) x += s_o[(v * GMAX + h) * OS + c4 + e];
-                o[e] = x;
+            for (int v = 0; v < SPLIT_W; ++v) {
+                const float f = Exp2Weight()(s_m[v][h], m_c);
+                const float4 x = *reinterpret_cast<const float4*>(&s_o[v][h][c4]);
+                o[0] = fmaf(x.x, f, o[0]);
+                o[1] = fmaf(x.y, f, o[1]);
+                o[2] = fmaf(x.z, f, o[2]);
+                o[3] = fmaf(x.w, f, o[3]);
+                lc = fmaf(s_l[v][h], f, lc);
             }
             *reinterpret_cast<uint2*>(part.o + static_cast<size_t>(pbase + h) * D + c4) =
                 make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-            *reinterpret_cast<uint2*>(part.p + static_cast<size_t>(pbase + h) * CHUNK + c4) =
-                *reinterpret_cast<const uint2*>(&s_p[h][c4]);
+            if (c4 == 0) part.ml[(l * Hq + g * G + h) * nc_max + it.first + c] = make_float2(m_c, lc);
         }
     }
 }
 
 // ---- finishing: merge of the chunk partials ----
 // Sums use explicit fused multiply-adds, so the bits do not depend on how the
-// compiler contracts each kernel (the single-sequence and ragged calls give
-// the same bits).
+// compiler contracts each kernel (the single-sequence and ragged calls, and
+// the two forms of the finishing launches, give the same bits).
 constexpr int OUT_THREADS = 256;
 constexpr int OUT_ROWS = OUT_THREADS / 16;  // row groups
-constexpr int OUT_BATCH = 8;                // chunks per row group and round
+constexpr int OUT_BATCH = vz::kPairs;       // chunks per row group and round
+static_assert(OUT_ROWS == 16, "a row group per lane of a DPP row");
 
-// Merge of the OUT_ROWS row-group statistics: (layer max M, 1 / sum S).
-__device__ __forceinline__ float2 combine_rows(const float* sm, const float* sl, int stride) {
-    float Mg = sm[0];
+// Output row of head h of (layer l, sequence s) by a whole block: thread t
+// owns channels 8 (t % 16) .. + 7 of the rows of chunks t / 16, t / 16 + 16,
+// ...; o = sum_c O_c exp2(m_c - M) / S with the head's (M, S), which every
+// 16-lane row of the block forms itself (no barrier before the weights), so
+// the weighted rows are independent of one another; the 16 row groups are
+// summed in registers within a wave and through LDS across the waves.
+struct OutLoads {
+    float2 pr[vz::kPairs];   // the statistics' pairs (lane t % 16)
+    float m[OUT_BATCH];      // the maxima of the thread's own chunks
+    uint4 x[OUT_BATCH];      // their row pieces
+};
+__device__ __forceinline__ void out_load(const float2* ml, const uint16_t* po, int Hq, int c0, int n_load, float* m,
+                                         uint4* x) {
 #pragma unroll
-    for (int r = 1; r < OUT_ROWS; ++r) Mg = fmaxf(Mg, sm[r * stride]);
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < OUT_ROWS; ++r) {
-        const float f = sm[r * stride] == -INFINITY ? 0.f : exp2f(sm[r * stride] - Mg);
-        sum = fmaf(sl[r * stride], f, sum);
+    for (int k = 0; k < OUT_BATCH; ++k) {  // rows clamped (every load in bounds), masked later
+        m[k] = -INFINITY;
+        x[k] = make_uint4(0, 0, 0, 0);
+        if (OUT_ROWS * k >= n_load) continue;  // uniform
+        const int cc = min(c0 + OUT_ROWS * k, n_load - 1);
+        m[k] = ml[cc].x;
+        x[k] = *reinterpret_cast<const uint4*>(po + static_cast<size_t>(cc) * Hq * D);
     }
-    return make_float2(Mg, 1.0f / sum);
 }
-
-// One round of a row group's chunks: chunk c0 + OUT_ROWS k of pair st[k] and
-// row piece xr[k], while it is below n_chunks, into the running (M, S, acc).
-__device__ __forceinline__ void merge_batch(const float2 (&st)[OUT_BATCH], const uint4 (&xr)[OUT_BATCH], int c0,
-                                            int n_chunks, float& M, float& S, float (&acc)[8]) {
+__device__ __forceinline__ void out_add(const float* m, const uint4* x, int c0, int n_chunks, float M, float (&acc)[8]) {
 #pragma unroll
     for (int k = 0; k < OUT_BATCH; ++k) {
-        if (c0 + OUT_ROWS * k >= n_chunks) break;
-        if (st[k].x > M) {
-            const float r = exp2f(M - st[k].x);  // 0 while M is -inf
+        if (OUT_ROWS * k >= n_chunks) break;  // uniform
+        const float wgt = Exp2Weight()(c0 + OUT_ROWS * k < n_chunks ? m[k] : -INFINITY, M);
+        float f[8];
+        vz::unpack16<VZ_BF16>(x[k], f);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] *= r;
-            S *= r;
-            M = st[k].x;
-        }
-        const float wgt = exp2f(st[k].x - M);
-        float x[8];
-        vz::unpack16<VZ_BF16>(xr[k], x);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(wgt, x[i], acc[i]);
-        S = fmaf(wgt, st[k].y, S);
+        for (int i = 0; i < 8; ++i) acc[i] = fmaf(wgt, c0 + OUT_ROWS * k < n_chunks ? f[i] : 0.f, acc[i]);
     }
 }
-
-// The 16 row groups' (M, S, acc) merged in LDS, the output row stored;
-// returns the layer's (max, 1 / sum) of head h in thread 0.
-__device__ float2 merge_rows_store(const FusedArgs& a, int h, int l, int s, float M, float S, const float (&acc)[8]) {
-    __shared__ float s_acc[OUT_ROWS][D + 4];
-    __shared__ float s_m[OUT_ROWS], s_l[OUT_ROWS];
-    const int t = threadIdx.x, Hq = a.Hq;
-    const int rg = t / 16, c8 = 8 * (t % 16);
+__device__ __forceinline__ void out_store(const FusedArgs& a, int h, int l, int s, float inv_S, float (&acc)[8]) {
+    constexpr int WAVES = OUT_THREADS / vz::kWave;
+    __shared__ __attribute__((aligned(16))) float s_acc[WAVES][D];
+    const int t = threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s_acc[rg][c8 + i] = acc[i];
-    if (t % 16 == 0) {
-        s_m[rg] = M;
-        s_l[rg] = S;
+    for (int i = 0; i < 8; ++i) acc[i] = vz::rows_sum(acc[i]);
+    if (t % vz::kWave < 16) {
+        float* const d = &s_acc[t / vz::kWave][8 * (t % 16)];
+        *reinterpret_cast<float4*>(d) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        *reinterpret_cast<float4*>(d + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
     }
     __syncthreads();
-    float2 stats = make_float2(0.f, 0.f);
     if (t < D) {
-        stats = combine_rows(s_m, s_l, 1);
-        float o = 0.f;
+        float o = s_acc[0][t];
 #pragma unroll
-        for (int r = 0; r < OUT_ROWS; ++r) {
-            const float f = s_m[r] == -INFINITY ? 0.f : exp2f(s_m[r] - stats.x);
-            o = fmaf(s_acc[r][t], f, o);
-        }
-        const size_t row_sl = static_cast<size_t>(s) * a.L + l;
-        a.out[(row_sl * Hq + h) * D + t] = vz::f32_to_bf16(o * stats.y);
-    }
-    return stats;
-}
-
-// Loads of one round: the pairs and row pieces of chunks c0 + OUT_ROWS k,
-// rows clamped to n_load - 1 (every load in bounds, the values masked later).
-__device__ __forceinline__ void merge_load(const float2* ml, const uint16_t* po, int Hq, int c0, int n_load,
-                                           float2 (&st)[OUT_BATCH], uint4 (&xr)[OUT_BATCH]) {
-#pragma unroll
-    for (int k = 0; k < OUT_BATCH; ++k) {
-        const int cc = min(c0 + OUT_ROWS * k, n_load - 1);
-        st[k] = ml[static_cast<size_t>(cc) * Hq];
-        xr[k] = *reinterpret_cast<const uint4*>(po + static_cast<size_t>(cc) * Hq * D);
+        for (int v = 1; v < WAVES; ++v) o += s_acc[v][t];
+        a.out[((static_cast<size_t>(s) * a.L + l) * a.Hq + h) * D + t] = vz::f32_to_bf16(o * inv_S);
     }
 }
 
-// Output row of head h of (layer l, sequence s) from the sequence's n_chunks
-// partials starting at chunk row `first`, by a whole block of OUT_THREADS
-// threads.  Thread t owns channels 8 (t % 16) .. +7 of the rows of chunks
-// t / 16, t / 16 + 16, ...: a running max, o = sum_c O_c exp2(m_c - M) /
-// sum_c l_c exp2(m_c - M); the 16 row groups then merge in LDS.  All loads of
-// a round (16-byte row pieces and the chunk pairs) are issued before any use:
-// indexes past the end are clamped and the values masked afterwards.
-// Returns the layer's (max, 1 / sum) of head h in thread 0.
-__device__ float2 merge_output_row(const FusedArgs& a, const Partials& part, int h, int l, int s, int first,
-                                   int n_chunks) {
-    const int t = threadIdx.x, Hq = a.Hq;
-    const int rg = t / 16, c8 = 8 * (t % 16);
-    const size_t row0 = static_cast<size_t>(l) * a.nc_max + first;  // first chunk row of (layer, sequence)
-    const float2* ml = part.ml + row0 * Hq + h;
-    const uint16_t* po = part.o + (row0 * Hq + h) * D + c8;
-    float M = -INFINITY, S = 0.f, acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-    for (int c0 = rg; c0 < n_chunks; c0 += OUT_ROWS * OUT_BATCH) {
-        float2 st[OUT_BATCH];
-        uint4 xr[OUT_BATCH];
-        merge_load(ml, po, Hq, c0, n_chunks, st, xr);
-        merge_batch(st, xr, c0, n_chunks, M, S, acc);
-    }
-    return merge_rows_store(a, h, l, s, M, S, acc);
-}
-
-// Output block of a call of one sequence whose planes hold at most
-// OUT_ROWS * OUT_BATCH chunks (one round): its chunk rows start at row 0, so
-// the round's loads (rows clamped to the layer's n_load rows) go out before
-// the sequence's values arrive, and the same arithmetic as merge_output_row
-// follows.  A ragged call of one sequence reports its status here (head 0 of
-// layer 0).
-template <bool RAG>
-__device__ void output_block_one(const FusedArgs& a, int h, int l) {
+// Output block of (head h, layer l, sequence s); store_layer: also the head's
+// (M, 1 / S) for the fold kernel.  ONE (a call of one sequence whose planes
+// hold at most vz::kPairChunks chunks): its chunk rows start at row 0, so the
+// partial results' loads (rows clamped to the layer's) go out before the
+// sequence's values arrive.  In a ragged call the block of head 0 of layer 0
+// reports the sequence's status.
+template <bool RAG, bool ONE>
+__device__ void output_block(const FusedArgs& a, int h, int l, int s, bool store_layer) {
     const int t = threadIdx.x, Hq = a.Hq;
     const int rg = t / 16, c8 = 8 * (t % 16);
     Partials part(a.ws, a.hdr_bytes, a.L, a.nc_max, Hq);
-    const size_t row0 = static_cast<size_t>(l) * a.nc_max;
-    float2 st[OUT_BATCH];
-    uint4 xr[OUT_BATCH];
-    merge_load(part.ml + row0 * Hq + h, part.o + (row0 * Hq + h) * D + c8, Hq, rg, RAG ? a.nc_max : a.n_chunks, st,
-               xr);
-    int n_chunks = a.n_chunks;
-    if constexpr (RAG) {
-        const int st0 = vz::ragged_decode_status(a.rag, 0);
-        n_chunks = st0 == VZ_OK ? (a.rag.len[0] + CHUNK) / CHUNK : 0;
-        const bool ok = st0 == VZ_OK && n_chunks <= a.nc_max;
-        if (a.rag.status && h == 0 && l == 0 && t == 0) a.rag.status[0] = ok ? VZ_OK : (st0 != VZ_OK ? st0 : VZ_ERR_CAPACITY);
-        if (!ok) return;
+    const float2* const ml = part.ml + (static_cast<size_t>(l) * Hq + h) * a.nc_max;
+    const uint16_t* const po = part.o + (static_cast<size_t>(l) * a.nc_max * Hq + h) * D + c8;
+    OutLoads ld;
+    auto load = [&](int first, int n_load) {
+        vz::load_pairs(ml + first, n_load, t % 16, ld.pr);
+        out_load(ml + first, po + static_cast<size_t>(first) * Hq * D, Hq, rg, n_load, ld.m, ld.x);
+    };
+    if constexpr (ONE) {
+        load(0, RAG ? a.nc_max : a.n_chunks);
+        __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first wait
     }
-    float M = -INFINITY, S = 0.f, acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-    merge_batch(st, xr, rg, n_chunks, M, S, acc);
-    merge_rows_store(a, h, l, 0, M, S, acc);
-}
-
-// Output kernel, one block per (head, layer, sequence):
-// the output row, the layer's (max, 1 / sum) of the head for the fold kernel
-// and, in a ragged call, the sequence's status.
-template <bool RAG>
-__device__ void output_block(const FusedArgs& a, int h, int l, int s_arg, bool store_layer) {
-    const int t = threadIdx.x;
-    int s = 0, first = 0, n_chunks = a.n_chunks;
+    int first = 0, n_chunks = a.n_chunks;
     if constexpr (RAG) {
-        s = s_arg;
         // the sequence's own values and the earlier sequences' chunk counts
         // are loaded side by side (one round of loads)
         const int st = vz::ragged_decode_status(a.rag, s);
-        const int fst = vz::ragged_first(s, a.nc_max, [&](int u) { return ragged_chunks(a.rag, u); });
-        first = st == VZ_OK ? fst : -1;
+        if constexpr (!ONE) first = vz::ragged_first(s, a.nc_max, [&](int u) { return ragged_chunks(a.rag, u); });
         n_chunks = st == VZ_OK ? (a.rag.len[s] + CHUNK) / CHUNK : 0;
         const bool ok = st == VZ_OK && first >= 0 && first + n_chunks <= a.nc_max;
         if (a.rag.status && h == 0 && l == 0 && t == 0) a.rag.status[s] = ok ? VZ_OK : (st != VZ_OK ? st : VZ_ERR_CAPACITY);
         if (!ok) return;
     }
-    Partials part(a.ws, a.hdr_bytes, a.L, a.nc_max, a.Hq);
-    const float2 stats = merge_output_row(a, part, h, l, s, first, n_chunks);
-    if (store_layer && t == 0) part.layer[(static_cast<size_t>(s) * a.L + l) * a.Hq + h] = stats;
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    float2 stats;
+    if (ONE || n_chunks <= vz::kPairChunks) {
+        if constexpr (!ONE) {
+            load(first, n_chunks);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stats = vz::merge_pairs(ld.pr, n_chunks, t % 16, Exp2Weight());
+        out_add(ld.m, ld.x, rg, n_chunks, stats.x, acc);
+    } else {
+        stats = vz::merge_all(ml + first, n_chunks, t % 16, Exp2Weight());
+        for (int c0 = rg; c0 - rg < n_chunks; c0 += OUT_ROWS * OUT_BATCH) {
+            out_load(ml + first, po + static_cast<size_t>(first) * Hq * D, Hq, c0, n_chunks, ld.m, ld.x);
+            out_add(ld.m, ld.x, c0, n_chunks, stats.x, acc);
+        }
+    }
+    const float inv_S = 1.0f / stats.y;
+    if (store_layer && t == 0) part.layer[(static_cast<size_t>(s) * a.L + l) * Hq + h] = make_float2(stats.x, inv_S);
+    out_store(a, h, l, s, inv_S, acc);
 }
 
+// Fold of one chunk's scores, Eq. (6), by a block of OUT_THREADS threads:
+// A[j] = gamma A[j] + sum_h p~_hj f_h with f_h = exp2(m_c,h - M_h) / S_h (the
+// new slot starts from 0).  Wave w adds its quarter of the heads for every key
+// of the chunk, two keys per lane, and the four waves' sums meet in LDS.  The
+// p~ loads (rows are complete, CHUNK entries each) and the old score's are
+// issued before the factors are known.
+constexpr int FOLD_HEADS = 16;  // heads per wave: Hq <= Hkv * GMAX with Hkv <= 8
+struct FoldLoads {
+    uint32_t p[FOLD_HEADS];
+    float old;
+};
+__device__ __forceinline__ int fold_heads_per_wave(int Hq) { return (Hq + 3) / 4; }
+// (chunk_row: the chunk's row of the workspace arrays; one descriptor over its
+// Hq rows, so a load is an immediate offset from one address, and heads past
+// the last read as zero)
+__device__ __forceinline__ void fold_load(const ConstPartials& part, size_t chunk_row, int Hq, FoldLoads& ld) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / vz::kWave), lane = threadIdx.x % vz::kWave;
+    const int hpw = fold_heads_per_wave(Hq);
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(part.p + chunk_row * Hq * CHUNK), 0, Hq * CHUNK * 2, kBufferDword3);
+    const int off = w * hpw * CHUNK * 2 + 4 * lane;
+#pragma unroll
+    for (int q = 0; q < FOLD_HEADS; ++q) {
+        if (q % 8 == 0 && q >= hpw) break;  // wave-uniform
+        ld.p[q] = __builtin_amdgcn_raw_buffer_load_b32(rp, off + q * CHUNK * 2, 0, 0);
+    }
+}
+__device__ __forceinline__ void fold_finish(const FusedArgs& a, const FoldLoads& ld, const float* s_f, float* sc, int Hq,
+                                            int nk, bool new_key) {
+    __shared__ float s_sum[OUT_THREADS / vz::kWave][CHUNK];
+    const int t = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(t / vz::kWave), lane = t % vz::kWave;
+    const int hpw = fold_heads_per_wave(Hq);
+    float x = 0.f, y = 0.f;
+#pragma unroll
+    for (int q = 0; q < FOLD_HEADS; ++q) {
+        if (q < hpw && w * hpw + q < Hq) {
+            const float f = s_f[w * hpw + q];
+            x = fmaf(bf16_lo(ld.p[q]), f, x);
+            y = fmaf(bf16_hi(ld.p[q]), f, y);
+        }
+    }
+    *reinterpret_cast<float2*>(&s_sum[w][2 * lane]) = make_float2(x, y);
+    __syncthreads();
+    if (t < nk) {
+        float acc = s_sum[0][t];
+#pragma unroll
+        for (int v = 1; v < OUT_THREADS / vz::kWave; ++v) acc += s_sum[v][t];
+        *sc = fmaf(a.gamma, new_key ? 0.f : ld.old, acc);  // zero pad of Eq. (6) for the new slot
+    }
+}
+
+// Two launches, for the calls that finish_in_one_launch refuses: the output
+// kernel, one block per (head, layer, sequence), then the fold kernel, one
+// block per (chunk, layer), with the statistics the output kernel stored.
 template <bool RAG>
 __global__ __launch_bounds__(OUT_THREADS) void decode_output_kernel(const FusedArgs a) {
-    output_block<RAG>(a, blockIdx.x, blockIdx.y, blockIdx.z, true);
+    output_block<RAG, false>(a, blockIdx.x, blockIdx.y, blockIdx.z, true);
 }
-
-// Fold kernel, one block of CHUNK threads per (chunk, layer), thread = key:
-// Eq. (6), A[j] = gamma A[j] + sum_h p~_hj f_h with f_h = exp2(m_c,h - M_h) / S_h
-// from the layer statistics the output kernel stored (the new slot starts
-// from 0).  Heads go in rounds of 32: the round's p~ loads are issued before
-// its factors are formed (p~ rows are complete, CHUNK entries each, so every
-// load is in bounds; heads past Hq are clamped and masked, so no load sits
-// behind a branch).
-constexpr int FOLD_HEADS = 32;
 template <bool RAG>
-__global__ __launch_bounds__(CHUNK) void decode_fold_kernel(const FusedArgs a) {
-    __shared__ float s_f[FOLD_HEADS];
-    const int l = blockIdx.y, t = threadIdx.x;
-    const int Hq = a.Hq;
+__global__ __launch_bounds__(OUT_THREADS) void decode_fold_kernel(const FusedArgs a) {
+    __shared__ float s_f[8 * GMAX];
+    const int l = blockIdx.y, t = threadIdx.x, Hq = a.Hq;
     SeqItem it;
     int c;
     if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
     const ConstPartials part(a.ws, a.hdr_bytes, a.L, a.nc_max, Hq);
-    const int len = it.len, T = len + 1;
-    const int k_begin = chunk_begin(c);
-    const int nk = chunk_keys(c, T);
-    const int j = k_begin + (t < nk ? t : 0);
-    float* sc = a.score + static_cast<size_t>(l) * a.plane + it.base + j;
-    const float a_ld = *sc;
-    const float a_old = (t < nk && j < len) ? a_ld : 0.f;  // zero pad of Eq. (6) for the new slot
-    const size_t cbase = (static_cast<size_t>(l) * a.nc_max + it.first + c) * Hq;
-    const float2* layer = part.layer + (static_cast<size_t>(it.s) * a.L + l) * Hq;
-    const uint16_t* pp = part.p + cbase * CHUNK + t;
-    float acc = 0.f;
-    for (int hb = 0; hb < Hq; hb += FOLD_HEADS) {
-        uint16_t pr[FOLD_HEADS];
-#pragma unroll
-        for (int q = 0; q < FOLD_HEADS; ++q) pr[q] = pp[min(hb + q, Hq - 1) * CHUNK];
-        if (t < FOLD_HEADS && hb + t < Hq) {
-            const float2 gl = layer[hb + t];
-            s_f[t] = exp2f(part.ml[cbase + hb + t].x - gl.x) * gl.y;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < FOLD_HEADS; ++q)
-            if (hb + q < Hq) acc = fmaf(vz::bf16_to_f32(pr[q]), s_f[q], acc);
-        __syncthreads();
-    }
-    if (t < nk) *sc = fmaf(a.gamma, a_old, acc);
+    const int nk = chunk_keys(c, it.len + 1), tk = min(t, nk - 1);
+    float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base + chunk_begin(c) + tk;
+    FoldLoads ld;
+    const float2 gl = part.layer[(static_cast<size_t>(it.s) * a.L + l) * Hq + min(t, Hq - 1)];
+    const float m_c = part.ml[(static_cast<size_t>(l) * Hq + min(t, Hq - 1)) * a.nc_max + it.first + c].x;
+    fold_load(part, static_cast<size_t>(l) * a.nc_max + it.first + c, Hq, ld);
+    ld.old = *sc;
+    if (t < Hq) s_f[t] = Exp2Rel()(m_c, gl.x) * gl.y;
+    __syncthreads();
+    fold_finish(a, ld, s_f, sc, Hq, nk, chunk_begin(c) + tk == it.len);
 }
 
-// Output merge and score fold in one launch, for calls whose sequences have
-// few chunks (planes of at most FINISH_MAX_CHUNKS chunks).  Blocks
-// [0, n_chunks) of a layer are fold blocks: one per chunk, each forms every
-// head's layer statistics itself from its sequence's chunk pairs, with the
-// output kernel's arithmetic and order (the same bits), then folds its
-// chunk's keys as the fold kernel does.  The blocks after them are the output
-// kernel's blocks, one per (head, sequence), run beside the fold blocks.  The
-// recomputation reads n_chunks x Hq pairs per fold block, cheap while chunks
-// are few.
-constexpr int FINISH_MAX_CHUNKS = 128;
-constexpr int FINISH_MAX_HEADS = 8 * GMAX;  // Hq <= Hkv * GMAX with Hkv <= 8
+// One launch (see finish_in_one_launch).  Blocks [0, n_chunks)
+// of a layer are fold blocks: one per chunk, each forms every head's layer
+// statistics itself from its sequence's chunk pairs (16 lanes per head, four
+// heads per wave at a time, in registers), with the output blocks' arithmetic
+// and order, then folds its chunk's keys.  The blocks after them are output
+// blocks, one per (head, sequence), run beside the fold blocks.  The
+// recomputation reads n_chunks x Hq pairs per fold block.  Of its 3.5 us above
+// an empty kernel (65 chunks, in a graph) 2.5 us are the loads of what the
+// attend kernel has just written; addresses are immediate offsets from a few
+// descriptors, because at one wave per SIMD each instruction before the loads
+// costs its own 2 ns.
+constexpr int FINISH_BATCH_CHUNKS = 640;
+constexpr int FINISH_BATCH_BLOCKS = 2048;
+constexpr int FINISH_ROUNDS = 8 * GMAX / 16;  // of 16 heads
 template <bool RAG>
 __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedArgs a) {
-    __shared__ float s_gm[FINISH_MAX_HEADS * OUT_ROWS], s_gl[FINISH_MAX_HEADS * OUT_ROWS];
-    __shared__ float2 s_stat[FINISH_MAX_HEADS];
-    __shared__ float s_f[FOLD_HEADS];
+    __shared__ float s_f[8 * GMAX];
     const int t = threadIdx.x, l = blockIdx.y, Hq = a.Hq;
     // One sequence (a single-sequence call, or a ragged call of one): its
     // chunk rows start at row 0 of the layer and a fold block's chunk is row
@@ -593,142 +593,89 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
     if (static_cast<int>(blockIdx.x) >= a.n_chunks) {
         const int ob = static_cast<int>(blockIdx.x) - a.n_chunks;
         if (one)
-            output_block_one<RAG>(a, ob % Hq, l);
+            output_block<RAG, true>(a, ob % Hq, l, 0, false);
         else
-            output_block<RAG>(a, ob % Hq, l, ob / Hq, false);
+            output_block<RAG, false>(a, ob % Hq, l, ob / Hq, false);
         return;
     }
     const ConstPartials part(a.ws, a.hdr_bytes, a.L, a.nc_max, Hq);
-    // Loads first, all independent of one another: the chunk pairs of the
-    // statistics (thread t: (head, row group) pairs t, t + OUT_THREADS, ...,
-    // up to FINISH_GROUP_CHUNKS chunks each, indexes clamped), the fold's p~
-    // of the first FOLD_HEADS heads, its chunk's own pairs and the scores.
-    constexpr int FINISH_GROUP_CHUNKS = FINISH_MAX_CHUNKS / OUT_ROWS;
-    constexpr int FINISH_PAIRS = FINISH_MAX_HEADS * OUT_ROWS / OUT_THREADS;
-    float2 stv[FINISH_PAIRS][FINISH_GROUP_CHUNKS];
-    uint16_t pr[FOLD_HEADS];
-    float m_own;
+    float2 pr[FINISH_ROUNDS][vz::kPairs];
+    float m_own[FINISH_ROUNDS];
+    FoldLoads ld;
     const int tk = t < CHUNK ? t : 0;
-    // (head, row group) pair pi = rg * Hq + h: the 64 lanes of a load
-    // instruction read whole rows of heads (two rows of 32 heads, four cache
-    // lines); rounds past the Hq * OUT_ROWS pairs are skipped (uniform)
-    auto load_pairs = [&](size_t row0, int n_load) {
+    // (one descriptor over the layer's pairs: a load is an immediate offset
+    // from the lane's address, and nothing needs clamping)
+    auto load = [&](int first, int n_load, int row) {
+        const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float2*>(part.ml + static_cast<size_t>(l) * Hq * a.nc_max), 0,
+            __builtin_amdgcn_readfirstlane(Hq * a.nc_max * 8), kBufferDword3);
 #pragma unroll
-        for (int u = 0; u < FINISH_PAIRS; ++u) {
-            if (u * OUT_THREADS >= Hq * OUT_ROWS) break;
-            const int pi = min(t + u * OUT_THREADS, Hq * OUT_ROWS - 1);
-            const int rg = pi / Hq, h = pi - rg * Hq;
+        for (int u = 0; u < FINISH_ROUNDS; ++u) {
+            if (16 * u >= Hq) break;  // uniform
+            const int head = (16 * u + t / 16) * a.nc_max;
+            const int off = 8 * (head + first + t % 16);
 #pragma unroll
-            for (int k = 0; k < FINISH_GROUP_CHUNKS; ++k)
-                stv[u][k] = part.ml[(row0 + min(rg + k * OUT_ROWS, n_load - 1)) * Hq + h];
+            for (int k = 0; k < vz::kPairs; ++k) {
+                pr[u][k] = make_float2(-INFINITY, 0.f);
+                if (16 * k < n_load)
+                    pr[u][k] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rm, off + 128 * k, 0, 0));
+            }
+            m_own[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, 8 * (head + row), 0, 0));
         }
-    };
-    auto load_own = [&](size_t cbase) {
-        const uint16_t* pp = part.p + cbase * CHUNK + tk;
-#pragma unroll
-        for (int q = 0; q < FOLD_HEADS; ++q) pr[q] = pp[min(q, Hq - 1) * CHUNK];
-        m_own = part.ml[cbase + min(t % FOLD_HEADS, Hq - 1)].x;
+        fold_load(part, static_cast<size_t>(l) * a.nc_max + row, Hq, ld);
     };
     SeqItem it;
     int c;
-    float a_spec = 0.f;
     if (one) {
-        // the sequence's values first (a ragged call of one: sequence 0 owns
-        // chunk rows [0, its chunks)), then the partial results, then the
-        // checks: the score load below waits only for the values
-        int64_t b = 0;
-        int cp = a.plane, ln = a.len, np = a.next_pos;
-        if constexpr (RAG) {
-            b = a.rag.base[0];
-            cp = a.rag.cap[0];
-            ln = a.rag.len[0];
-            np = a.rag.next_pos[0];
-        }
-        load_pairs(static_cast<size_t>(l) * a.nc_max, RAG ? a.nc_max : a.n_chunks);
-        load_own((static_cast<size_t>(l) * a.nc_max + blockIdx.x) * Hq);
-        // the score of key tk of chunk blockIdx.x for a sequence at slot 0
-        // (a single-sequence call, or the one slot of a decode loop), with the
+        load(0, RAG ? a.nc_max : a.n_chunks, blockIdx.x);
+        // the score of key tk of chunk blockIdx.x for a sequence at slot 0 (a
+        // single-sequence call, or the one slot of a decode loop), with the
         // other loads; another base loads it again once the values are in
-        a_spec = a.score[static_cast<size_t>(l) * a.plane +
+        ld.old = a.score[static_cast<size_t>(l) * a.plane +
                          min(static_cast<int64_t>(chunk_begin(blockIdx.x) + tk), a.plane - 1)];
-        int nc = a.n_chunks;
-        if constexpr (RAG) {
-            const bool ok = vz::decode_status_of(b, cp, ln, np, a.rag.total) == VZ_OK;
-            nc = ok ? (ln + CHUNK) / CHUNK : 0;
-            if (nc > a.nc_max) nc = 0;
-        }
-        if (static_cast<int>(blockIdx.x) >= nc) return;
-        it.s = 0;
-        it.len = ln;
-        it.next_pos = np;
-        it.n_chunks = nc;
-        it.first = 0;
-        it.base = b;
-        c = blockIdx.x;
-    } else if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) {
-        return;
+        __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first wait
+        if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
+    } else {
+        if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
+        load(it.first, min(it.n_chunks, vz::kPairChunks), it.first + c);
     }
-    const size_t row0 = static_cast<size_t>(l) * a.nc_max + it.first;
-    const int nch = it.n_chunks;
-    const size_t cbase = (row0 + c) * Hq;  // = (layer row + blockIdx.x) * Hq
-    if (!one) {
-        load_pairs(row0, nch);
-        load_own(cbase);
-    }
-    const int len = it.len, T = len + 1;
-    const int nk = chunk_keys(c, T);
-    const int j = chunk_begin(c) + (tk < nk ? tk : 0);
-    float* sc = a.score + static_cast<size_t>(l) * a.plane + it.base + j;
+    const int nk = chunk_keys(c, it.len + 1);
+    const int j = chunk_begin(c) + min(tk, nk - 1);
+    float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base + j;
+    if (!one || it.base != 0) ld.old = *sc;
     // (used only for tk < nk, where j is the slot the speculative load read)
-    const float a_ld = one && it.base == 0 ? a_spec : *sc;
-    const uint16_t* pp = part.p + cbase * CHUNK + tk;
 
-    // the layer statistics of every head: row group rg of head h takes
-    // chunks rg, rg + OUT_ROWS, ... with a running max, then the groups merge
+    // the layer statistics and the chunk's factor of every head
 #pragma unroll
-    for (int u = 0; u < FINISH_PAIRS; ++u) {
-        const int pi = t + u * OUT_THREADS;
-        if (pi < Hq * OUT_ROWS) {
-            const int rg = pi / Hq, h = pi - rg * Hq;
-            float M = -INFINITY, S = 0.f;
-#pragma unroll
-            for (int k = 0; k < FINISH_GROUP_CHUNKS; ++k) {
-                if (rg + k * OUT_ROWS >= nch) break;
-                const float2 st = stv[u][k];
-                if (st.x > M) {
-                    S *= exp2f(M - st.x);
-                    M = st.x;
-                }
-                S = fmaf(exp2f(st.x - M), st.y, S);
-            }
-            s_gm[h * OUT_ROWS + rg] = M;
-            s_gl[h * OUT_ROWS + rg] = S;
-        }
+    for (int u = 0; u < FINISH_ROUNDS; ++u) {
+        if (16 * u >= Hq) break;
+        const int h = 16 * u + t / 16;
+        const float2 st =
+            it.n_chunks <= vz::kPairChunks
+                ? vz::merge_pairs(pr[u], it.n_chunks, t % 16, Exp2Weight())
+                : vz::merge_all(part.ml + (static_cast<size_t>(l) * Hq + min(h, Hq - 1)) * a.nc_max + it.first,
+                                it.n_chunks, t % 16, Exp2Weight());
+        if (t % 16 == 0 && h < Hq) s_f[h] = Exp2Rel()(m_own[u], st.x) * (1.0f / st.y);
     }
     __syncthreads();
-    if (t < Hq) s_stat[t] = combine_rows(&s_gm[t * OUT_ROWS], &s_gl[t * OUT_ROWS], 1);
-    __syncthreads();
+    fold_finish(a, ld, s_f, sc, Hq, nk, j == it.len);
+}
 
-    // Eq. (6) for the chunk's keys (threads below CHUNK), as the fold kernel
-    const float a_old = (tk < nk && j < len) ? a_ld : 0.f;
-    float acc = 0.f;
-    for (int hb = 0; hb < Hq; hb += FOLD_HEADS) {
-        if (hb > 0) {
-#pragma unroll
-            for (int q = 0; q < FOLD_HEADS; ++q) pr[q] = pp[min(hb + q, Hq - 1) * CHUNK];
-        }
-        if (t < FOLD_HEADS && hb + t < Hq) {
-            const float2 gl = s_stat[hb + t];
-            const float m_c = hb == 0 ? m_own : part.ml[cbase + hb + t].x;
-            s_f[t] = exp2f(m_c - gl.x) * gl.y;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < FOLD_HEADS; ++q)
-            if (hb + q < Hq) acc = fmaf(vz::bf16_to_f32(pr[q]), s_f[q], acc);
-        __syncthreads();
-    }
-    if (t < CHUNK && t < nk) *sc = fmaf(a.gamma, a_old, acc);
+// Whether a call's outputs and scores are finished in one launch.  `chunks`:
+// of a plane; `blocks`: fold and output blocks of a layer in that launch.
+// One sequence: while its chunks' pairs are one round of loads (one layer 8.2
+// against 10.1 us at 500 keys, 8.5 against 10.6 at 8000; 30 layers equal at
+// 8000).  A batch: while its blocks are at most two rounds of the CUs' eight
+// resident ones (4 x 2000 keys: one layer 9.1 against 11.4 us, 8 layers 30.9
+// against 31.5, 16 layers 53.6 against 53.0, where the kernel's registers cost
+// more than a launch), its sequences hold at most kPairChunks chunks on
+// average, and its planes at most FINISH_BATCH_CHUNKS, which bounds what one
+// sequence of nearly every slot costs (16 sequences of 1.2k-6.1k keys 26.9
+// against 29.2 us; one of 80,000 keys, past the line, 45.8 against 40.6).
+bool finish_in_one_launch(int64_t chunks, int seqs, int32_t L, int64_t blocks) {
+    if (seqs == 1) return chunks <= vz::kPairChunks;
+    return chunks <= std::min<int64_t>(FINISH_BATCH_CHUNKS, static_cast<int64_t>(vz::kPairChunks) * seqs) &&
+           blocks * L <= FINISH_BATCH_BLOCKS;
 }
 
 template <int NW, bool RAG>
@@ -775,10 +722,11 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
         }
         return vz_launch_decode_range(a, NW, stream);
     }
-    hipLaunchKernelGGL((decode_attend_kernel<NW, RAG>), dim3(a.L * a.n_chunks * NW), dim3(64 * SPLIT_W), 0, stream, a);
+    hipLaunchKernelGGL((decode_attend_kernel<NW, RAG>), RAG ? dim3(a.n_chunks * NW, a.L) : dim3(a.L * a.n_chunks * NW),
+                       dim3(64 * SPLIT_W), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if ((a.plane + CHUNK - 1) / CHUNK <= FINISH_MAX_CHUNKS) {
+    if (finish_in_one_launch((a.plane + CHUNK - 1) / CHUNK, seqs, a.L, a.n_chunks + a.Hq * static_cast<int64_t>(seqs))) {
         hipLaunchKernelGGL((decode_finish_kernel<RAG>), dim3(a.n_chunks + a.Hq * seqs, a.L), dim3(OUT_THREADS), 0,
                            stream, a);
         return hipGetLastError();
@@ -786,7 +734,7 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
     hipLaunchKernelGGL((decode_output_kernel<RAG>), dim3(a.Hq, a.L, seqs), dim3(OUT_THREADS), 0, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((decode_fold_kernel<RAG>), dim3(a.n_chunks, a.L), dim3(CHUNK), 0, stream, a);
+    hipLaunchKernelGGL((decode_fold_kernel<RAG>), dim3(a.n_chunks, a.L), dim3(OUT_THREADS), 0, stream, a);
     return hipGetLastError();
 }
 

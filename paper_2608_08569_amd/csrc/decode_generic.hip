@@ -49,7 +49,7 @@ constexpr int kWaves = kThreads / vz::kWave;
 constexpr int kKeysPerWave = kChunk / kWaves;  // 32: two 16-key tiles
 constexpr int kHeads = 16;                     // head columns of a matrix instruction, and the largest group
 constexpr int kMaxRuns = 64;                   // runs of chunks per sequence
-constexpr int kStatChunks = 128;               // chunks whose pairs the values kernel merges itself
+constexpr int kStatChunks = vz::kPairChunks;   // chunks whose pairs the values kernel merges itself
 
 // Arguments of the launches (a single-sequence call has rag.n == 0).
 struct GenericArgs {
@@ -62,7 +62,7 @@ struct GenericArgs {
     float* score;
     void* out;
     float* S;        // logits [L][nc_max][Hq][kChunk], then key sums and run outputs in their place
-    float2* ml;      // max and sum of exp per (layer, chunk row, head) [L][nc_max][Hq]
+    float2* ml;      // max and sum of exp per (layer, head, chunk row) [L][Hq][nc_max]
     float2* layer;   // the same per (sequence, layer, head), for planes of more than kStatChunks chunks
     int32_t len, next_pos, n_chunks;  // single sequence
     int32_t nc_max;                   // chunk rows per layer
@@ -100,9 +100,12 @@ __host__ __device__ inline Runs runs_of(int nc, int G) {
     return r;
 }
 
-// Row (layer, chunk row, head) of the workspace arrays.
+// Row (layer, chunk row, head) of the logits; a head's pairs.
 __device__ __forceinline__ size_t ws_row(const GenericArgs& a, int l, int chunk_row, int h) {
     return (static_cast<size_t>(l) * a.nc_max + chunk_row) * a.Hq + h;
+}
+__device__ __forceinline__ float2* ml_of(const GenericArgs& a, int l, int h) {
+    return a.ml + (static_cast<size_t>(l) * a.Hq + h) * a.nc_max;
 }
 // Run output of head hg of KV head g (first chunk row `row` of the run): heads
 // 1 .. in their own rows of that chunk, head 0 in row 1 of the next one (rows
@@ -111,24 +114,6 @@ __device__ __forceinline__ float* run_out(const GenericArgs& a, int l, int row, 
     return a.S + (hg > 0 ? ws_row(a, l, row, g * G + hg) : ws_row(a, l, row + 1, g * G + 1)) * kChunk;
 }
 
-// Max and sum over the 16 lanes of a DPP row, in every lane (rotations by 8,
-// 4, 2 and 1; each step adds the same two values in both lanes of a pair).
-template <int ROR>
-__device__ __forceinline__ float ror16(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float row16_max(float v) {
-    v = fmaxf(v, ror16<8>(v));
-    v = fmaxf(v, ror16<4>(v));
-    v = fmaxf(v, ror16<2>(v));
-    return fmaxf(v, ror16<1>(v));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-    v += ror16<8>(v);
-    v += ror16<4>(v);
-    v += ror16<2>(v);
-    return v + ror16<1>(v);
-}
 // exp(x - m), 0 for an absent x (-inf, also when m is -inf).
 __device__ __forceinline__ float exp_rel(float x, float m) { return x == -INFINITY ? 0.f : expf(x - m); }
 
@@ -213,15 +198,13 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
         if (r16 < G)
             *reinterpret_cast<float4*>(S + 16 * ti + 4 * q4) = make_float4(sv[ti][0], sv[ti][1], sv[ti][2], sv[ti][3]);
     }
-    m_w = fmaxf(m_w, __shfl_xor(m_w, 16, vz::kWave));
-    m_w = fmaxf(m_w, __shfl_xor(m_w, 32, vz::kWave));
+    m_w = vz::rows_max(m_w);
     float l_w = 0.f;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
         for (int i = 0; i < 4; ++i) l_w += exp_rel(sv[ti][i], m_w);
-    l_w += __shfl_xor(l_w, 16, vz::kWave);
-    l_w += __shfl_xor(l_w, 32, vz::kWave);
+    l_w = vz::rows_sum(l_w);
     if (q4 == 0) {
         s_m[w][r16] = m_w;
         s_l[w][r16] = l_w;
@@ -233,48 +216,13 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
         for (int v = 1; v < kWaves; ++v) m = fmaxf(m, s_m[v][tid]);
 #pragma unroll
         for (int v = 0; v < kWaves; ++v) z = fmaf(s_l[v][tid], exp_rel(s_m[v][tid], m), z);
-        a.ml[ws_row(a, l, it.first + c, g * G + tid)] = make_float2(m, z);
+        ml_of(a, l, g * G + tid)[it.first + c] = make_float2(m, z);
     }
 }
 
-// Max and sum of exp of one head over nc chunks, by 16 neighbouring lanes
-// (lane i takes chunks i, i + 16, ...): ml points at the head's pair of chunk
-// 0.  Up to kStatChunks chunks: eight pairs per lane, all loaded (indexes
-// clamped) before any is used.
-constexpr int kStatPairs = kStatChunks / 16;
-__device__ __forceinline__ void load_pairs(const float2* ml, int nc, int Hq, int c0, float2 (&p)[kStatPairs]) {
-#pragma unroll
-    for (int k = 0; k < kStatPairs; ++k) p[k] = ml[static_cast<size_t>(min(c0 + 16 * k, nc - 1)) * Hq];
-}
-__device__ __forceinline__ float2 merge_pairs(float2 (&p)[kStatPairs], int nc, int i) {
-    float m = -INFINITY, z = 0.f;
-#pragma unroll
-    for (int k = 0; k < kStatPairs; ++k) {
-        p[k].x = i + 16 * k < nc ? p[k].x : -INFINITY;
-        m = fmaxf(m, p[k].x);
-    }
-    m = row16_max(m);
-#pragma unroll
-    for (int k = 0; k < kStatPairs; ++k) z = fmaf(p[k].x == -INFINITY ? 0.f : p[k].y, exp_rel(p[k].x, m), z);
-    return make_float2(m, row16_sum(z));
-}
-// Any number of chunks (the same order of additions).
-__device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int Hq, int i) {
-    float2 p[kStatPairs];
-    float m = -INFINITY, z = 0.f;
-    for (int c0 = i; c0 - i < nc; c0 += kStatChunks) {
-        load_pairs(ml, nc, Hq, c0, p);
-#pragma unroll
-        for (int k = 0; k < kStatPairs; ++k) m = fmaxf(m, p[k].x);  // a clamped pair is one of the head's own
-    }
-    m = row16_max(m);
-    for (int c0 = i; c0 - i < nc; c0 += kStatChunks) {
-        load_pairs(ml, nc, Hq, c0, p);
-#pragma unroll
-        for (int k = 0; k < kStatPairs; ++k) z = fmaf(c0 + 16 * k < nc ? p[k].y : 0.f, exp_rel(p[k].x, m), z);
-    }
-    return make_float2(m, row16_sum(z));
-}
+struct ExpRel {
+    __device__ __forceinline__ float operator()(float x, float m) const { return exp_rel(x, m); }
+};
 
 // Statistics of every head of a (sequence, layer), once, for calls whose
 // planes hold more than kStatChunks chunks (where merging them in every
@@ -289,7 +237,7 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(const GenericArgs a) {
         if (nc == 0 || first < 0 || first + nc > a.nc_max) return;
     }
     const int h = blockIdx.x * (kThreads / 16) + threadIdx.x / 16, i = threadIdx.x % 16;
-    const float2 st = merge_all(a.ml + ws_row(a, l, first, min(h, a.Hq - 1)), nc, a.Hq, i);
+    const float2 st = vz::merge_all(ml_of(a, l, min(h, a.Hq - 1)) + first, nc, i, ExpRel());
     if (i == 0 && h < a.Hq) a.layer[(static_cast<size_t>(s) * a.L + l) * a.Hq + h] = st;
 }
 
@@ -381,8 +329,8 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     // the statistics do not wait for the tiles)
     const bool own_stats = (a.plane + kChunk - 1) / kChunk <= kStatChunks;
     const int hs = min(tid / 16, G - 1);  // 16 lanes per head
-    float2 pr[kStatPairs];
-    if (own_stats) load_pairs(a.ml + ws_row(a, l, it.first, g * G + hs), it.n_chunks, Hq, tid % 16, pr);
+    float2 pr[vz::kPairs];
+    if (own_stats) vz::load_pairs(ml_of(a, l, g * G + hs) + it.first, it.n_chunks, tid % 16, pr);
     else pr[0] = a.layer[row_sl * Hq + g * G + hs];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -391,7 +339,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     __builtin_amdgcn_sched_barrier(0);
 
     {
-        const float2 st = own_stats ? merge_pairs(pr, it.n_chunks, tid % 16) : pr[0];
+        const float2 st = own_stats ? vz::merge_pairs(pr, it.n_chunks, tid % 16, ExpRel()) : pr[0];
         if (tid % 16 == 0) s_stat[tid / 16] = st;
     }
     __syncthreads();
@@ -424,7 +372,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
                         __builtin_amdgcn_mfma_f32_16x16x4f32(on[i] ? f[k] : 0.f, e[i], acc[PER * j + k], 0, 0, 0);
             }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ks[i] = row16_sum(ks[i]);
+        for (int i = 0; i < 4; ++i) ks[i] = vz::row16_sum(ks[i]);
         if (r16 < 4) {
             const float sum = r16 == 0 ? ks[0] : r16 == 1 ? ks[1] : r16 == 2 ? ks[2] : ks[3];
             const int key = k0 + 4 * q4 + r16;

@@ -52,6 +52,10 @@ __device__ __forceinline__ float ror8(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kRor8, 0xF, 0xF, false));
 }
 
+__device__ __forceinline__ uint32_t ror8_u32(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kRor8, 0xF, 0xF, false));
+}
+
 // Two floats to packed bfloat16 (low half a), round to nearest even: one
 // v_cvt_pk_bf16_f32 on gfx950 (the same bits as vz::f32_to_bf16 for finite
 // values).  Used for the P operand of the P.V products and for the stored

@@ -84,21 +84,10 @@ __device__ uint64_t block_min_u64(uint64_t v, SH& sh) {
     return r;
 }
 
-// Inclusive wave scan of an int.
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = threadIdx.x % vz::kWave;
-#pragma unroll
-    for (int o = 1; o < vz::kWave; o <<= 1) {
-        int t = __shfl_up(v, o, vz::kWave);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
 // Exclusive block scan of two ints; also returns the block totals.
 template <int NT, class SH>
 __device__ void block_scan2(int a, int b, int& ax, int& bx, int& at, int& bt, SH& sh) {
-    const int ia = wave_incl_scan(a), ib = wave_incl_scan(b);
+    const int ia = vz::wave_incl_scan(a), ib = vz::wave_incl_scan(b);
     const int w = threadIdx.x / vz::kWave, lane = threadIdx.x % vz::kWave;
     __syncthreads();
     if (lane == vz::kWave - 1) {

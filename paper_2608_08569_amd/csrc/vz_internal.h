@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -106,11 +107,100 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
     const uint32_t lmin = __reduce_min_sync(~0ull, hi == hmin ? lo : 0xFFFFFFFFu);
     return (static_cast<uint64_t>(hmin) << 32) | lmin;
 }
-__device__ __forceinline__ int wave_sum_i(int v) {
+// Max and sum over the 16 lanes of a DPP row, in every lane (rotations by 8,
+// 4, 2 and 1; each step combines the same two values in both lanes of a pair).
+template <int ROR>
+__device__ __forceinline__ float ror16(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float row16_max(float v) {
+    v = fmaxf(v, ror16<8>(v));
+    v = fmaxf(v, ror16<4>(v));
+    v = fmaxf(v, ror16<2>(v));
+    return fmaxf(v, ror16<1>(v));
+}
+__device__ __forceinline__ float row16_sum(float v) {
+    v += ror16<8>(v);
+    v += ror16<4>(v);
+    v += ror16<2>(v);
+    return v + ror16<1>(v);
+}
+// The same across the wave's four rows (lanes l, l ^ 16, l ^ 32, l ^ 48): row
+// swaps in registers, with the values and order of shuffles by 16 and then 32.
+__device__ __forceinline__ float rows_max(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float rows_sum(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// ---- softmax statistics of a head from its chunks' pairs ----
+// (max and sum of exp of each chunk, from ml on), by the 16 lanes of a DPP row: lane i takes chunks i,
+// i + 16, ....  Every lane of the row gets the sequence's pair.  Up to
+// kPairChunks chunks: at most eight pairs per lane, all loaded (indexes
+// clamped) before any is used, in rounds of 16 chunks of which those past
+// n_load are left out (uniform); merge_all takes any number, with the same
+// order of additions.  rel(x, m): exp of x relative to m, 0 for x = -inf.
+constexpr int kPairs = 8;
+constexpr int kPairChunks = 16 * kPairs;
+__device__ __forceinline__ void load_pairs(const float2* ml, int n_load, int c0, float2 (&p)[kPairs]) {
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    for (int k = 0; k < kPairs; ++k) {
+        p[k] = make_float2(-INFINITY, 0.f);
+        if (16 * k < n_load) p[k] = ml[min(c0 + 16 * k, n_load - 1)];
+    }
+}
+template <class Rel>
+__device__ __forceinline__ float2 merge_pairs(const float2 (&p)[kPairs], int nc, int i, Rel rel) {
+    float m = -INFINITY, z = 0.f;
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k) m = fmaxf(m, i + 16 * k < nc ? p[k].x : -INFINITY);
+    m = row16_max(m);
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k) {
+        if (16 * k >= nc) break;
+        const float f = rel(i + 16 * k < nc ? p[k].x : -INFINITY, m);
+        z = fmaf(i + 16 * k < nc ? p[k].y : 0.f, f, z);
+    }
+    return make_float2(m, row16_sum(z));
+}
+template <class Rel>
+__device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int i, Rel rel) {
+    float2 p[kPairs];
+    float m = -INFINITY, z = 0.f;
+    for (int c0 = i; c0 - i < nc; c0 += kPairChunks) {
+        load_pairs(ml, nc, c0, p);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) m = fmaxf(m, p[k].x);  // a clamped pair is one of the head's own
+    }
+    m = row16_max(m);
+    for (int c0 = i; c0 - i < nc; c0 += kPairChunks) {
+        load_pairs(ml, nc, c0, p);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) {
+            const float f = rel(c0 + 16 * k < nc ? p[k].x : -INFINITY, m);
+            z = fmaf(c0 + 16 * k < nc ? p[k].y : 0.f, f, z);
+        }
+    }
+    return make_float2(m, row16_sum(z));
+}
+
+// Inclusive wave scan (DPP row shifts, then the row totals broadcast upwards).
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
     return v;
 }
+__device__ __forceinline__ int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), kWave - 1); }
 
 }  // namespace vz
 
@@ -147,6 +237,11 @@ __device__ __forceinline__ int decode_status_of(int64_t b, int c, int n, int p, 
     if (n >= c) return VZ_ERR_CAPACITY;  // no free slot (len + 1 > cap, without overflow)
     return VZ_OK;
 }
+// decode_status_of(...) == VZ_OK without branches: a value loaded for it is
+// not loaded behind the check of another.
+__device__ __forceinline__ bool decode_served(int64_t b, int c, int n, int p, int64_t total) {
+    return (c > 0) & (n >= 0) & (p >= 0) & (b >= 0) & (b <= total - c) & (n < c);
+}
 __device__ __forceinline__ int ragged_decode_status(const VzRagged& r, int s) {
     return decode_status_of(r.base[s], r.cap[s], r.len[s], r.next_pos[s], r.total);
 }
@@ -157,7 +252,8 @@ constexpr int kChunk = 128;
 
 // Chunks of sequence s in a ragged call (0 when it cannot be served).
 __device__ __forceinline__ int ragged_chunks(const VzRagged& r, int s) {
-    return ragged_decode_status(r, s) == VZ_OK ? (r.len[s] + kChunk) / kChunk : 0;
+    const int n = r.len[s];
+    return decode_served(r.base[s], r.cap[s], n, r.next_pos[s], r.total) ? (n + kChunk) / kChunk : 0;
 }
 
 // The sequence a work item belongs to, resolved at the top of every kernel.
@@ -171,42 +267,49 @@ struct SeqItem {
 
 // Flat chunk f of a ragged call, found by a whole wave: each lane loads one
 // sequence's values (64 sequences per round), a wave scan of their chunk
-// counts finds the owner of f, and the owner's values are forwarded from the
-// lane that loaded them, so the kernel waits for one round of loads.  False
-// when f lies past the call's chunks (or past the nc_max rows).
+// counts finds the owner of f, and the owner's values are taken from the lane
+// that loaded them, so the kernel waits for one round of loads.  A call of one
+// sequence needs no search (scalar loads only).  False when f lies past the
+// call's chunks (or past the nc_max rows).
 __device__ __forceinline__ bool locate_ragged_chunk(const VzRagged& r, int nc_max, int f, SeqItem& it, int& c) {
+    if (r.n == 1) {
+        it.s = 0;
+        it.base = r.base[0];
+        it.len = r.len[0];
+        it.next_pos = r.next_pos[0];
+        const bool ok = decode_served(it.base, r.cap[0], it.len, it.next_pos, r.total);
+        it.n_chunks = (it.len + kChunk) / kChunk;
+        it.first = 0;
+        c = f;
+        return ok && f < it.n_chunks && it.n_chunks <= nc_max;
+    }
     const int lane = threadIdx.x % kWave;
     int run = 0;
     for (int s0 = 0; s0 < r.n && run <= nc_max; s0 += kWave) {
         const int su = min(s0 + lane, r.n - 1);  // load for every lane, mask after
         const int64_t b = r.base[su];
         const int cp = r.cap[su], ln = r.len[su], np = r.next_pos[su];
-        const bool ok = s0 + lane < r.n && decode_status_of(b, cp, ln, np, r.total) == VZ_OK;
+        const bool ok = (s0 + lane < r.n) & decode_served(b, cp, ln, np, r.total);
         const int n = ok ? (ln + kChunk) / kChunk : 0;
-        int incl = n;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int t = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += t;
-        }
+        const int incl = wave_incl_scan(n);
         const unsigned long long hit = __ballot(run + incl > f);
         if (hit) {
             const int src = __builtin_ctzll(hit);
-            const int nc = __builtin_amdgcn_readfirstlane(__shfl(n, src, kWave));
-            const int first = __builtin_amdgcn_readfirstlane(run + __shfl(incl, src, kWave) - nc);
+            const int nc = __builtin_amdgcn_readlane(n, src);
+            const int first = run + __builtin_amdgcn_readlane(incl, src) - nc;
             if (first + nc > nc_max) return false;
             it.s = s0 + src;
-            it.len = __builtin_amdgcn_readfirstlane(__shfl(ln, src, kWave));
-            it.next_pos = __builtin_amdgcn_readfirstlane(__shfl(np, src, kWave));
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b), src, kWave));
-            const uint32_t hi = __builtin_amdgcn_readfirstlane(__shfl(static_cast<int>(b >> 32), src, kWave));
+            it.len = __builtin_amdgcn_readlane(ln, src);
+            it.next_pos = __builtin_amdgcn_readlane(np, src);
+            const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(b), src);
+            const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), src);
             it.base = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
             it.n_chunks = nc;
             it.first = first;
             c = f - first;
             return true;
         }
-        run += __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
+        run += __builtin_amdgcn_readlane(incl, kWave - 1);
     }
     return false;
 }
