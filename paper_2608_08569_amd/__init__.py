@@ -96,7 +96,7 @@ def _ptr(t):
         raise ValueError("tensors must be on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()  # (argtypes converts: no c_void_p object per argument)
 
 
 def _expect(t, shape, what: str, dtype=None):
@@ -110,10 +110,25 @@ def _expect(t, shape, what: str, dtype=None):
         raise TypeError(f"{what} has dtype {t.dtype}, expected {dtype}")
 
 
+def _expect_all(wanted):
+    """_expect for (tensor, shape, what, dtype) entries.  A small call's time is
+    the host's (one layer's step of 129 slots: 14 us of checks and argument
+    passing beside 14 us of kernels), so the check that passes is two
+    comparisons, and only one that does not is spelled out."""
+    for t, shape, what, dtype in wanted:
+        if t is not None and (t.shape != shape or (dtype is not None and t.dtype != dtype)):
+            _expect(t, shape, what, dtype)
+
+
+def _nbytes(t) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 def voxzip_build_span_offsets(t_start_ms, t_end_ms, conf, text_len, t_total_ms: int, L_a: int,
@@ -149,14 +164,11 @@ def voxzip_fuse_spans(k_in, v_in, span_off, k_out, v_out, score_out, pos_out,
     L, H, T_in, d = k_in.shape
     cap = k_out.shape[2]
     n = span_off.numel() - 1
-    _expect(v_in, k_in.shape, "v_in", k_in.dtype)
-    _expect(k_out, (L, H, cap, d), "k_out", k_in.dtype)
-    _expect(v_out, (L, H, cap, d), "v_out", k_in.dtype)
-    _expect(score_out, (L, cap), "score_out", torch.float32)
-    _expect(pos_out, (L, cap), "pos_out", torch.int32)
-    _expect(span_off, (n + 1,), "span_off", torch.int32)
-    _expect(anchor_k, (L, H, n, d), "anchor_k", k_in.dtype)
-    _expect(anchor_v, (L, H, n, d), "anchor_v", k_in.dtype)
+    dt, out_shape, span_shape = k_in.dtype, (L, H, cap, d), (L, H, n, d)
+    _expect_all(((v_in, (L, H, T_in, d), "v_in", dt), (k_out, out_shape, "k_out", dt), (v_out, out_shape, "v_out", dt),
+                 (score_out, (L, cap), "score_out", torch.float32), (pos_out, (L, cap), "pos_out", torch.int32),
+                 (span_off, (n + 1,), "span_off", torch.int32), (anchor_k, span_shape, "anchor_k", dt),
+                 (anchor_v, span_shape, "anchor_v", dt)))
     _check(lib().voxzip_fuse_spans(_ptr(k_in), _ptr(v_in), T_in, _ptr(span_off), n,
                                    _ptr(anchor_k), _ptr(anchor_v), _ptr(k_out), _ptr(v_out),
                                    _ptr(score_out), _ptr(pos_out), L, H, d, cap,
@@ -170,14 +182,11 @@ def voxzip_decode_attend_score(q, k_new, v_new, k_cache, v_cache, score, pos, ou
     L, Hkv, cap, d = k_cache.shape
     Hq = q.shape[1]
     dt = k_cache.dtype
-    _expect(q, (L, Hq, d), "q", dt)
-    _expect(out, (L, Hq, d), "out", dt)
-    _expect(k_new, (L, Hkv, d), "k_new", dt)
-    _expect(v_new, (L, Hkv, d), "v_new", dt)
-    _expect(v_cache, k_cache.shape, "v_cache", dt)
-    _expect(score, (L, cap), "score", torch.float32)
-    _expect(pos, (L, cap), "pos", torch.int32)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    rows, new_rows, plane = (L, Hq, d), (L, Hkv, d), (L, cap)
+    _expect_all(((q, rows, "q", dt), (out, rows, "out", dt), (k_new, new_rows, "k_new", dt),
+                 (v_new, new_rows, "v_new", dt), (v_cache, (L, Hkv, cap, d), "v_cache", dt),
+                 (score, plane, "score", torch.float32), (pos, plane, "pos", torch.int32)))
+    ws_bytes = _nbytes(workspace)
     _check(lib().voxzip_decode_attend_score(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
                                             _ptr(v_cache), _ptr(score), _ptr(pos), _ptr(out),
                                             int(length), int(next_pos), float(gamma), float(sm_scale),
@@ -190,11 +199,9 @@ def voxzip_evict_compact(k_cache, v_cache, score, pos, length, budget, next_pos,
     """Stage-2 eviction in place; returns the new resident length."""
     import torch
     L, Hkv, cap, d = k_cache.shape
-    _expect(v_cache, k_cache.shape, "v_cache", k_cache.dtype)
-    _expect(score, (L, cap), "score", torch.float32)
-    _expect(pos, (L, cap), "pos", torch.int32)
-    _expect(kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _expect_all(((v_cache, (L, Hkv, cap, d), "v_cache", k_cache.dtype), (score, (L, cap), "score", torch.float32),
+                 (pos, (L, cap), "pos", torch.int32), (kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)))
+    ws_bytes = _nbytes(workspace)
     new_len = ctypes.c_int32(0)
     _check(lib().voxzip_evict_compact(_ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos), int(length),
                                       int(budget), int(n_sink), int(n_recent), int(next_pos),
@@ -213,15 +220,12 @@ def voxzip_decode_evict(q, k_new, v_new, k_cache, v_cache, score, pos, out, leng
     L, Hkv, cap, d = k_cache.shape
     Hq = q.shape[1]
     dt = k_cache.dtype
-    _expect(q, (L, Hq, d), "q", dt)
-    _expect(out, (L, Hq, d), "out", dt)
-    _expect(k_new, (L, Hkv, d), "k_new", dt)
-    _expect(v_new, (L, Hkv, d), "v_new", dt)
-    _expect(v_cache, k_cache.shape, "v_cache", dt)
-    _expect(score, (L, cap), "score", torch.float32)
-    _expect(pos, (L, cap), "pos", torch.int32)
-    _expect(kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    rows, new_rows, plane = (L, Hq, d), (L, Hkv, d), (L, cap)
+    _expect_all(((q, rows, "q", dt), (out, rows, "out", dt), (k_new, new_rows, "k_new", dt),
+                 (v_new, new_rows, "v_new", dt), (v_cache, (L, Hkv, cap, d), "v_cache", dt),
+                 (score, plane, "score", torch.float32), (pos, plane, "pos", torch.int32),
+                 (kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)))
+    ws_bytes = _nbytes(workspace)
     new_len = ctypes.c_int32(0)
     _check(lib().voxzip_decode_evict(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), _ptr(score),
                                      _ptr(pos), _ptr(out), int(length), int(next_pos), float(gamma),
@@ -240,14 +244,11 @@ def voxzip_decode_evict_noalloc(q, k_new, v_new, k_cache, v_cache, score, pos, o
     L, Hkv, cap, d = k_cache.shape
     Hq = q.shape[1]
     dt = k_cache.dtype
-    _expect(q, (L, Hq, d), "q", dt)
-    _expect(out, (L, Hq, d), "out", dt)
-    _expect(k_new, (L, Hkv, d), "k_new", dt)
-    _expect(v_new, (L, Hkv, d), "v_new", dt)
-    _expect(v_cache, k_cache.shape, "v_cache", dt)
-    _expect(score, (L, cap), "score", torch.float32)
-    _expect(pos, (L, cap), "pos", torch.int32)
-    _expect(kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)
+    rows, new_rows, plane = (L, Hq, d), (L, Hkv, d), (L, cap)
+    _expect_all(((q, rows, "q", dt), (out, rows, "out", dt), (k_new, new_rows, "k_new", dt),
+                 (v_new, new_rows, "v_new", dt), (v_cache, (L, Hkv, cap, d), "v_cache", dt),
+                 (score, plane, "score", torch.float32), (pos, plane, "pos", torch.int32),
+                 (kept_pos_out, (L, int(budget)), "kept_pos_out", torch.int32)))
     new_len = ctypes.c_int32(0)
     _check(lib().voxzip_decode_evict_noalloc(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
                                              _ptr(score), _ptr(pos), _ptr(out), int(length), int(next_pos),
@@ -299,15 +300,13 @@ def voxzip_fuse_spans_ragged(k_in, v_in, in_base, T_in, span_off, off_base, n_sp
     L, H, total_in, d = k_in.shape
     total = k_out.shape[2]
     n = seq_base.numel()
-    _expect(v_in, k_in.shape, "v_in", k_in.dtype)
-    _expect(k_out, (L, H, total, d), "k_out", k_in.dtype)
-    _expect(v_out, (L, H, total, d), "v_out", k_in.dtype)
-    _expect(score_out, (L, total), "score_out", torch.float32)
-    _expect(pos_out, (L, total), "pos_out", torch.int32)
+    dt, out_shape = k_in.dtype, (L, H, total, d)
+    _expect_all(((v_in, (L, H, total_in, d), "v_in", dt), (k_out, out_shape, "k_out", dt),
+                 (v_out, out_shape, "v_out", dt), (score_out, (L, total), "score_out", torch.float32),
+                 (pos_out, (L, total), "pos_out", torch.int32)))
     if span_off.dtype != torch.int32 or span_off.dim() != 1:
         raise TypeError("span_off must be a 1-D int32 tensor")
-    _expect(anchor_k, (L, H, total, d), "anchor_k", k_in.dtype)
-    _expect(anchor_v, (L, H, total, d), "anchor_v", k_in.dtype)
+    _expect_all(((anchor_k, out_shape, "anchor_k", dt), (anchor_v, out_shape, "anchor_v", dt)))
     _check(lib().voxzip_fuse_spans_ragged(
         _ptr(k_in), _ptr(v_in), _seq_array(in_base, n, "int64", "in_base"), _seq_array(T_in, n, "int32", "T_in"),
         total_in, _ptr(span_off), _seq_array(off_base, n, "int64", "off_base"),
@@ -328,14 +327,11 @@ def voxzip_decode_attend_score_ragged(q, k_new, v_new, k_cache, v_cache, score, 
     L, Hkv, total, d = k_cache.shape
     n, Hq = q.shape[0], q.shape[2]
     dt = k_cache.dtype
-    _expect(q, (n, L, Hq, d), "q", dt)
-    _expect(out, (n, L, Hq, d), "out", dt)
-    _expect(k_new, (n, L, Hkv, d), "k_new", dt)
-    _expect(v_new, (n, L, Hkv, d), "v_new", dt)
-    _expect(v_cache, k_cache.shape, "v_cache", dt)
-    _expect(score, (L, total), "score", torch.float32)
-    _expect(pos, (L, total), "pos", torch.int32)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    rows, new_rows, plane = (n, L, Hq, d), (n, L, Hkv, d), (L, total)
+    _expect_all(((q, rows, "q", dt), (out, rows, "out", dt), (k_new, new_rows, "k_new", dt),
+                 (v_new, new_rows, "v_new", dt), (v_cache, (L, Hkv, total, d), "v_cache", dt),
+                 (score, plane, "score", torch.float32), (pos, plane, "pos", torch.int32)))
+    ws_bytes = _nbytes(workspace)
     _check(lib().voxzip_decode_attend_score_ragged(
         _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos), _ptr(out),
         _seq_array(seq_base, n, "int64", "seq_base"), _seq_array(cap, n, "int32", "cap"),
@@ -353,11 +349,10 @@ def voxzip_evict_compact_ragged(k_cache, v_cache, score, pos, seq_base, cap, len
     import torch
     L, Hkv, total, d = k_cache.shape
     n = seq_base.numel()
-    _expect(v_cache, k_cache.shape, "v_cache", k_cache.dtype)
-    _expect(score, (L, total), "score", torch.float32)
-    _expect(pos, (L, total), "pos", torch.int32)
-    _expect(kept_pos_out, (L, total), "kept_pos_out", torch.int32)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    plane = (L, total)
+    _expect_all(((v_cache, (L, Hkv, total, d), "v_cache", k_cache.dtype), (score, plane, "score", torch.float32),
+                 (pos, plane, "pos", torch.int32), (kept_pos_out, plane, "kept_pos_out", torch.int32)))
+    ws_bytes = _nbytes(workspace)
     _check(lib().voxzip_evict_compact_ragged(
         _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos), _seq_array(seq_base, n, "int64", "seq_base"),
         _seq_array(cap, n, "int32", "cap"), _seq_array(length, n, "int32", "length"),
