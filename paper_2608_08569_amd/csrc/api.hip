@@ -302,8 +302,8 @@ int launch_step(const char* fn, const void* q, const void* k_new, const void* v_
                    n_layers, kv_heads, d, cap, dtype, ews, ws_bytes - split, VzRagged{}, nullptr};
     const bool evict = T > budget || kept_pos_out != nullptr;
     hipError_t e;
-    if (evict && vz_decode_evicts(da, budget)) {
-        // one launch: the decode kernel's last workgroup per layer folds and evicts
+    if (evict && vz_decode_evicts(da, budget, kept_pos_out != nullptr)) {
+        // the decode launches' last workgroup per layer evicts
         da.ev = 1;
         da.ev_budget = budget;
         da.ev_sink = n_sink;

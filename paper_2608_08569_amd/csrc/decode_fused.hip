@@ -1,36 +1,32 @@
 // Decode step (Sec. 3.1 Eq. 1-2, Sec. 3.2.2 Eq. 6) for bfloat16 caches with
-// d = 128 and at most 8 query heads per KV head, chunked path.  Three
-// launches cover every layer: the attend kernel streams the cache once and
-// leaves per-chunk partial results in the workspace; the output and fold
-// kernels merge them into the output rows and the decayed scores.  No
-// workgroup ever waits for another.  Single-sequence calls with enough
-// (layer, KV head) items and a short enough cache go to the whole-range path
-// (decode_range.hip) instead.
+// d = 128 and at most 8 query heads per KV head, chunked path.  The attend
+// kernel streams the cache once and leaves per-chunk partial results in the
+// workspace; a finishing launch (or an output and a fold launch) merges them
+// into the output rows and the decayed scores.  No workgroup ever waits for
+// another.  Calls with enough (layer, KV head) items go to the whole-range
+// path (decode_range.hip) instead.
 //
 // Attend kernel: work item = (layer, key chunk of <= 128 keys, KV head), a
 // workgroup of four waves, one 32-key tile each (the query rows and the K
 // and V tiles of a wave are requested at once: one memory round trip per
-// chunk).
+// chunk, and both tiles are used from registers).
 //   logits  S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (M = 16 keys, N = 16
 //           query-head columns of which n_q/n_kv <= 8 are used, K = 32
-//           channels).  K tiles of 32 rows are loaded straight into the
-//           A-operand layout (each 1 KB instruction reads 64-byte pieces of
-//           16 rows) and used from registers.  The logits
+//           channels), K rows loaded in the A-operand layout.  The logits
 //           of the odd 16-key half of a tile are moved into the unused head
 //           columns 8..15 (DPP row rotate by 8), so 32 keys x 8 heads take 4
 //           registers per lane.
-//   stats   the chunk's max m_c per head (the four waves' maxima through
-//           LDS); p~ = exp2(s - m_c) and the sum l_c of exp2 per head.
-//           (m_c, l_c) and p~ (bfloat16) go to the workspace.
-//   P V     V tiles take the same coalesced path into LDS and are read back
-//           with ds_read_b64_tr_b16 directly in the B-operand layout; P is
-//           rebuilt from p~ with one row rotate.  The four waves' O (fp32)
-//           are summed in wave order through LDS; O_c (relative to m_c) goes
-//           to the workspace in bfloat16.
-// Output kernel: per (head, layer), the output row merged from the chunk
-// partials, and the layer's (max, sum) of the head.  Fold kernel: per (chunk,
-// layer), the chunk's scores A[j] = gamma A[j] + sum_h p_hj from p~ and one
-// factor per head.
+//   stats   per wave and head the max m_w and the sum of exp2 relative to it.
+//   P V     O^T = V^T P^T with the same instruction over the tile's 32 keys:
+//           the A operands are gathered from whole V rows by byte permutes, P
+//           (bfloat16) needs one row rotate.
+//   merge   at the one barrier the waves' outputs are rescaled to the chunk's
+//           max m_c and added in wave order; (m_c, l_c), O_c and p~ = exp2(s -
+//           m_c) per key (both bfloat16) go to the workspace.
+// Output blocks: per (head, layer), the output row merged from the chunk
+// partials.  Fold blocks: per (chunk, layer), the chunk's scores A[j] = gamma
+// A[j] + sum_h p_hj from p~ and one factor per head; in a generation step with
+// one eviction due the layer's last fold block does it.
 #include <algorithm>
 #include <atomic>
 #include <random>
@@ -176,6 +172,7 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     // Lane (r16, q4) holds K channels 8 (q4 + 4 s) .. + 7 of its K rows and V
     // channels 8 r16 .. + 7 of its V rows (the tile layouts below).
     const int rr = len - kw0;
+    if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l] = 0;  // counted by the finishing launch
     const bool writer = rr >= 0 && rr < VT;  // wave-uniform
     uint4 kn_row[KSTEPS], vn_row;
     if (writer) {
@@ -515,7 +512,7 @@ __device__ __forceinline__ void fold_load(const ConstPartials& part, size_t chun
     }
 }
 __device__ __forceinline__ void fold_finish(const FusedArgs& a, const FoldLoads& ld, const float* s_f, float* sc, int Hq,
-                                            int nk, bool new_key) {
+                                            int nk, bool new_key, bool coherent) {
     __shared__ float s_sum[OUT_THREADS / vz::kWave][CHUNK];
     const int t = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(t / vz::kWave), lane = t % vz::kWave;
@@ -535,7 +532,8 @@ __device__ __forceinline__ void fold_finish(const FusedArgs& a, const FoldLoads&
         float acc = s_sum[0][t];
 #pragma unroll
         for (int v = 1; v < OUT_THREADS / vz::kWave; ++v) acc += s_sum[v][t];
-        *sc = fmaf(a.gamma, new_key ? 0.f : ld.old, acc);  // zero pad of Eq. (6) for the new slot
+        // (zero pad of Eq. (6) for the new slot)
+        vz_sel::store_score(sc, fmaf(a.gamma, new_key ? 0.f : ld.old, acc), coherent);
     }
 }
 
@@ -563,7 +561,7 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_fold_kernel(const FusedArg
     ld.old = *sc;
     if (t < Hq) s_f[t] = Exp2Rel()(m_c, gl.x) * gl.y;
     __syncthreads();
-    fold_finish(a, ld, s_f, sc, Hq, nk, chunk_begin(c) + tk == it.len);
+    fold_finish(a, ld, s_f, sc, Hq, nk, chunk_begin(c) + tk == it.len, false);
 }
 
 // One launch (see finish_in_one_launch).  Blocks [0, n_chunks)
@@ -658,8 +656,23 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
         if (t % 16 == 0 && h < Hq) s_f[h] = Exp2Rel()(m_own[u], st.x) * (1.0f / st.y);
     }
     __syncthreads();
-    fold_finish(a, ld, s_f, sc, Hq, nk, j == it.len);
+    const bool evict = !RAG && a.ev != 0;
+    fold_finish(a, ld, s_f, sc, Hq, nk, j == it.len, evict);
+    if constexpr (!RAG) {
+        if (!evict) return;
+        const vz_sel::EvictOne e{a.cnt, a.ev, a.ev_budget, a.ev_sink, a.ev_M};
+        if (!vz_sel::last_of_layer(e, l, a.n_chunks)) return;
+        const size_t row = static_cast<size_t>(l) * a.plane;
+        const int Hkv = a.Hkv;
+        vz_sel::evict_one_slot<OUT_THREADS, uint16_t, D>(e, a.score + row, a.pos + row, a.k_cache + row * Hkv * D,
+                                                         a.v_cache + row * Hkv * D, static_cast<size_t>(a.plane) * D, Hkv,
+                                                         a.len + 1, a.next_pos + 1);
+    }
 }
+
+// Slots of a cache whose single eviction the folding launch does itself: one
+// block of 128 or 256 threads then looks at every score of the layer.
+constexpr int64_t kEvictOneSlots = 8224;
 
 // Whether a call's outputs and scores are finished in one launch.  `chunks`:
 // of a plane; `blocks`: fold and output blocks of a layer in that launch.
@@ -691,6 +704,7 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
     a.out = static_cast<uint16_t*>(v.out);
     a.ws = static_cast<uint8_t*>(v.ws);
     a.Hq = v.Hq;
+    a.Hkv = NW;
     a.L = v.L;
     a.hdr_bytes = static_cast<int32_t>(vz_decode_hdr_bytes(v.L));
     a.scale_log2 = (v.sm_scale > 0.f ? v.sm_scale : 1.0f / sqrtf(static_cast<float>(D))) * kLog2e;
@@ -709,17 +723,17 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
         a.n_chunks = static_cast<int32_t>((static_cast<int64_t>(v.len) + CHUNK) / CHUNK);  // of len + 1 keys
         a.nc_max = static_cast<int32_t>(vz_decode_chunk_rows(a.plane, 0));
     }
+    if (!RAG) {
+        a.cnt = vz_decode_counters(v.ws);
+        a.tag = vz_call_tag();
+        a.ev = v.ev;
+        a.ev_budget = v.ev_budget;
+        a.ev_sink = v.ev_sink;
+        a.ev_M = v.ev_M;
+        a.ev_kept = v.ev_kept;
+        a.ev_n = v.ev_n;
+    }
     if (vz_decode_range_ok(a.L, NW, RAG ? v.rag.n : 0)) {
-        if (!RAG) {
-            a.cnt = reinterpret_cast<uint64_t*>(a.ws + kHeaderBytes);
-            a.tag = vz_call_tag();
-            a.ev = v.ev;
-            a.ev_budget = v.ev_budget;
-            a.ev_sink = v.ev_sink;
-            a.ev_M = v.ev_M;
-            a.ev_kept = v.ev_kept;
-            a.ev_n = v.ev_n;
-        }
         return vz_launch_decode_range(a, NW, stream);
     }
     hipLaunchKernelGGL((decode_attend_kernel<NW, RAG>), RAG ? dim3(a.n_chunks * NW, a.L) : dim3(a.L * a.n_chunks * NW),
@@ -756,6 +770,10 @@ int64_t vz_decode_chunk_rows(int64_t plane, int32_t n_seqs) {
 
 size_t vz_decode_hdr_bytes(int32_t L) {
     return kHeaderBytes + (static_cast<size_t>(L) * sizeof(uint64_t) + 255) / 256 * 256;
+}
+
+uint64_t* vz_decode_counters(void* ws) {
+    return reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(ws) + kHeaderBytes);
 }
 
 uint32_t vz_call_tag() {
@@ -796,8 +814,11 @@ bool vz_decode_takes_range(const VzDecodeArgs& a) {
            vz_decode_range_ok(a.L, a.Hkv, 0) && vz_decode_range_whole(a.len);
 }
 
-bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget) {
+bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget, bool kept) {
     const int64_t T = static_cast<int64_t>(a.len) + 1;
     const int64_t E = T > budget ? T - budget : 0;
-    return vz_decode_takes_range(a) && a.Hkv <= 4 && E <= vz_sel::kInlineRows;
+    if (vz_decode_takes_range(a)) return a.Hkv <= 4 && E <= vz_sel::kInlineRows;
+    if (E != 1 || kept || T > kEvictOneSlots) return false;
+    if (!vz_decode_fused_ok(a.dtype, a.d, a.Hq, a.Hkv, a.L, a.cap, 0)) return true;  // general path
+    return !vz_decode_range_ok(a.L, a.Hkv, 0) && finish_in_one_launch((static_cast<int64_t>(a.cap) + CHUNK - 1) / CHUNK, 1, a.L, 0);
 }

@@ -34,7 +34,7 @@
 
 #include <type_traits>
 
-#include "vz_internal.h"
+#include "select.h"
 
 namespace {
 
@@ -70,6 +70,7 @@ struct GenericArgs {
     int64_t plane;
     float scale, gamma;
     VzRagged rag;
+    vz_sel::EvictOne ev;              // a single sequence's eviction, by the launch that folds
 };
 
 // Flat chunk f of a layer: false when it holds no work; c = chunk inside the sequence.
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
             T* dst = (tid < CH ? K : V) + static_cast<size_t>(len) * D + o;
             *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>((tid < CH ? kn : vn) + o);
         }
+        if (!RAG && a.ev.on && g == 0 && tid == 2 * CH) a.ev.cnt[l] = 0;  // counted by the launch that folds
         if (g == 0 && tid == 2 * CH) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
     }
     if (r16 >= G) {  // unused head columns
@@ -249,6 +251,15 @@ __device__ __forceinline__ void widen(const uint32_t* x, float* f) {
         if constexpr (DT == VZ_F32) f[i] = __uint_as_float(x[i]);
         else f[i] = __uint_as_float((i & 1) ? x[i / 2] & 0xFFFF0000u : x[i / 2] << 16);
     }
+}
+
+// The eviction of a layer, by the block that folded its last scores.
+template <int NT, class T, int D>
+__device__ void evict_layer(const GenericArgs& a, int l) {
+    const size_t row = static_cast<size_t>(l) * a.plane;
+    vz_sel::evict_one_slot<NT, T, D>(a.ev, a.score + row, a.pos + row, static_cast<T*>(a.k_cache) + row * a.Hkv * D,
+                                     static_cast<T*>(a.v_cache) + row * a.Hkv * D, static_cast<size_t>(a.plane) * D,
+                                     a.Hkv, a.len + 1, a.next_pos + 1);
 }
 
 template <int DT, int D, bool RAG>
@@ -377,7 +388,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
             const float sum = r16 == 0 ? ks[0] : r16 == 1 ? ks[1] : r16 == 2 ? ks[2] : ks[3];
             const int key = k0 + 4 * q4 + r16;
             if (fold) {
-                if (key <= len) sc[key] = fmaf(a.gamma, key < len ? cur.a : 0.f, sum);
+                if (key <= len) vz_sel::store_score(sc + key, fmaf(a.gamma, key < len ? cur.a : 0.f, sum), !RAG && a.ev.on);
             } else {
                 // (the logits of these keys are in registers: only this wave reads them)
                 a.S[ws_row(a, l, it.first + c0 + x / 2, g * G) * kChunk + key % kChunk] = sum;
@@ -413,6 +424,9 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
         else
             run_out(a, l, it.first + c0, g, G, h)[ch] = o;
     }
+    if constexpr (!RAG) {
+        if (fold && a.ev.on && vz_sel::last_of_layer(a.ev, l, rn.n)) evict_layer<kThreads, T, D>(a, l);
+    }
 }
 
 // Fold blocks [0, fold_blocks) of a layer: one chunk's scores, thread = key.
@@ -428,13 +442,18 @@ __global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int
         int c;
         if (!resolve_chunk<RAG>(a, blockIdx.x, it, c)) return;
         const int key = c * kChunk + t;
-        if (key > it.len) return;
-        float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base + key;
-        const float old = *sc;
-        float sum = 0.f;
-#pragma unroll 4
-        for (int g = 0; g < Hkv; ++g) sum += a.S[ws_row(a, l, it.first + c, g * G) * kChunk + t];
-        *sc = fmaf(a.gamma, key < it.len ? old : 0.f, sum);  // zero pad of Eq. (6) for the new slot
+        if (key <= it.len) {
+            float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base + key;
+            const float old = *sc;
+            float sum = 0.f;
+    #pragma unroll 4
+            for (int g = 0; g < Hkv; ++g) sum += a.S[ws_row(a, l, it.first + c, g * G) * kChunk + t];
+            // (zero pad of Eq. (6) for the new slot)
+            vz_sel::store_score(sc, fmaf(a.gamma, key < it.len ? old : 0.f, sum), !RAG && a.ev.on);
+        }
+        if constexpr (!RAG) {
+            if (a.ev.on && vz_sel::last_of_layer(a.ev, l, fold_blocks)) evict_layer<kChunk, typename E::T, D>(a, l);
+        }
         return;
     }
     const int ob = static_cast<int>(blockIdx.x) - fold_blocks, h = ob % Hq, s = ob / Hq;
@@ -487,6 +506,7 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
         a.next_pos = v.next_pos;
         a.n_chunks = chunks = v.len / kChunk + 1;  // of len + 1 keys
         runs = runs_of(chunks, G).n;
+        a.ev = vz_sel::EvictOne{vz_decode_counters(v.ws), v.ev, v.ev_budget, v.ev_sink, v.ev_M};
     }
     hipLaunchKernelGGL((logits_kernel<DT, D, RAG>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
     hipError_t e = hipGetLastError();

@@ -30,9 +30,8 @@ constexpr int kBufferDword3 = 0x00020000;  // raw buffer descriptor word 3 (32-b
 // LDS address is one per-lane base plus an immediate (bank analysis in the
 // design notes): K rows 272 bytes apart (16 rows at one 16-byte column fall on
 // 16 distinct bank groups), V rows 288 bytes apart (4 rows x 32 bytes of a
-// transposed read fall on distinct banks).  (The chunked attend kernel loads
-// its K tiles straight into the MFMA operand layout instead; only its V
-// tiles go through LDS.)
+// transposed read fall on distinct banks).  (The chunked attend kernel
+// keeps its tiles in registers.)
 constexpr int KSTRIDE = 256 + 16;
 constexpr int VSTRIDE = 256 + 32;
 constexpr int TILE_BYTES = VT * VSTRIDE;
@@ -90,7 +89,7 @@ struct FusedArgs {
     int32_t len, next_pos;  // single sequence
     int32_t n_chunks;       // single sequence
     int32_t nc_max;         // chunk rows of the partials per layer (grid bound for a ragged call)
-    int32_t Hq, L, hdr_bytes;
+    int32_t Hq, Hkv, L, hdr_bytes;
     int64_t plane;          // slots per (layer, KV head) plane
     float scale_log2, gamma;
     VzRagged rag;
@@ -100,9 +99,9 @@ struct FusedArgs {
     int32_t n_parts, part_keys, R, FB;
     int32_t MB;   // a ragged call's bound on sequences in several parts
     int32_t cus;  // compute units of the device (the choice of parts)
-    // whole-range path, a single sequence in one part: the last workgroup of
-    // each layer to finish (elected on the arrival counters cnt[L] with the
-    // call's tag) folds the scores (Eq. 6) and, when ev != 0, runs the
+    // a single sequence: the last workgroup of each layer to finish (elected
+    // on the arrival counters cnt[L] with the call's tag) folds the scores
+    // (Eq. 6; whole-range path in one part) and, when ev != 0, runs the
     // eviction of the len + 1 slots (Sec. 3.2.2 Eq. 7-9) with budget ev_budget,
     // ev_sink sinks, an ev_M recent window, optional kept positions ev_kept
     // [L][ev_budget] and the move counts ev_n [L] of the eviction workspace

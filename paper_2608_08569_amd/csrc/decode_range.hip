@@ -212,27 +212,6 @@ __device__ __forceinline__ RangeItem uniform_item(const RangeItem& x) {
     return it;
 }
 
-// Arrival of one workgroup of a layer (thread 0, after every store the others
-// need has completed): a lock-free compare-and-swap on the layer's counter,
-// whose high word is the call's tag and whose low word counts this call's
-// arrivals.  A counter holding another tag (an earlier call, or memory never
-// used) counts as zero, so the workspace needs no initialisation.  Returns
-// true for the n-th arrival, which also resets the counter to 0 (a graph
-// replaying the call with the same tag starts from zero again).  Relaxed
-// device-scope atomics: the data the last arriver reads was written with
-// device-coherent stores that completed before the arrivals.
-__device__ __forceinline__ bool arrive_last(uint64_t* c, uint32_t tag, uint32_t n) {
-    uint64_t cur = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t want;
-    do {
-        want = (static_cast<uint32_t>(cur >> 32) == tag ? cur : static_cast<uint64_t>(tag) << 32) + 1;
-    } while (!__hip_atomic_compare_exchange_weak(c, &cur, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT));
-    const bool last = static_cast<uint32_t>(want) == n;
-    if (last) __hip_atomic_store(c, uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return last;
-}
-
 // Grid (NW, L) for a sequence of one part; NW x L x items, flattened, for
 // parts and ragged calls (KV head fastest, then layer, then item, so a
 // ragged call's items go out in the table's order): workgroup (g, l, r)
@@ -663,7 +642,7 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
         f.n_out = a.ev_n ? a.ev_n + l : nullptr;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's sums have reached the device
         __syncthreads();
-        if (tid == 0) s_last = arrive_last(a.cnt + l, a.tag, NW);
+        if (tid == 0) s_last = vz_sel::arrive_last(a.cnt + l, a.tag, NW);
         __syncthreads();
         if (!s_last) return;
         Sel& sh = *reinterpret_cast<Sel*>(&s_pt[0][0][0][0]);             // the p~ rows are no longer read

@@ -341,9 +341,8 @@ struct VzDecodeArgs {
     // ragged batch (rag.n > 0): len, next_pos and cap above are unused; q, out
     // are [n][L][Hq][d], k_new, v_new [n][L][Hkv][d], planes hold rag.total slots
     VzRagged rag;
-    // a single sequence on the whole-range path in one part
-    // (vz_decode_evicts): the eviction of the len + 1 slots the step leaves
-    // runs in the decode kernel (ev = 1), with these arguments; ev_n is the
+    // a single sequence for which vz_decode_evicts says so: the eviction of
+    // the len + 1 slots the step leaves runs in the decode launches (ev = 1), with these arguments; ev_n is the
     // eviction workspace's move-count array
     int32_t ev, ev_budget, ev_sink, ev_M;
     int32_t* ev_kept;
@@ -402,9 +401,13 @@ hipError_t vz_launch_decode(const VzDecodeArgs& a, hipStream_t stream);
 bool vz_decode_takes_range(const VzDecodeArgs& a);
 // Workspace of the whole-range path (single sequence or ragged batch).
 size_t vz_decode_range_ws_bytes(int32_t L, int32_t Hq, int32_t Hkv, int64_t plane, int32_t n_seqs);
-// Whether a decode call's kernel also runs the eviction of the len + 1 slots
-// it leaves (whole-range path in one part, Hkv <= 4, at most 256 moved rows).
-bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget);
+// Whether a decode call's launches also run the eviction of the len + 1 slots
+// it leaves: on the whole-range path in one part with Hkv <= 4 and at most 256
+// moved rows; on the other paths one eviction (T = budget + 1) with no kept
+// positions asked for.
+bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget, bool kept);
+// The layers' arrival counters of a decode workspace.
+uint64_t* vz_decode_counters(void* ws);
 // A fresh nonzero tag per call (arrival counters of the whole-range path).
 uint32_t vz_call_tag();
 size_t vz_evict_ws_bytes(int32_t L, int64_t plane, int32_t n_seqs);
