@@ -12,6 +12,9 @@
 // the loop keeps four rows in flight per lane.  Accumulation is float32 in row
 // order; the mean is an IEEE division by the span length, so a length-1 span
 // reproduces its row bit for bit.
+#include <algorithm>
+#include <type_traits>
+
 #include "vz_internal.h"
 
 namespace {
@@ -61,6 +64,51 @@ __device__ int ragged_fuse_status(const FuseArgs& a, int s) {
     return VZ_OK;
 }
 
+// Adds rows [b, e) of NC 16-byte columns (gap elements apart) to acc in row
+// order (col: row 0 of the first, stride elements per row), four rows' loads
+// at a time.  bfloat16: the last round's loads past the span read its last row
+// again (a cache hit) and add nothing, so no row waits for another's round
+// trip; a remainder of up to three rows, one load after the other, is most of
+// a span of mean length 4 (48 layers x 4 heads x 32,768 rows: 722 -> 704 us;
+// mean length 1.5: 278 -> 270, 8: 185.5 -> 187).  float32 rows are twice as
+// long and the repeated reads cost what they save (222 against 227 us at 12
+// layers x 20,000 rows): the remainder goes row by row.
+template <int DT, int NC>
+__device__ __forceinline__ void add_rows(const typename vz::Elem<DT>::T* col, size_t stride, int gap, int32_t b,
+                                         int32_t e, float (*acc)[vz::Elem<DT>::kPer16B]) {
+    constexpr int PER = vz::Elem<DT>::kPer16B, ROWS = 4;
+    constexpr bool MASKED = DT == VZ_BF16;
+    auto add = [&](const uint4 (&x)[NC], bool on) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            float f[PER];
+            vz::unpack16<DT>(x[c], f);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) acc[c][i] += on ? f[i] : 0.f;
+        }
+    };
+    auto load = [&](int32_t r, uint4 (&x)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            x[c] = *reinterpret_cast<const uint4*>(col + static_cast<size_t>(r) * stride + c * gap);
+    };
+    int32_t r = b;
+    for (; MASKED ? r < e : r + ROWS <= e; r += ROWS) {
+        uint4 x[ROWS][NC];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) load(MASKED ? min(r + u, e - 1) : r + u, x[u]);
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) add(x[u], !MASKED || r + u < e);
+    }
+    if constexpr (!MASKED) {
+        for (; r < e; ++r) {
+            uint4 x[NC];
+            load(r, x);
+            add(x, true);
+        }
+    }
+}
+
 template <int DT, int D, bool RAG>
 __global__ __launch_bounds__(256) void fuse_spans_kernel(const FuseArgs a) {
     using E = vz::Elem<DT>;
@@ -98,31 +146,11 @@ __global__ __launch_bounds__(256) void fuse_spans_kernel(const FuseArgs a) {
 
     const T* src = static_cast<const T*>(which ? a.v_in : a.k_in) +
                    ((static_cast<size_t>(l) * a.H + h) * static_cast<size_t>(a.in_plane) + in_row) * D + lane * PER;
-    float acc[PER];
+    float sum[1][PER];
+    float* const acc = sum[0];
 #pragma unroll
     for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-
-    int32_t r = b;
-    for (; r + 4 <= e; r += 4) {
-        uint4 x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            x[u] = *reinterpret_cast<const uint4*>(src + static_cast<size_t>(r + u) * D);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float f[PER];
-            vz::unpack16<DT>(x[u], f);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) acc[i] += f[i];
-        }
-    }
-    for (; r < e; ++r) {
-        uint4 x = *reinterpret_cast<const uint4*>(src + static_cast<size_t>(r) * D);
-        float f[PER];
-        vz::unpack16<DT>(x, f);
-#pragma unroll
-        for (int i = 0; i < PER; ++i) acc[i] += f[i];
-    }
+    add_rows<DT, 1>(src, D, 0, b, e, sum);
     const float cnt = static_cast<float>(e - b);
 #pragma unroll
     for (int i = 0; i < PER; ++i) acc[i] = (e > b) ? acc[i] / cnt : 0.f;
@@ -149,12 +177,17 @@ __global__ __launch_bounds__(256) void fuse_spans_kernel(const FuseArgs a) {
 }
 
 // Wide rows (d a multiple of one 16-byte vector, other than 64 and 128): one
-// block of WIDE_THREADS threads per (span, K-or-V, head, layer); thread t
-// owns the 16-byte columns t, t + WIDE_THREADS, ... of the row and sums them
-// over the span's rows in row order (4 rows in flight), as the lane-group
-// kernel does, so the arithmetic is the same.
+// block per (span, K-or-V, head, layer); thread t owns the 16-byte columns t,
+// t + threads, ... of the row, NC of them at a time, and sums them over the
+// span's rows in row order, as the lane-group kernel does, so the arithmetic
+// is the same.  Rows of more than WIDE_THREADS columns take two columns at a
+// time (32,768 rows of 3584 bfloat16, spans of mean length 4: 74.5 -> 68.3 us,
+// 5.15 TB/s, with eight loads in flight per thread instead of one to four);
+// narrower ones one, in a block of as many waves as the row needs (the second
+// column's registers would cost waves in flight: 1032 elements 22.6 us with
+// one column, 27.0 with two).
 constexpr int WIDE_THREADS = 256;
-template <int DT, bool RAG>
+template <int DT, bool RAG, int NC>
 __global__ __launch_bounds__(WIDE_THREADS) void fuse_wide_kernel(const FuseArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
@@ -190,41 +223,33 @@ __global__ __launch_bounds__(WIDE_THREADS) void fuse_wide_kernel(const FuseArgs 
     const size_t orow = (static_cast<size_t>(l) * a.H + h) * static_cast<size_t>(a.out_plane) + out_row + j;
     const size_t arow = RAG ? orow : (static_cast<size_t>(l) * a.H + h) * static_cast<size_t>(n_spans) + j;
     T* dst = static_cast<T*>(which ? a.v_out : a.k_out) + orow * a.d;
-    for (int c = threadIdx.x; c < nv; c += WIDE_THREADS) {
-        const T* col = src + c * PER;
-        float acc[PER];
+    const int threads = blockDim.x;
+    auto columns = [&](auto n, int c0) {
+        constexpr int N = decltype(n)::value;
+        float acc[N][PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-        int32_t r = b;
-        for (; r + 4 <= e; r += 4) {
-            uint4 x[4];
+        for (int k = 0; k < N; ++k)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const uint4*>(col + static_cast<size_t>(r + u) * a.d);
+            for (int i = 0; i < PER; ++i) acc[k][i] = 0.f;
+        add_rows<DT, N>(src + c0 * PER, a.d, WIDE_THREADS * PER, b, e, acc);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+        for (int k = 0; k < N; ++k) {
+            const int c = c0 + k * WIDE_THREADS;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) acc[k][i] = (e > b) ? acc[k][i] / cnt : 0.f;
+            if (anchor) {
+                const uint4 x = *reinterpret_cast<const uint4*>(anchor + arow * a.d + c * PER);
                 float f[PER];
-                vz::unpack16<DT>(x[u], f);
+                vz::unpack16<DT>(x, f);
 #pragma unroll
-                for (int i = 0; i < PER; ++i) acc[i] += f[i];
+                for (int i = 0; i < PER; ++i) acc[k][i] += f[i];
             }
+            *reinterpret_cast<uint4*>(dst + c * PER) = vz::pack16<DT>(acc[k]);
         }
-        for (; r < e; ++r) {
-            const uint4 x = *reinterpret_cast<const uint4*>(col + static_cast<size_t>(r) * a.d);
-            float f[PER];
-            vz::unpack16<DT>(x, f);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) acc[i] += f[i];
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) acc[i] = (e > b) ? acc[i] / cnt : 0.f;
-        if (anchor) {
-            const uint4 x = *reinterpret_cast<const uint4*>(anchor + arow * a.d + c * PER);
-            float f[PER];
-            vz::unpack16<DT>(x, f);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) acc[i] += f[i];
-        }
-        *reinterpret_cast<uint4*>(dst + c * PER) = vz::pack16<DT>(acc);
+    };
+    for (int c = threadIdx.x; c < nv; c += NC * threads) {
+        if (NC > 1 && c + WIDE_THREADS < nv) columns(std::integral_constant<int, NC>{}, c);
+        else columns(std::integral_constant<int, 1>{}, c);
     }
     if (which == 0 && h == 0 && threadIdx.x == 0) {
         const size_t prow = static_cast<size_t>(l) * a.out_plane + out_row + j;
@@ -233,19 +258,25 @@ __global__ __launch_bounds__(WIDE_THREADS) void fuse_wide_kernel(const FuseArgs 
     }
 }
 
-template <int DT>
+template <int DT, int NC>
 hipError_t launch_wide(const FuseArgs& a, int32_t L, hipStream_t stream) {
+    const int nv = a.d / vz::Elem<DT>::kPer16B;
+    const dim3 block(std::min(WIDE_THREADS, (nv + vz::kWave - 1) / vz::kWave * vz::kWave));
     if (a.n_seqs > 0) {
         FuseArgs r = a;
         r.blocks_per_seq = a.max_spans > 0 ? a.max_spans : 1;  // still report every sequence's status
         dim3 grid(static_cast<unsigned>(static_cast<int64_t>(r.blocks_per_seq) * a.n_seqs), a.kinds * a.H, L);
-        hipLaunchKernelGGL((fuse_wide_kernel<DT, true>), grid, dim3(WIDE_THREADS), 0, stream, r);
+        hipLaunchKernelGGL((fuse_wide_kernel<DT, true, NC>), grid, block, 0, stream, r);
         return hipGetLastError();
     }
     if (a.n_spans == 0) return hipSuccess;
     dim3 grid(a.n_spans, a.kinds * a.H, L);
-    hipLaunchKernelGGL((fuse_wide_kernel<DT, false>), grid, dim3(WIDE_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((fuse_wide_kernel<DT, false, NC>), grid, block, 0, stream, a);
     return hipGetLastError();
+}
+template <int DT>
+hipError_t launch_wide_any(const FuseArgs& a, int32_t L, hipStream_t stream) {
+    return a.d / vz::Elem<DT>::kPer16B > WIDE_THREADS ? launch_wide<DT, 2>(a, L, stream) : launch_wide<DT, 1>(a, L, stream);
 }
 
 template <int DT, int D>
@@ -272,8 +303,8 @@ hipError_t dispatch(FuseArgs a, int32_t L, int32_t d, int32_t dtype, hipStream_t
     if (dtype == VZ_BF16 && d == 64) return launch<VZ_BF16, 64>(a, L, stream);
     if (dtype == VZ_F32 && d == 128) return launch<VZ_F32, 128>(a, L, stream);
     if (dtype == VZ_F32 && d == 64) return launch<VZ_F32, 64>(a, L, stream);
-    if (dtype == VZ_BF16 && d % vz::Elem<VZ_BF16>::kPer16B == 0) return launch_wide<VZ_BF16>(a, L, stream);
-    if (dtype == VZ_F32 && d % vz::Elem<VZ_F32>::kPer16B == 0) return launch_wide<VZ_F32>(a, L, stream);
+    if (dtype == VZ_BF16 && d % vz::Elem<VZ_BF16>::kPer16B == 0) return launch_wide_any<VZ_BF16>(a, L, stream);
+    if (dtype == VZ_F32 && d % vz::Elem<VZ_F32>::kPer16B == 0) return launch_wide_any<VZ_F32>(a, L, stream);
     return hipErrorInvalidValue;
 }
 

@@ -231,3 +231,26 @@ def test_fuse_ragged_wide_rows_k_only():
         n, b, ib = n_sp[i], int(seq_base[i]), int(in_base[i])
         ref = oracle.fuse(x[:, :, ib:ib + T_in[i]], offs[i], dtype, anchor=anc[:, :, b:b + n])
         check_close(widen(k[:, :, b:b + n], dtype), ref, RTOL[dtype], f"sequence {i}")
+
+
+@pytest.mark.parametrize("dtype,d", [(synth.DT_BF16, 8), (synth.DT_BF16, 520), (synth.DT_BF16, 2048),
+                                     (synth.DT_BF16, 2056), (synth.DT_BF16, 4096), (synth.DT_BF16, 4104),
+                                     (synth.DT_F32, 1024), (synth.DT_F32, 1028), (synth.DT_F32, 2052)])
+def test_fuse_wide_rows_at_the_column_rounds(dtype, d):
+    """1, 65, 256, 257, 512 and 513 vectors per row: one column per thread, two
+    at a time, and a second column or round that only some threads have; one
+    tensor, rows that end in infinities behind the spans that must not see
+    them."""
+    key = synth.stream_key(19, "fuse-rounds", dtype, d)
+    lens = np.array([1, 2, 3, 4, 5, 7, 8, 9, 1, 6], dtype=np.int64)
+    off = synth.offsets_from_lengths(lens)
+    T, n = int(off[-1]), len(lens)
+    x = synth.as_storage(synth.normal_f32(key, T * d).reshape(1, 1, T, d), dtype)
+    x[0, 0, off[3] - 1] = np.float32(np.inf) if dtype == synth.DT_F32 else 0x7F80  # last row of a 3-row span
+    k, _, s, p, sen = _fuse_wide(x, None, off, dtype, n + 2)
+    inf = synth.storage_to_f64(k, dtype)[0, 0, :n]
+    assert np.all(np.isposinf(inf[2])) and np.all(np.isfinite(np.delete(inf, 2, axis=0)))
+    ref = oracle.fuse(x, off, dtype)[0, 0]
+    for j in range(n):
+        if j != 2:
+            assert np.all(np.abs(inf[j] - ref[j]) <= RTOL[dtype] * (np.abs(ref[j]) + np.sqrt(np.mean(ref[j] ** 2)))), j
