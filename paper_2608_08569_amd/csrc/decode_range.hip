@@ -32,10 +32,10 @@ using namespace vz_mfma;
 // of p_hj goes to the workspace.  For a sequence in one part, the last of a
 // layer's workgroups to finish then adds the KV heads' sums into Eq. (6) and,
 // in a generation step, runs the eviction of Sec. 3.2.2 for the layer (see
-// arrive_last); no workgroup ever waits for another.  For ragged calls a fold
-// kernel adds the sums.  A part of a longer sequence instead leaves its statistics,
-// output and per-head probabilities relative to its own max, which a merge
-// kernel and the fold combine.  Compared with the chunked path there are no
+// arrive_last); no workgroup ever waits for another.  For ragged calls a
+// finishing launch adds the sums.  A part of a longer sequence instead leaves its statistics,
+// output and per-head probabilities relative to its own max, which a finishing
+// launch combines.  Compared with the chunked path there are no
 // per-chunk partial outputs or probabilities in HBM; it needs enough (layer,
 // KV head) items to occupy the GPU, one workgroup per CU.
 constexpr int RW = 8;                              // waves per workgroup (256 registers per lane)
@@ -109,7 +109,6 @@ static_assert(sizeof(RangeItem) == 64, "one 64-byte record per item");
 //                                      its part's max (sequences of several parts)
 //   pstat [L][Hkv][R][GMAX] float2     each part's max and sum of exp2, per head
 //   pout  [L][Hkv][R][GMAX][D] float   each part's output relative to its max
-//   ftab  [L][R][Hq] float             exp2(m_part - M) / S per part and head
 //   items [R] RangeItem                a ragged call's parts, in dispatch order
 //   fblk  [FB] int2                    a ragged call's fold blocks: (item, first key)
 //   mlist [MB] int32                   a ragged call's sequences in several parts:
@@ -123,7 +122,6 @@ struct RangeWs {
     uint16_t* rows;
     float2* pstat;
     float* pout;
-    float* ftab;
     RangeItem* items;
     int2* fblk;
     int32_t* mlist;
@@ -133,7 +131,7 @@ struct RangeWs {
 __host__ __device__ inline size_t ws_align(size_t x) { return (x + 255) / 256 * 256; }
 // Byte offsets of the arrays from the start of the workspace; returns the end.
 __host__ __device__ inline size_t range_layout(size_t hdr, int L, int NW, int Hq, int64_t plane, int R, int FB,
-                                               int MB, bool ragged, size_t off[8]) {
+                                               int MB, bool ragged, size_t off[7]) {
     const size_t row = static_cast<size_t>(range_row(plane));
     const size_t heads = static_cast<size_t>(L) * NW;
     const bool parts = plane > RANGE_MAX_KEYS;
@@ -147,28 +145,25 @@ __host__ __device__ inline size_t range_layout(size_t hdr, int L, int NW, int Hq
     off[3] = o;
     if (parts) o = ws_align(o + heads * R * GMAX * D * sizeof(float));
     off[4] = o;
-    if (parts) o = ws_align(o + static_cast<size_t>(L) * R * Hq * sizeof(float));
-    off[5] = o;
     if (ragged) o = ws_align(o + static_cast<size_t>(R) * sizeof(RangeItem));
-    off[6] = o;
+    off[5] = o;
     if (ragged) o = ws_align(o + static_cast<size_t>(FB) * sizeof(int2));
-    off[7] = o;
+    off[6] = o;
     if (ragged) o = ws_align(o + static_cast<size_t>(MB) * sizeof(int32_t));
     return o;
 }
 template <int NW>
 __device__ __forceinline__ RangeWs range_ws(const FusedArgs& a, bool ragged) {
-    size_t off[8];
+    size_t off[7];
     range_layout(a.hdr_bytes, a.L, NW, a.Hq, a.plane, a.R, a.FB, a.MB, ragged, off);
     RangeWs w;
     w.sums = reinterpret_cast<float*>(a.ws + off[0]);
     w.rows = reinterpret_cast<uint16_t*>(a.ws + off[1]);
     w.pstat = reinterpret_cast<float2*>(a.ws + off[2]);
     w.pout = reinterpret_cast<float*>(a.ws + off[3]);
-    w.ftab = reinterpret_cast<float*>(a.ws + off[4]);
-    w.items = reinterpret_cast<RangeItem*>(a.ws + off[5]);
-    w.fblk = reinterpret_cast<int2*>(a.ws + off[6]);
-    w.mlist = reinterpret_cast<int32_t*>(a.ws + off[7]);
+    w.items = reinterpret_cast<RangeItem*>(a.ws + off[4]);
+    w.fblk = reinterpret_cast<int2*>(a.ws + off[5]);
+    w.mlist = reinterpret_cast<int32_t*>(a.ws + off[6]);
     w.counts = reinterpret_cast<int32_t*>(a.ws);
     w.row = range_row(a.plane);
     return w;
@@ -651,66 +646,65 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
     }
 }
 
-// Merge of a sequence in parts, one block per (sequence in parts, layer,
-// pair of query heads) -- a ragged call's sequences in parts are listed by
-// the order kernel, a single sequence is item 0 -- and thread t takes
-// channel t % D of head 2 hb + t / D.  Per head, the sequence's max M and sum S from the parts'
-// pairs, each part's factor exp2(m_part - M) / S (kept for the fold), and the
-// output row, the parts' outputs times their factors, added in part order.
-// (Every thread of a head forms M, S and the factors itself, from the same
-// few pairs; a block per (sequence, layer) over all heads left the call's
-// merge on 48 CUs at a time.)
-constexpr int RMERGE_THREADS = 2 * D;
-constexpr int RMERGE_HEADS = RMERGE_THREADS / D;
-template <int NW, bool RAG>
-__global__ __launch_bounds__(RMERGE_THREADS) void range_merge_kernel(const FusedArgs a) {
-    const int l = blockIdx.y, t = threadIdx.x;
-    const RangeWs rws = range_ws<NW>(a, RAG);
-    int r = 0;
-    RangeItem it;
-    if constexpr (RAG) {
-        if (static_cast<int>(blockIdx.x) >= rws.counts[2]) return;
-        r = rws.mlist[blockIdx.x];
-        it = rws.items[r];
-    } else {
-        it = single_item(a, r);
-    }
-    if (it.P == 1 || it.p != 0) return;
-    const int Hq = a.Hq, G = Hq / NW, P = it.P;
-    const int h = static_cast<int>(blockIdx.z) * RMERGE_HEADS + t / D, ch = t % D;
-    if (h >= Hq) return;
-    const int g = h / G, hg = h - g * G;
-    const float2* ps = rws.pstat + ((static_cast<size_t>(l) * NW + g) * a.R + r) * GMAX + hg;
-    float M = -INFINITY;
+// Max M and sum S of a head over the parts of a sequence from the parts' pairs
+// (ps: the first part's, pairs GMAX apart).
+__device__ __forceinline__ float2 parts_stats(const float2* ps, int P) {
+    float M = -INFINITY, S = 0.f;
     for (int p = 0; p < P; ++p) M = fmaxf(M, ps[static_cast<size_t>(p) * GMAX].x);
-    float S = 0.f;
     for (int p = 0; p < P; ++p) {
         const float2 x = ps[static_cast<size_t>(p) * GMAX];
         S = fmaf(x.y, exp2f(x.x - M), S);
     }
-    const float inv_S = 1.0f / S;
-    const float* po = rws.pout + (((static_cast<size_t>(l) * NW + g) * a.R + r) * GMAX + hg) * D + ch;
-    float o = 0.f;
-    for (int p = 0; p < P; ++p) {
-        const float f = exp2f(ps[static_cast<size_t>(p) * GMAX].x - M) * inv_S;
-        if (ch == 0) rws.ftab[(static_cast<size_t>(l) * a.R + r + p) * Hq + h] = f;
-        o = fmaf(po[static_cast<size_t>(p) * GMAX * D], f, o);
-    }
-    a.out[((static_cast<size_t>(it.s) * a.L + l) * Hq + h) * D + ch] = vz::f32_to_bf16(o);
+    return make_float2(M, S);
 }
 
-// Fold kernel of a ragged call or of a sequence in parts, one block of
-// RFOLD_KEYS threads per fold block (keys of one item), thread = key: Eq. (6)
-// from the KV heads' sums added in head order (a sequence of one part, the
-// same arithmetic as the single-part fold kernel), or from each key's
-// per-head rows and its part's factors.
+// Finishing launch of a ragged call or of a sequence in parts.  Blocks
+// [0, folds) of a layer fold scores, one per RFOLD_KEYS keys of one item,
+// thread = key: Eq. (6) from the KV heads' sums added in head order (a
+// sequence of one part, the arithmetic of the single-part fold), or from each
+// key's per-head rows times its part's factors exp2(m_part - M) / S, which the
+// block forms itself from the parts' few pairs.  The blocks after them write
+// the output rows of the sequences in parts, one per (sequence in parts, pair
+// of query heads) -- a ragged call's are listed by the order kernel, a single
+// sequence is item 0 -- and thread t takes channel t % D of head 2 hb + t / D:
+// the parts' outputs times their factors, added in part order.
+// (One launch: as two, the merge of a few rows -- of none, in a batch of
+// sequences in one part whose planes could hold longer ones -- was 4.7 us and
+// a gap of its own beside 9.5 us of folding: RANGE_FINISH_TIMES.)
+constexpr int RMERGE_HEADS = RFOLD_KEYS / D;
+__host__ __device__ inline int merge_blocks(int Hq) { return (Hq + RMERGE_HEADS - 1) / RMERGE_HEADS; }
 template <int NW, bool RAG>
-__global__ __launch_bounds__(RFOLD_KEYS) void range_fold_parts_kernel(const FusedArgs a) {
+__global__ __launch_bounds__(RFOLD_KEYS) void range_finish_kernel(const FusedArgs a, int folds) {
     __shared__ float s_f[NW * GMAX];
     const int b = blockIdx.x, l = blockIdx.y, t = threadIdx.x;
     const RangeWs rws = range_ws<NW>(a, RAG);
-    int r, j0;
+    const int Hq = a.Hq, G = Hq / NW;
+    int r = 0;
     RangeItem it;
+    if (b >= folds) {
+        const int m = (b - folds) / merge_blocks(Hq), hb = (b - folds) % merge_blocks(Hq);
+        if constexpr (RAG) {
+            if (m >= rws.counts[2]) return;
+            r = rws.mlist[m];
+            it = rws.items[r];
+        } else {
+            it = single_item(a, r);
+        }
+        const int P = it.P, h = hb * RMERGE_HEADS + t / D, ch = t % D;
+        if (P == 1 || it.p != 0 || h >= Hq) return;
+        const int g = h / G, hg = h - g * G;
+        const size_t row = ((static_cast<size_t>(l) * NW + g) * a.R + r) * GMAX + hg;
+        const float2* ps = rws.pstat + row;
+        const float2 st = parts_stats(ps, P);
+        const float inv_S = 1.0f / st.y;
+        const float* po = rws.pout + row * D + ch;
+        float o = 0.f;
+        for (int p = 0; p < P; ++p)
+            o = fmaf(po[static_cast<size_t>(p) * GMAX * D], exp2f(ps[static_cast<size_t>(p) * GMAX].x - st.x) * inv_S, o);
+        a.out[((static_cast<size_t>(it.s) * a.L + l) * Hq + h) * D + ch] = vz::f32_to_bf16(o);
+        return;
+    }
+    int j0;
     if constexpr (RAG) {
         if (b >= rws.counts[1]) return;
         const int2 e = rws.fblk[b];
@@ -737,14 +731,19 @@ __global__ __launch_bounds__(RFOLD_KEYS) void range_fold_parts_kernel(const Fuse
 #pragma unroll
         for (int g = 1; g < NW; ++g) acc += gs[g * rws.row];
     } else {
-        const int Hq = a.Hq, G = Hq / NW;
         uint4 rw[NW];
 #pragma unroll
         for (int g = 0; g < NW; ++g)
             rw[g] = *reinterpret_cast<const uint4*>(rws.rows + ((static_cast<size_t>(l) * NW + g) * rws.row + slot) * GMAX);
         if (t < NW * GMAX) {
             const int g = t / GMAX, hg = t - g * GMAX;
-            s_f[t] = hg < G ? rws.ftab[(static_cast<size_t>(l) * a.R + r) * Hq + g * G + hg] : 0.f;
+            const float2* ps = rws.pstat + ((static_cast<size_t>(l) * NW + g) * a.R + r - it.p) * GMAX + hg;
+            float f = 0.f;
+            if (hg < G) {
+                const float2 st = parts_stats(ps, it.P);
+                f = exp2f(ps[static_cast<size_t>(it.p) * GMAX].x - st.x) * (1.0f / st.y);
+            }
+            s_f[t] = f;
         }
         __syncthreads();
         acc = 0.f;
@@ -774,9 +773,12 @@ constexpr int ORDER_THREADS = RANGE_MAX_SEQS;
 template <int NW>
 __device__ __forceinline__ void order_seq(const FusedArgs& a, int s, int& st, int& T, int& P, int& kp, int& F) {
     T = P = kp = F = 0;
-    st = vz::ragged_decode_status(a.rag, s);
-    if (st == VZ_OK) {
-        T = a.rag.len[s] + 1;
+    const int64_t b = a.rag.base[s];  // (every load before any check)
+    const int c = a.rag.cap[s], n = a.rag.len[s], np = a.rag.next_pos[s];
+    const bool ok = vz::decode_served(b, c, n, np, a.rag.total);
+    st = ok ? VZ_OK : vz::decode_status_of(b, c, n, np, a.rag.total);
+    if (ok) {
+        T = n + 1;
         range_parts(T, a.L * NW, a.cus, P, kp);
         F = range_fold_blocks(T, P, kp);
     }
@@ -968,24 +970,20 @@ int32_t ragged_fold_bound(int32_t n_seqs, int64_t total) {
 
 template <int NW>
 hipError_t launch_range(const FusedArgs& a, hipStream_t stream) {
+    const int merges = merge_blocks(a.Hq);  // per sequence in parts and layer
     if (a.rag.n > 0) {
         hipLaunchKernelGGL((range_order_kernel<NW>), dim3(1), dim3(ORDER_THREADS), 0, stream, a);
         hipLaunchKernelGGL((decode_range_kernel<NW, true, true>), dim3(NW * a.L * a.R), dim3(64 * RW), 0, stream, a);
-        if (a.MB > 0)
-            hipLaunchKernelGGL((range_merge_kernel<NW, true>),
-                               dim3(a.MB, a.L, (a.Hq + RMERGE_HEADS - 1) / RMERGE_HEADS), dim3(RMERGE_THREADS), 0,
-                               stream, a);
-        hipLaunchKernelGGL((range_fold_parts_kernel<NW, true>), dim3(a.FB, a.L), dim3(RFOLD_KEYS), 0, stream, a);
+        hipLaunchKernelGGL((range_finish_kernel<NW, true>), dim3(a.FB + a.MB * merges, a.L), dim3(RFOLD_KEYS), 0, stream,
+                           a, a.FB);
         return hipGetLastError();
     }
     if (a.n_parts > 1) {
         hipLaunchKernelGGL((decode_range_kernel<NW, false, true>), dim3(NW * a.L * a.n_parts), dim3(64 * RW), 0,
                            stream, a);
-        hipLaunchKernelGGL((range_merge_kernel<NW, false>), dim3(1, a.L, (a.Hq + RMERGE_HEADS - 1) / RMERGE_HEADS),
-                           dim3(RMERGE_THREADS), 0, stream, a);
-        hipLaunchKernelGGL((range_fold_parts_kernel<NW, false>),
-                           dim3(range_fold_blocks(a.len + 1, a.n_parts, a.part_keys), a.L), dim3(RFOLD_KEYS), 0,
-                           stream, a);
+        const int folds = range_fold_blocks(a.len + 1, a.n_parts, a.part_keys);
+        hipLaunchKernelGGL((range_finish_kernel<NW, false>), dim3(folds + merges, a.L), dim3(RFOLD_KEYS), 0, stream, a,
+                           folds);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((decode_range_kernel<NW, false, false>), dim3(NW, a.L), dim3(64 * RW), 0, stream, a);
@@ -1023,7 +1021,7 @@ hipError_t vz_launch_decode_range(const FusedArgs& a0, int32_t Hkv, hipStream_t 
 bool vz_decode_range_whole(int32_t len) { return static_cast<int64_t>(len) + 1 <= RANGE_MAX_KEYS; }
 
 size_t vz_decode_range_ws_bytes(int32_t L, int32_t Hq, int32_t Hkv, int64_t plane, int32_t n_seqs) {
-    size_t off[8];
+    size_t off[7];
     const bool rag = n_seqs > 0;
     const int R = rag ? ragged_items_bound(n_seqs, plane) : single_parts_bound(plane);
     const int FB = rag ? ragged_fold_bound(n_seqs, plane) : 0;
