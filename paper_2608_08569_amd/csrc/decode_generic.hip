@@ -27,9 +27,9 @@
 // and small ones by the launches and the round trips inside each.  Measured
 // (kernel times, before: one thread per key for the logits, one workgroup per
 // (layer, head) for softmax and P V, one thread per key for the scores):
-//   16 layers, 16Q/4KV, d = 128, float32, 2049 keys   365 -> 39 us (3.5 TB/s)
-//   24 layers, 14Q/2KV, d = 64, bfloat16, 4001 keys   345 -> 27 us (1.8 TB/s)
-//   1 layer, 4Q/1KV, d = 64, float32, 129 keys        22.4 -> 9.4 us
+//   16 layers, 16Q/4KV, d = 128, float32, 2049 keys   365 -> 38 us (3.6 TB/s)
+//   24 layers, 14Q/2KV, d = 64, bfloat16, 4001 keys   345 -> 25 us (2.0 TB/s)
+//   1 layer, 4Q/1KV, d = 64, float32, 129 keys        22.4 -> 10.5 us (with the eviction)
 #include <math.h>
 
 #include <type_traits>
@@ -40,6 +40,7 @@ namespace {
 
 using vz::SeqItem;
 using vz::kChunk;
+using vz_sel::kBufferDword3;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -118,12 +119,15 @@ __device__ __forceinline__ float* run_out(const GenericArgs& a, int l, int row, 
 // exp(x - m), 0 for an absent x (-inf, also when m is -inf).
 __device__ __forceinline__ float exp_rel(float x, float m) { return x == -INFINITY ? 0.f : expf(x - m); }
 
-template <int DT, int D, bool RAG>
+// PACK: groups of at most 8 heads, whose second tile's logits are rotated into
+// head columns 8..15, so every exp serves a key and a head that exist.
+template <int DT, int D, bool RAG, bool PACK>
 __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
     constexpr int PER = E::kPer16B;
     constexpr int NV = D / (4 * PER);  // 16-byte pieces of a row per lane: channels 4 PER s + PER q4 ..
+    constexpr int NS = PACK ? 1 : 2;   // sets of four logits per lane
     __shared__ float s_m[kWaves][kHeads], s_l[kWaves][kHeads];
     const int l = blockIdx.y, g = blockIdx.z;
     SeqItem it;
@@ -143,12 +147,24 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
     // rows of the wave's two tiles (past the new one: the new row again, masked)
     const int k0 = c * kChunk + kKeysPerWave * w;
     uint4 kr[2][NV], qr[NV];
+    if (k0 + kKeysPerWave <= len) {  // wave-uniform: all in the cache, one address and immediate offsets
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(K + static_cast<size_t>(k0) * D, 0,
+                                                                            kKeysPerWave * D * sizeof(T), kBufferDword3);
+        const int off = (r16 * D + PER * q4) * static_cast<int>(sizeof(T));
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti) {
-        const int key = k0 + 16 * ti + r16;
-        const T* row = key < len ? K + static_cast<size_t>(key) * D : kn;
+        for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-        for (int s = 0; s < NV; ++s) kr[ti][s] = *reinterpret_cast<const uint4*>(row + PER * (4 * s + q4));
+            for (int s = 0; s < NV; ++s)
+                kr[ti][s] = __builtin_bit_cast(
+                    uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off + 64 * s, ti * 16 * D * sizeof(T), 0));
+    } else {
+#pragma unroll
+        for (int ti = 0; ti < 2; ++ti) {
+            const int key = k0 + 16 * ti + r16;
+            const T* row = key < len ? K + static_cast<size_t>(key) * D : kn;
+#pragma unroll
+            for (int s = 0; s < NV; ++s) kr[ti][s] = *reinterpret_cast<const uint4*>(row + PER * (4 * s + q4));
+        }
     }
     {
         const T* row = static_cast<const T*>(a.q) + (row_sl * Hq + g * G + min(r16, G - 1)) * D;
@@ -170,11 +186,10 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
 #pragma unroll
         for (int s = 0; s < NV; ++s) qr[s] = make_uint4(0, 0, 0, 0);
     }
-    float* const S = a.S + ws_row(a, l, it.first + c, g * G + r16) * kChunk + kKeysPerWave * w;
-    float sv[2][4], m_w = -INFINITY;
+    f32x4 acc[2];
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc[ti] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < NV; ++s) {
             if constexpr (DT == VZ_F32) {
@@ -183,30 +198,44 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
                 const float qf[4] = {__uint_as_float(qr[s].x), __uint_as_float(qr[s].y), __uint_as_float(qr[s].z),
                                      __uint_as_float(qr[s].w)};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[i], acc, 0, 0, 0);
+                for (int i = 0; i < 4; ++i)
+                    acc[ti] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[i], acc[ti], 0, 0, 0);
             } else {
                 bf16x8_t kf, qf;
                 __builtin_memcpy(&kf, &kr[ti][s], 16);
                 __builtin_memcpy(&qf, &qr[s], 16);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf, acc, 0, 0, 0);
+                acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf, acc[ti], 0, 0, 0);
             }
         }
-        // lane: head r16, keys 16 ti + 4 q4 + i
+    }
+    // lane: head hc, keys 16 (ti or half) + 4 q4 + i
+    const int hc = PACK ? r16 & 7 : r16, half = PACK ? r16 >> 3 : 0;
+    float* const S = a.S + ws_row(a, l, it.first + c, g * G + hc) * kChunk + kKeysPerWave * w + 16 * half + 4 * q4;
+    float sv[NS][4], m_w = -INFINITY;
+#pragma unroll
+    for (int ti = 0; ti < NS; ++ti) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            sv[ti][i] = k0 + 16 * ti + 4 * q4 + i <= len ? acc[i] * a.scale : -INFINITY;
+            float x = acc[ti][i];
+            if constexpr (PACK) {
+                const float second = vz::ror16<8>(acc[1][i]);
+                x = half ? second : x;
+            }
+            sv[ti][i] = k0 + 16 * (ti + half) + 4 * q4 + i <= len ? x * a.scale : -INFINITY;
             m_w = fmaxf(m_w, sv[ti][i]);
         }
-        if (r16 < G)
-            *reinterpret_cast<float4*>(S + 16 * ti + 4 * q4) = make_float4(sv[ti][0], sv[ti][1], sv[ti][2], sv[ti][3]);
+        if (hc < G)
+            *reinterpret_cast<float4*>(S + 16 * ti) = make_float4(sv[ti][0], sv[ti][1], sv[ti][2], sv[ti][3]);
     }
     m_w = vz::rows_max(m_w);
+    if constexpr (PACK) m_w = fmaxf(m_w, vz::ror16<8>(m_w));
     float l_w = 0.f;
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int ti = 0; ti < NS; ++ti)
 #pragma unroll
         for (int i = 0; i < 4; ++i) l_w += exp_rel(sv[ti][i], m_w);
     l_w = vz::rows_sum(l_w);
+    if constexpr (PACK) l_w += vz::ror16<8>(l_w);
     if (q4 == 0) {
         s_m[w][r16] = m_w;
         s_l[w][r16] = l_w;
@@ -243,6 +272,19 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(const GenericArgs a) {
     if (i == 0 && h < a.Hq) a.layer[(static_cast<size_t>(s) * a.L + l) * a.Hq + h] = st;
 }
 
+// Sums over the lanes of a DPP row that hold a key's heads, in every lane: all
+// 16, or (PACK) the 8 of each half row.
+template <bool PACK>
+__device__ __forceinline__ float heads_sum(float v) {
+    if constexpr (!PACK) return vz::row16_sum(v);
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    v += dpp(v, std::integral_constant<int, 0xB1>{});         // quad_perm [1, 0, 3, 2]
+    v += dpp(v, std::integral_constant<int, 0x4E>{});         // quad_perm [2, 3, 0, 1]
+    return v + dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+}
+
 // Values of a row piece (four or eight channels of one key) as floats.
 template <int DT, int PER>
 __device__ __forceinline__ void widen(const uint32_t* x, float* f) {
@@ -262,7 +304,11 @@ __device__ void evict_layer(const GenericArgs& a, int l) {
                                      a.Hkv, a.len + 1, a.next_pos + 1);
 }
 
-template <int DT, int D, bool RAG>
+// PACK (groups of at most 8 heads): lanes r16 >= 8 of a row hold the heads of
+// the second 16 keys of a wave's 32, so every exp serves a key and a head that
+// exist; a rotation by 8 lanes makes them the second tile's B operand (the
+// other columns of either product hold heads that are not read).
+template <int DT, int D, bool RAG, bool PACK>
 __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
@@ -273,7 +319,8 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     constexpr int NP = D / (16 * PER);
     constexpr int NT = D / 16;                          // output tiles
     constexpr int WORDS = PER * sizeof(T) / 4;
-    constexpr int DEPTH = NP * WORDS >= 8 ? 2 : 4;      // tiles in flight per wave (32 or 16 registers each, or 8)
+    constexpr int DEPTH = NP * WORDS <= 2 ? 2 : 1;      // 32-key units in flight per wave (16, 32 or 64 registers each)
+    constexpr int NS = PACK ? 1 : 2;                    // logit pieces of a unit per lane
     __shared__ float s_o[kWaves][kHeads][D + 4];
     __shared__ float2 s_stat[kHeads];
     const int l = blockIdx.y, g = blockIdx.z;
@@ -297,6 +344,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / vz::kWave), lane = tid % vz::kWave;
     const int q4 = lane >> 4, r16 = lane & 15;
+    const int hc = PACK ? r16 & 7 : r16, half = PACK ? r16 >> 3 : 0;  // the lane's head, and 16 keys of a unit
     const int len = it.len;
     const size_t row_sl = static_cast<size_t>(it.s) * a.L + l;
     const T* const V =
@@ -304,105 +352,138 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     float* const sc = a.score + static_cast<size_t>(l) * a.plane + it.base;
     const bool fold = a.Hkv == 1;  // one KV head: its key sums are the whole of Eq. (6)'s
 
-    // 16-key tile x of the wave: keys 32 w + 16 (x % 2) .. of chunk c0 + x / 2
-    struct Tile {
-        float4 s;
-        uint32_t v[4][NP][WORDS];
-        float a;  // the old score of key 4 q4 + r16 (r16 < 4), for the fold
+    // Unit x of the wave: keys 32 w .. + 31 of chunk c0 + x, two tiles of 16.
+    // Scalar descriptors bound every access, so an address is one lane offset
+    // and an immediate: heads past the group and rows past the new one read
+    // as zero (their p is 0: the logits of keys past the new one are -inf, the
+    // max of heads past the group +inf).
+    auto unit_key = [&](int x) { return (c0 + x) * kChunk + kKeysPerWave * w; };
+    auto logits_of = [&](int x) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            a.S + ws_row(a, l, it.first + c0 + x, g * G) * kChunk, 0,
+            __builtin_amdgcn_readfirstlane(G * kChunk * 4), kBufferDword3);
     };
-    auto tile_key = [&](int x) { return (c0 + x / 2) * kChunk + kKeysPerWave * w + 16 * (x % 2); };
-    const int v_off = 4 * q4 * D + PER * r16;                    // lane offsets inside a tile
-    const int s_off = min(r16, G - 1) * kChunk + 4 * q4;
-    auto load = [&](int x, Tile& t) {
-        const int k0 = tile_key(x);
-        const float* sr = a.S + ws_row(a, l, it.first + c0 + x / 2, g * G) * kChunk + k0 % kChunk;
-        t.s = *reinterpret_cast<const float4*>(sr + s_off);
-        if (k0 + 15 <= len) {  // wave-uniform
-            const T* vr = V + static_cast<size_t>(k0) * D;
+    // a plane's `bytes` per key, for `keys` keys from k0 on of those below n
+    auto keys_of = [&](const void* p, int k0, int n, int bytes, int keys) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(static_cast<const char*>(p)) + static_cast<size_t>(k0) * bytes, 0,
+            __builtin_amdgcn_readfirstlane(min(max(n - k0, 0), keys) * bytes), kBufferDword3);
+    };
+    const int s_off = 4 * (hc * kChunk + kKeysPerWave * w + 16 * half + 4 * q4);
+    struct Logits {
+        float4 s;
+        float old;  // when this kernel folds: the old score of the key the lane will store (0 for the new slot)
+    };
+    const int key_off = 16 * half + 4 * q4 + (r16 & 3);  // the lane's key of the 16 or 32 it sums for
+    auto load_s = [&](int x, Logits (&p)[NS]) {
+        const __amdgpu_buffer_rsrc_t rs = logits_of(x);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < NP; ++j) __builtin_memcpy(t.v[i][j], vr + v_off + i * D + 16 * PER * j, WORDS * 4);
-            t.a = sc[k0 + 4 * q4 + (r16 & 3)];
-        } else {  // rows past the new one: that row again, masked later
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const T* vr = V + static_cast<size_t>(min(k0 + 4 * q4 + i, len)) * D + PER * r16;
-#pragma unroll
-                for (int j = 0; j < NP; ++j) __builtin_memcpy(t.v[i][j], vr + 16 * PER * j, WORDS * 4);
+        for (int h = 0; h < NS; ++h) {
+            p[h].s = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, s_off + 64 * h, 0, 0));
+            if (fold) {
+                const __amdgpu_buffer_rsrc_t ro = keys_of(sc, unit_key(x) + 16 * h, len, 4, PACK ? 32 : 16);
+                p[h].old = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ro, 4 * key_off, 0, 0));
             }
-            t.a = sc[min(k0 + 4 * q4 + (r16 & 3), len)];
         }
     };
-    const int n_tiles = 2 * nch;
-    Tile tile[DEPTH];
-    // the statistics' loads first, then the first tiles (behind them, so that
-    // the statistics do not wait for the tiles)
+    const int v_off = (4 * q4 * D + PER * r16) * static_cast<int>(sizeof(T));
+    auto load_v = [&](int x, int h, uint32_t (&v)[4][NP][WORDS]) {
+        const __amdgpu_buffer_rsrc_t rv = keys_of(V, unit_key(x) + 16 * h, len + 1, D * sizeof(T), 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const int off = v_off + (i * D + 16 * PER * j) * static_cast<int>(sizeof(T));
+                if constexpr (WORDS == 4) {
+                    const auto y = __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0);
+                    __builtin_memcpy(v[i][j], &y, 16);
+                } else {
+                    const auto y = __builtin_amdgcn_raw_buffer_load_b64(rv, off, 0, 0);
+                    __builtin_memcpy(v[i][j], &y, 8);
+                }
+            }
+    };
+
+    // the statistics' loads first, then the first units (behind them, so that
+    // the statistics do not wait for the units)
     const bool own_stats = (a.plane + kChunk - 1) / kChunk <= kStatChunks;
     const int hs = min(tid / 16, G - 1);  // 16 lanes per head
     float2 pr[vz::kPairs];
     if (own_stats) vz::load_pairs(ml_of(a, l, g * G + hs) + it.first, it.n_chunks, tid % 16, pr);
     else pr[0] = a.layer[row_sl * Hq + g * G + hs];
     __builtin_amdgcn_sched_barrier(0);
+    Logits sp[DEPTH][NS];
+    uint32_t v[DEPTH][2][4][NP][WORDS];
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u)
-        load(min(u, n_tiles - 1), tile[u]);
+    for (int u = 0; u < DEPTH; ++u) {
+        const int x = min(u, nch - 1);
+        load_s(x, sp[u]);
+        load_v(x, 0, v[u][0]);
+        load_v(x, 1, v[u][1]);
+    }
     __builtin_amdgcn_sched_barrier(0);
-
     {
         const float2 st = own_stats ? vz::merge_pairs(pr, it.n_chunks, tid % 16, ExpRel()) : pr[0];
-        if (tid % 16 == 0) s_stat[tid / 16] = st;
+        if (tid % 16 == 0) s_stat[tid / 16] = tid / 16 < G ? st : make_float2(INFINITY, 1.f);
     }
     __syncthreads();
-    const float M = s_stat[r16].x, inv_Z = 1.0f / s_stat[r16].y;
+    const float M = s_stat[hc].x, inv_Z = 1.0f / s_stat[hc].y;
 
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto use = [&](int x, const Tile& cur, auto tail) {
-        constexpr bool TAIL = decltype(tail)::value;  // keys past the new one: no p, and no value times a p of 0
-        const int k0 = tile_key(x);
-        float e[4] = {cur.s.x, cur.s.y, cur.s.z, cur.s.w};
+    // p of four keys of a head per lane; Sum_h p of each key to its place
+    auto probabilities = [&](int x, int h, const Logits& p, float (&e)[4]) {
+        const int k0 = unit_key(x) + 16 * h;
+        e[0] = expf(p.s.x - M);
+        e[1] = expf(p.s.y - M);
+        e[2] = expf(p.s.z - M);
+        e[3] = expf(p.s.w - M);
         float ks[4];
-        bool on[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            on[i] = !TAIL || k0 + 4 * q4 + i <= len;
-            e[i] = r16 < G && on[i] ? expf(e[i] - M) : 0.f;
-            ks[i] = e[i] * inv_Z;
+        for (int i = 0; i < 4; ++i) ks[i] = heads_sum<PACK>(e[i] * inv_Z);
+        const float sum = (r16 & 2) ? ((r16 & 1) ? ks[3] : ks[2]) : ((r16 & 1) ? ks[1] : ks[0]);
+        if (hc < 4) {
+            if (fold) {
+                if (k0 + key_off <= len)
+                    vz_sel::store_score(sc + k0 + key_off, fmaf(a.gamma, p.old, sum), !RAG && a.ev.on);
+            } else {
+                // (the logits of these keys are in registers: only this wave reads them)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), logits_of(x), 4 * (k0 % kChunk + key_off), 0, 0);
+            }
         }
+    };
+    auto product = [&](const uint32_t (&vt)[4][NP][WORDS], const float (&e)[4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
                 float f[PER];
-                widen<DT, PER>(cur.v[i][j], f);
+                widen<DT, PER>(vt[i][j], f);
 #pragma unroll
                 for (int k = 0; k < PER; ++k)
-                    acc[PER * j + k] =
-                        __builtin_amdgcn_mfma_f32_16x16x4f32(on[i] ? f[k] : 0.f, e[i], acc[PER * j + k], 0, 0, 0);
+                    acc[PER * j + k] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[k], e[i], acc[PER * j + k], 0, 0, 0);
             }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ks[i] = vz::row16_sum(ks[i]);
-        if (r16 < 4) {
-            const float sum = r16 == 0 ? ks[0] : r16 == 1 ? ks[1] : r16 == 2 ? ks[2] : ks[3];
-            const int key = k0 + 4 * q4 + r16;
-            if (fold) {
-                if (key <= len) vz_sel::store_score(sc + key, fmaf(a.gamma, key < len ? cur.a : 0.f, sum), !RAG && a.ev.on);
-            } else {
-                // (the logits of these keys are in registers: only this wave reads them)
-                a.S[ws_row(a, l, it.first + c0 + x / 2, g * G) * kChunk + key % kChunk] = sum;
-            }
-        }
     };
-    for (int x = 0; x < n_tiles; x += DEPTH) {
+    for (int x0 = 0; x0 < nch; x0 += DEPTH) {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
-            if (x + u < n_tiles) {
-                if (tile_key(x + u) + 15 <= len) use(x + u, tile[u], std::false_type{});
-                else if (tile_key(x + u) <= len) use(x + u, tile[u], std::true_type{});
+            const int x = x0 + u;
+            if (x >= nch || unit_key(x) > len) break;
+            const bool more = x + DEPTH < nch;
+            float e0[4], e1[4];
+            probabilities(x, 0, sp[u][0], e0);
+            if constexpr (PACK) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e1[i] = vz::ror16<8>(e0[i]);
+            } else {
+                probabilities(x, 1, sp[u][NS - 1], e1);
             }
-            if (x + u + DEPTH < n_tiles) load(x + u + DEPTH, tile[u]);
+            if (more) load_s(x + DEPTH, sp[u]);
+            product(v[u][0], e0);
+            if (more) load_v(x + DEPTH, 0, v[u][0]);
+            product(v[u][1], e1);
+            if (more) load_v(x + DEPTH, 1, v[u][1]);
         }
     }
     // ---- the four waves' outputs, added in wave order ----
@@ -508,7 +589,10 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
         runs = runs_of(chunks, G).n;
         a.ev = vz_sel::EvictOne{vz_decode_counters(v.ws), v.ev, v.ev_budget, v.ev_sink, v.ev_M};
     }
-    hipLaunchKernelGGL((logits_kernel<DT, D, RAG>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
+    if (G <= 8)
+        hipLaunchKernelGGL((logits_kernel<DT, D, RAG, true>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((logits_kernel<DT, D, RAG, false>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if ((a.plane + kChunk - 1) / kChunk > kStatChunks) {
@@ -516,7 +600,10 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((values_kernel<DT, D, RAG>), dim3(runs, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
+    if (G <= 8)
+        hipLaunchKernelGGL((values_kernel<DT, D, RAG, true>), dim3(runs, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((values_kernel<DT, D, RAG, false>), dim3(runs, a.L, a.Hkv), dim3(kThreads), 0, stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int folds = a.Hkv > 1 ? chunks : 0;  // one KV head: folded by the values kernel
