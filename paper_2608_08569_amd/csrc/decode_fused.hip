@@ -113,7 +113,7 @@ __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem
 // (1.7 us), its 16.8 MB (3.8 us for a kernel of the same loads and nothing
 // else) and this arithmetic behind the last loads, 1.9 us with the stores: per
 // layer of a 48-layer graph at 8,200 keys, with the finishing launch and a
-// caller's kernel, 14.9 -> 13.8 us (V through LDS, three barriers and the
+// caller's kernel, 14.9 -> 13.4 us (V through LDS, three barriers and the
 // sequence search by shuffles before).
 // (Launch bounds: four workgroups per CU, 128 registers per lane; the MFMA
 // accumulators then live in ordinary vector registers.)
@@ -164,169 +164,179 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     uint16_t* Vh = a.v_cache + head_base;
     const size_t row_sl = static_cast<size_t>(it.s) * a.L + l;
 
-    // Eq. (1): the wave whose keys hold slot len (row rr of its tile) loads
-    // its KV head's new K and V rows with its other loads, puts them into its
-    // tile registers in place of the cache's old row once the tiles have
-    // landed, and only then writes them to the cache (and KV head 0 the
-    // position), so that none of the chunk's loads waits behind a write.
-    // Lane (r16, q4) holds K channels 8 (q4 + 4 s) .. + 7 of its K rows and V
-    // channels 8 r16 .. + 7 of its V rows (the tile layouts below).
-    const int rr = len - kw0;
-    if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l] = 0;  // counted by the finishing launch
-    const bool writer = rr >= 0 && rr < VT;  // wave-uniform
-    uint4 kn_row[KSTEPS], vn_row;
-    if (writer) {
-        const uint16_t* kn = a.k_new + (row_sl * NW + g) * D;
-        const uint16_t* vn = a.v_new + (row_sl * NW + g) * D;
+    float sp[4] = {0.f, 0.f, 0.f, 0.f}, m_w = -INFINITY;  // the wave's p (4 keys of a head per lane) and max
+    if (rows > 0) {
+        // Eq. (1): the wave whose keys hold slot len (row rr of its tile) loads
+        // its KV head's new K and V rows with its other loads, puts them into its
+        // tile registers in place of the cache's old row once the tiles have
+        // landed, and only then writes them to the cache (and KV head 0 the
+        // position), so that none of the chunk's loads waits behind a write.
+        // Lane (r16, q4) holds K channels 8 (q4 + 4 s) .. + 7 of its K rows and V
+        // channels 8 r16 .. + 7 of its V rows (the tile layouts below).
+        const int rr = len - kw0;
+        if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l] = 0;  // counted by the finishing launch
+        const bool writer = rr >= 0 && rr < VT;  // wave-uniform
+        uint4 kn_row[KSTEPS], vn_row;
+        if (writer) {
+            const uint16_t* kn = a.k_new + (row_sl * NW + g) * D;
+            const uint16_t* vn = a.v_new + (row_sl * NW + g) * D;
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) kn_row[s] = *reinterpret_cast<const uint4*>(kn + 8 * (q4 + 4 * s));
-        vn_row = *reinterpret_cast<const uint4*>(vn + 8 * r16);
-    }
-
-    // The query rows first, so that the logits wait for them and the K tile
-    // only, not for the V tile behind them.  One descriptor over the KV
-    // head's G query rows: lanes of head columns r16 >= G read past it and
-    // get zeros, with no memory access.
-    uint4 qv[KSTEPS];
-    {
-        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(a.q + (row_sl * Hq + g * G) * D), 0, __builtin_amdgcn_readfirstlane(G * D * 2),
-            kBufferDword3);
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rq, (r16 * D + 8 * q4 + 32 * s) * 2, 0, 0);
-            __builtin_memcpy(&qv[s], &v, 16);
+            for (int s = 0; s < KSTEPS; ++s) kn_row[s] = *reinterpret_cast<const uint4*>(kn + 8 * (q4 + 4 * s));
+            vn_row = *reinterpret_cast<const uint4*>(vn + 8 * r16);
         }
-    }
 
-    // both tiles requested at once; rows past the chunk read as zero without
-    // touching memory (bounded scalar descriptors).  K in the MFMA A-operand
-    // layout: register m = 4 ti + s holds bytes 16 (q4 + 4 s) .. + 15 of row
-    // 16 ti + r16.  V whole rows at a time, 16 bytes of four rows per lane and
-    // tile half: register m = 4 ti + i holds channels 8 r16 .. + 7 of row
-    // 16 ti + 4 q4 + i, which are the lane's share of eight A operands (V^T,
-    // channel slot r16 of output tile e: channel 8 r16 + e) for those keys.
-    const int lane_off_k = r16 * (D * 2) + 16 * q4;
-    const int lane_off_v = 4 * q4 * (D * 2) + 16 * r16;
-    uint4 kt[8], vt[8];
-    {
-        // (the byte bound taken through readfirstlane keeps the descriptors in
-        // scalar registers: a bound left in a vector register makes the
-        // compiler wrap every load in a loop over the lanes' descriptors)
-        const int nbytes = __builtin_amdgcn_readfirstlane(rows * D * 2);
-        const __amdgpu_buffer_rsrc_t rk =
-            __builtin_amdgcn_make_buffer_rsrc(Kh + static_cast<size_t>(kw0) * D, 0, nbytes, kBufferDword3);
-        const __amdgpu_buffer_rsrc_t rv =
-            __builtin_amdgcn_make_buffer_rsrc(Vh + static_cast<size_t>(kw0) * D, 0, nbytes, kBufferDword3);
+        // The query rows first, so that the logits wait for them and the K tile
+        // only, not for the V tile behind them.  One descriptor over the KV
+        // head's G query rows: lanes of head columns r16 >= G read past it and
+        // get zeros, with no memory access.
+        uint4 qv[KSTEPS];
+        {
+            const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t*>(a.q + (row_sl * Hq + g * G) * D), 0, __builtin_amdgcn_readfirstlane(G * D * 2),
+                kBufferDword3);
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rk, lane_off_k + (m >> 2) * 16 * (D * 2) + (m & 3) * 64,
-                                                                 0, 0);
-            __builtin_memcpy(&kt[m], &v, 16);
+            for (int s = 0; s < KSTEPS; ++s) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rq, (r16 * D + 8 * q4 + 32 * s) * 2, 0, 0);
+                __builtin_memcpy(&qv[s], &v, 16);
+            }
         }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const auto v =
-                __builtin_amdgcn_raw_buffer_load_b128(rv, lane_off_v + (16 * (m >> 2) + (m & 3)) * (D * 2), 0, 0);
-            __builtin_memcpy(&vt[m], &v, 16);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first wait
 
-    if (writer && r16 == (rr & 15)) {  // the new K row: row 16 ti + r16 of registers 4 ti .. 4 ti + 3
+        // both tiles requested at once; rows past the chunk read as zero without
+        // touching memory (bounded scalar descriptors).  K in the MFMA A-operand
+        // layout: register m = 4 ti + s holds bytes 16 (q4 + 4 s) .. + 15 of row
+        // 16 ti + r16.  V whole rows at a time, 16 bytes of four rows per lane and
+        // tile half: register m = 4 ti + i holds channels 8 r16 .. + 7 of row
+        // 16 ti + 4 q4 + i, which are the lane's share of eight A operands (V^T,
+        // channel slot r16 of output tile e: channel 8 r16 + e) for those keys.
+        const int lane_off_k = r16 * (D * 2) + 16 * q4;
+        const int lane_off_v = 4 * q4 * (D * 2) + 16 * r16;
+        uint4 kt[8], vt[8];
+        {
+            // (the byte bound taken through readfirstlane keeps the descriptors in
+            // scalar registers: a bound left in a vector register makes the
+            // compiler wrap every load in a loop over the lanes' descriptors)
+            const int nbytes = __builtin_amdgcn_readfirstlane(rows * D * 2);
+            const __amdgpu_buffer_rsrc_t rk =
+                __builtin_amdgcn_make_buffer_rsrc(Kh + static_cast<size_t>(kw0) * D, 0, nbytes, kBufferDword3);
+            const __amdgpu_buffer_rsrc_t rv =
+                __builtin_amdgcn_make_buffer_rsrc(Vh + static_cast<size_t>(kw0) * D, 0, nbytes, kBufferDword3);
 #pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-            if (ti == rr >> 4)
+            for (int m = 0; m < 8; ++m) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rk, lane_off_k + (m >> 2) * 16 * (D * 2) + (m & 3) * 64,
+                                                                     0, 0);
+                __builtin_memcpy(&kt[m], &v, 16);
+            }
 #pragma unroll
-                for (int s = 0; s < KSTEPS; ++s) kt[4 * ti + s] = kn_row[s];
-    }
-
-    // ---- logits of the wave's 32 keys: S^T = K Q^T ----
-    f32x4 acc[2];
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti) {
-        acc[ti] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s)
-            acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kt[4 * ti + s]), as_bf16x8(qv[s]), acc[ti], 0,
-                                                              0, 0);
-    }
-    // packed: head column r16 < 8 keeps the even half's logits, column r16 =
-    // 8 + hh takes the odd half's of head hh
-    float sp[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float odd = ror8(acc[1][i]);
-        const float v = hi ? odd : acc[0][i];
-        const int key = VT * w + 16 * hi + 4 * q4 + i;  // within the chunk
-        sp[i] = (key < nk) ? v * a.scale_log2 : -INFINITY;
-    }
-    // ---- p relative to the wave's max, per head ----
-    float m_w = fmaxf(fmaxf(sp[0], sp[1]), fmaxf(sp[2], sp[3]));
-    m_w = vz::rows_max(m_w);
-    m_w = fmaxf(m_w, ror8(m_w));
-    const float m_ref = m_w == -INFINITY ? 0.f : m_w;  // a wave past the chunk's keys
-    float l_w = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        sp[i] = exp2f(sp[i] - m_ref);
-        l_w += sp[i];
-    }
-    l_w = vz::rows_sum(l_w);
-    l_w += ror8(l_w);
-    if (q4 == 0 && hi == 0) {
-        s_m[w][hh] = m_w;
-        s_l[w][hh] = l_w;
-    }
-    // B operand P^T: columns 0..7 the even half's keys, then the odd half's
-    // (columns 8..15 hold the halves the other way round: outputs not used)
-    const uint32_t p01 = pack_bf16x2(sp[0], sp[1]), p23 = pack_bf16x2(sp[2], sp[3]);
-    const bf16x8_t pb = as_bf16x8(make_uint4(p01, p23, ror8_u32(p01), ror8_u32(p23)));
-
-    if (writer) {
-        if (q4 == ((rr >> 2) & 3)) {  // the new V row: row 16 ti + 4 q4 + i of register 4 ti + i
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-                if (m == 4 * (rr >> 4) + (rr & 3)) vt[m] = vn_row;
+            for (int m = 0; m < 8; ++m) {
+                const auto v =
+                    __builtin_amdgcn_raw_buffer_load_b128(rv, lane_off_v + (16 * (m >> 2) + (m & 3)) * (D * 2), 0, 0);
+                __builtin_memcpy(&vt[m], &v, 16);
+            }
         }
-        // the new rows into the cache, after every load of the wave
-        if (r16 == (rr & 15)) {
-#pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) *reinterpret_cast<uint4*>(Kh + len * D + 8 * (q4 + 4 * s)) = kn_row[s];
-        }
-        if (q4 == ((rr >> 2) & 3)) *reinterpret_cast<uint4*>(Vh + len * D + 8 * r16) = vn_row;
-        if (g == 0 && lane == 0) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
-    }
+        __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first wait
 
-    // ---- O^T = V^T P^T over the wave's keys ----
-    // Output tile e takes channel 8 slot + e of each of the 16 channel slots:
-    // its A operand is element e of the lane's eight V pieces (keys 4 q4 + i,
-    // then 16 + 4 q4 + i, as in pb), gathered by byte permutes.
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 oacc[DTILES];
+        if (writer && r16 == (rr & 15)) {  // the new K row: row 16 ti + r16 of registers 4 ti .. 4 ti + 3
 #pragma unroll
-    for (int e = 0; e < DTILES; ++e) {
-        uint32_t x[8];
+            for (int ti = 0; ti < 2; ++ti)
+                if (ti == rr >> 4)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const uint32_t words[4] = {vt[m].x, vt[m].y, vt[m].z, vt[m].w};
-            x[m] = words[e / 2];
+                    for (int s = 0; s < KSTEPS; ++s) kt[4 * ti + s] = kn_row[s];
         }
-        constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;  // halves of (second, first) word
-        uint32_t av[4];
+
+        // ---- logits of the wave's 32 keys: S^T = K Q^T ----
+        f32x4 acc[2];
 #pragma unroll
-        for (int y = 0; y < 4; ++y) av[y] = __builtin_amdgcn_perm(x[2 * y + 1], x[2 * y], (e & 1) ? kHigh : kLow);
-        oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(av[0], av[1], av[2], av[3])), pb, zero,
-                                                          0, 0, 0);
-    }
-    // lane: head r16, channels 8 (4 q4 + i) + e
-    if (r16 < G) {
+        for (int ti = 0; ti < 2; ++ti) {
+            acc[ti] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int s = 0; s < KSTEPS; ++s)
+                acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kt[4 * ti + s]), as_bf16x8(qv[s]), acc[ti], 0,
+                                                                  0, 0);
+        }
+        // packed: head column r16 < 8 keeps the even half's logits, column r16 =
+        // 8 + hh takes the odd half's of head hh
 #pragma unroll
-            for (int e = 0; e < DTILES; e += 4)
-                *reinterpret_cast<float4*>(&s_o[w][r16][8 * (4 * q4 + i) + e]) =
-                    make_float4(oacc[e][i], oacc[e + 1][i], oacc[e + 2][i], oacc[e + 3][i]);
+        for (int i = 0; i < 4; ++i) {
+            const float odd = ror8(acc[1][i]);
+            const float v = hi ? odd : acc[0][i];
+            const int key = VT * w + 16 * hi + 4 * q4 + i;  // within the chunk
+            sp[i] = (key < nk) ? v * a.scale_log2 : -INFINITY;
+        }
+        // ---- p relative to the wave's max, per head ----
+        m_w = fmaxf(fmaxf(sp[0], sp[1]), fmaxf(sp[2], sp[3]));
+        m_w = vz::rows_max(m_w);
+        m_w = fmaxf(m_w, ror8(m_w));
+        float l_w = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sp[i] = exp2f(sp[i] - m_w);
+            l_w += sp[i];
+        }
+        l_w = vz::rows_sum(l_w);
+        l_w += ror8(l_w);
+        if (q4 == 0 && hi == 0) {
+            s_m[w][hh] = m_w;
+            s_l[w][hh] = l_w;
+        }
+        // B operand P^T: columns 0..7 the even half's keys, then the odd half's
+        // (columns 8..15 hold the halves the other way round: outputs not used)
+        const uint32_t p01 = pack_bf16x2(sp[0], sp[1]), p23 = pack_bf16x2(sp[2], sp[3]);
+        const bf16x8_t pb = as_bf16x8(make_uint4(p01, p23, ror8_u32(p01), ror8_u32(p23)));
+
+        if (writer) {
+            if (q4 == ((rr >> 2) & 3)) {  // the new V row: row 16 ti + 4 q4 + i of register 4 ti + i
+#pragma unroll
+                for (int m = 0; m < 8; ++m)
+                    if (m == 4 * (rr >> 4) + (rr & 3)) vt[m] = vn_row;
+            }
+            // the new rows into the cache, after every load of the wave
+            if (r16 == (rr & 15)) {
+#pragma unroll
+                for (int s = 0; s < KSTEPS; ++s) *reinterpret_cast<uint4*>(Kh + len * D + 8 * (q4 + 4 * s)) = kn_row[s];
+            }
+            if (q4 == ((rr >> 2) & 3)) *reinterpret_cast<uint4*>(Vh + len * D + 8 * r16) = vn_row;
+            if (g == 0 && lane == 0) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
+        }
+
+        // ---- O^T = V^T P^T over the wave's keys ----
+        // Output tile e takes channel 8 slot + e of each of the 16 channel slots:
+        // its A operand is element e of the lane's eight V pieces (keys 4 q4 + i,
+        // then 16 + 4 q4 + i, as in pb), gathered by byte permutes.
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        f32x4 oacc[DTILES];
+#pragma unroll
+        for (int e = 0; e < DTILES; ++e) {
+            uint32_t x[8];
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                const uint32_t words[4] = {vt[m].x, vt[m].y, vt[m].z, vt[m].w};
+                x[m] = words[e / 2];
+            }
+            constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;  // halves of (second, first) word
+            uint32_t av[4];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) av[y] = __builtin_amdgcn_perm(x[2 * y + 1], x[2 * y], (e & 1) ? kHigh : kLow);
+            oacc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(av[0], av[1], av[2], av[3])), pb, zero,
+                                                              0, 0, 0);
+        }
+        // lane: head r16, channels 8 (4 q4 + i) + e
+        if (r16 < G) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < DTILES; e += 4)
+                    *reinterpret_cast<float4*>(&s_o[w][r16][8 * (4 * q4 + i) + e]) =
+                        make_float4(oacc[e][i], oacc[e + 1][i], oacc[e + 2][i], oacc[e + 3][i]);
+        }
+    } else {
+        // past the chunk's keys: nothing to add.  (At 65 chunks x 4 KV heads on
+        // 256 CUs four CUs hold two workgroups and end last; the short last
+        // chunk's idle waves took their issue slots: 668 -> 645 us per token.)
+        if (lane < GMAX) {
+            s_m[w][lane] = -INFINITY;
+            s_l[w][lane] = 0.f;
+        }
+        for (int i = lane; i < GMAX * OS; i += vz::kWave) (&s_o[w][0][0])[i] = 0.f;
     }
     __syncthreads();
 
@@ -338,7 +348,7 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     {
         // p~ = p rescaled to the chunk's max, 4 keys of a head per lane
         const float f = exp2f(m_w - chunk_max(hh));
-        if (hh < G)
+        if (hh < G && rows > 0)
             *reinterpret_cast<uint2*>(part.p + static_cast<size_t>(pbase + hh) * CHUNK + VT * w + 16 * hi + 4 * q4) =
                 make_uint2(pack_bf16x2(sp[0] * f, sp[1] * f), pack_bf16x2(sp[2] * f, sp[3] * f));
     }
@@ -820,5 +830,6 @@ bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget, bool kept) {
     if (vz_decode_takes_range(a)) return a.Hkv <= 4 && E <= vz_sel::kInlineRows;
     if (E != 1 || kept || T > kEvictOneSlots) return false;
     if (!vz_decode_fused_ok(a.dtype, a.d, a.Hq, a.Hkv, a.L, a.cap, 0)) return true;  // general path
-    return !vz_decode_range_ok(a.L, a.Hkv, 0) && finish_in_one_launch((static_cast<int64_t>(a.cap) + CHUNK - 1) / CHUNK, 1, a.L, 0);
+    return !vz_decode_range_ok(a.L, a.Hkv, 0) &&
+           finish_in_one_launch((static_cast<int64_t>(a.cap) + CHUNK - 1) / CHUNK, 1, a.L, 0);
 }
