@@ -214,7 +214,7 @@ __device__ __forceinline__ RangeItem uniform_item(const RangeItem& x) {
 // ragged call's table (dispatch order longest first); else the parts of the
 // single sequence.  SPLIT: items may be parts of a longer sequence, whose
 // statistics, outputs and per-head probabilities go to the workspace for the
-// merge and fold kernels.  Neither (a single sequence in one part): the
+// finishing launch.  Neither (a single sequence in one part): the
 // layer's last workgroup folds the scores and evicts (fold_select_layer).
 template <int NW, bool RAG, bool SPLIT>
 __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArgs a) {
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
         S = fmaf(st.y, st.x == -INFINITY ? 0.f : exp2f(st.x - M), S);
     }
     // a part of a longer sequence keeps its output and p~ relative to its own
-    // max; the merge kernel applies the sequence's statistics
+    // max; the finishing launch applies the sequence's statistics
     const float inv_S = split ? 1.f : 1.0f / S;
     if (w == 0 && q4 == 0 && hi == 0) s_MS[hh] = make_float2(M, inv_S);  // read after the next barrier
     const size_t part_row = (static_cast<size_t>(l) * NW + g) * a.R + r;  // (layer, KV head, item) of pstat, pout
@@ -670,7 +670,8 @@ __device__ __forceinline__ float2 parts_stats(const float2* ps, int P) {
 // the parts' outputs times their factors, added in part order.
 // (One launch: as two, the merge of a few rows -- of none, in a batch of
 // sequences in one part whose planes could hold longer ones -- was 4.7 us and
-// a gap of its own beside 9.5 us of folding: RANGE_FINISH_TIMES.)
+// a gap of its own beside 9.5 us of folding: 48 layers at 13,181 keys 269.5 ->
+// 267.1 us, eight sequences of 1k-8k keys 519.3 -> 517.5.)
 constexpr int RMERGE_HEADS = RFOLD_KEYS / D;
 __host__ __device__ inline int merge_blocks(int Hq) { return (Hq + RMERGE_HEADS - 1) / RMERGE_HEADS; }
 template <int NW, bool RAG>
