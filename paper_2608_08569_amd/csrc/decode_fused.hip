@@ -84,6 +84,12 @@ struct Exp2Weight {
     __device__ __forceinline__ float operator()(float x, float m) const { return __builtin_amdgcn_exp2f(x - m); }
 };
 
+// What the exp of keys with max m is relative to: m, or 0 when no key has a
+// finite logit (a key at -infinity, in a wave of its own or among others): the
+// keys' p and their weight beside others are then 0, where -inf - -inf would
+// make the head's output and scores not a number.
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 // Flat chunk f of a call: false when it holds no work.
 template <bool RAG>
 __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem& it, int& c) {
@@ -266,10 +272,11 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         m_w = fmaxf(fmaxf(sp[0], sp[1]), fmaxf(sp[2], sp[3]));
         m_w = vz::rows_max(m_w);
         m_w = fmaxf(m_w, ror8(m_w));
+        const float ref = finite_ref(m_w);
         float l_w = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            sp[i] = exp2f(sp[i] - m_w);
+            sp[i] = exp2f(sp[i] - ref);
             l_w += sp[i];
         }
         l_w = vz::rows_sum(l_w);
@@ -347,7 +354,7 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
     static_assert(SPLIT_W == 4, "four waves' maxima");
     {
         // p~ = p rescaled to the chunk's max, 4 keys of a head per lane
-        const float f = exp2f(m_w - chunk_max(hh));
+        const float f = exp2f(m_w - finite_ref(chunk_max(hh)));
         if (hh < G && rows > 0)
             *reinterpret_cast<uint2*>(part.p + static_cast<size_t>(pbase + hh) * CHUNK + VT * w + 16 * hi + 4 * q4) =
                 make_uint2(pack_bf16x2(sp[0] * f, sp[1] * f), pack_bf16x2(sp[2] * f, sp[3] * f));
@@ -356,11 +363,11 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         // 4 channels per thread, whole output rows per head
         const int h = tid >> 5, c4 = 4 * (tid & 31);
         if (h < G) {
-            const float m_c = chunk_max(h);
+            const float m_c = chunk_max(h), ref = finite_ref(m_c);
             float o[4] = {0.f, 0.f, 0.f, 0.f}, lc = 0.f;
 #pragma unroll
             for (int v = 0; v < SPLIT_W; ++v) {
-                const float f = Exp2Weight()(s_m[v][h], m_c);
+                const float f = Exp2Weight()(s_m[v][h], ref);
                 const float4 x = *reinterpret_cast<const float4*>(&s_o[v][h][c4]);
                 o[0] = fmaf(x.x, f, o[0]);
                 o[1] = fmaf(x.y, f, o[1]);
