@@ -296,12 +296,14 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
                 for (int m = 0; m < 8; ++m)
                     if (m == 4 * (rr >> 4) + (rr & 3)) vt[m] = vn_row;
             }
-            // the new rows into the cache, after every load of the wave
+            // the new rows into the cache, after every load of the wave (a plane's
+            // element offsets pass 2^31 at 2^24 slots)
+            const size_t at = static_cast<size_t>(len) * D;
             if (r16 == (rr & 15)) {
 #pragma unroll
-                for (int s = 0; s < KSTEPS; ++s) *reinterpret_cast<uint4*>(Kh + len * D + 8 * (q4 + 4 * s)) = kn_row[s];
+                for (int s = 0; s < KSTEPS; ++s) *reinterpret_cast<uint4*>(Kh + at + 8 * (q4 + 4 * s)) = kn_row[s];
             }
-            if (q4 == ((rr >> 2) & 3)) *reinterpret_cast<uint4*>(Vh + len * D + 8 * r16) = vn_row;
+            if (q4 == ((rr >> 2) & 3)) *reinterpret_cast<uint4*>(Vh + at + 8 * r16) = vn_row;
             if (g == 0 && lane == 0) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
         }
 
