@@ -658,12 +658,71 @@ __device__ __forceinline__ float2 parts_stats(const float2* ps, int P) {
     return make_float2(M, S);
 }
 
+// Up to how many parts the finishing launch's blocks form a head's statistics
+// themselves.  With a fold block per 256 keys and the pairs of every part in
+// each, that work grows with the square of the sequence; a launch of its own
+// (range_factors_kernel) costs about 4 us.  32 layers x 4 KV heads, without
+// and with it: 13,181 keys (2 parts) 162.6 and 164 us, 32,768 (4) 407 and 407,
+// 65,536 (8) 825-833 and 820-823, 131,072 (17) 1,700 and 1,660, 524,288 (65)
+// 7,400 and 6,766.  The host does not know the parts of a ragged call's
+// sequences, only what its planes can hold, and a batch of short sequences
+// would pay for an empty launch (eight of 1k-8k keys 519.1 -> 520.7 us): its
+// planes decide, at twice as many.
+constexpr int kOwnParts = 4, kOwnPartsRagged = 8;
+
+// For a sequence in parts of a call with more of them, one block per (sequence
+// in parts, layer): every pair's max becomes its part's factor exp2(m_part -
+// M) / S.  The block takes PARTS parts at a time, a pair per thread and load;
+// one thread per head adds the products, in part order, with the arithmetic of
+// parts_stats.
+template <int NW, bool RAG>
+__global__ __launch_bounds__(RFOLD_KEYS) void range_factors_kernel(const FusedArgs a) {
+    constexpr int HEADS = NW * GMAX, LANES = RFOLD_KEYS / HEADS, LOADS = 4, PARTS = LANES * LOADS;
+    __shared__ float s_m[LANES][HEADS], s_inv[HEADS];
+    __shared__ float2 s_w[PARTS][HEADS];
+    const int l = blockIdx.y, t = threadIdx.x, hd = t % HEADS, q = t / HEADS;
+    const RangeWs rws = range_ws<NW>(a, RAG);
+    int r = 0, P = a.n_parts;
+    if constexpr (RAG) {
+        if (static_cast<int>(blockIdx.x) >= rws.counts[2]) return;
+        r = rws.mlist[blockIdx.x];
+        P = rws.items[r].P;
+    }
+    const int g = hd / GMAX, hg = hd - g * GMAX;
+    if (a.Hq / NW <= hg) P = 0;  // pairs of columns without a head are not written
+    float2* const ps = rws.pstat + ((static_cast<size_t>(l) * NW + g) * a.R + r) * GMAX + hg;
+    auto pair = [&](int p) { return p < P ? ps[static_cast<size_t>(p) * GMAX] : make_float2(-INFINITY, 0.f); };
+    float M = -INFINITY, S = 0.f;
+    for (int p = q; p < P; p += LANES) M = fmaxf(M, pair(p).x);
+    s_m[q][hd] = M;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < LANES; ++i) M = fmaxf(M, s_m[i][hd]);
+    for (int p0 = 0;; p0 += PARTS) {  // (rounds of the block, whose heads have the same parts or none)
+        const int more = __syncthreads_or(p0 < P);
+        if (!more) break;
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) {
+            const float2 x = pair(p0 + q + LANES * k);
+            s_w[q + LANES * k][hd] = make_float2(x.y, exp2f(x.x - M));
+        }
+        __syncthreads();
+        if (t < HEADS)
+            for (int i = 0; i < min(PARTS, P - p0); ++i) S = fmaf(s_w[i][hd].x, s_w[i][hd].y, S);
+    }
+    if (t < HEADS) s_inv[hd] = 1.0f / S;
+    __syncthreads();
+    for (int p = q; p < P; p += LANES)
+        ps[static_cast<size_t>(p) * GMAX].x = exp2f(ps[static_cast<size_t>(p) * GMAX].x - M) * s_inv[hd];
+}
+
 // Finishing launch of a ragged call or of a sequence in parts.  Blocks
 // [0, folds) of a layer fold scores, one per RFOLD_KEYS keys of one item,
 // thread = key: Eq. (6) from the KV heads' sums added in head order (a
 // sequence of one part, the arithmetic of the single-part fold), or from each
 // key's per-head rows times its part's factors exp2(m_part - M) / S, which the
-// block forms itself from the parts' few pairs.  The blocks after them write
+// block forms itself from the parts' few pairs or (`table`) finds in the place
+// of the maxima.  The blocks after them write
 // the output rows of the sequences in parts, one per (sequence in parts, pair
 // of query heads) -- a ragged call's are listed by the order kernel, a single
 // sequence is item 0 -- and thread t takes channel t % D of head 2 hb + t / D:
@@ -675,7 +734,7 @@ __device__ __forceinline__ float2 parts_stats(const float2* ps, int P) {
 constexpr int RMERGE_HEADS = RFOLD_KEYS / D;
 __host__ __device__ inline int merge_blocks(int Hq) { return (Hq + RMERGE_HEADS - 1) / RMERGE_HEADS; }
 template <int NW, bool RAG>
-__global__ __launch_bounds__(RFOLD_KEYS) void range_finish_kernel(const FusedArgs a, int folds) {
+__global__ __launch_bounds__(RFOLD_KEYS) void range_finish_kernel(const FusedArgs a, int folds, bool table) {
     __shared__ float s_f[NW * GMAX];
     const int b = blockIdx.x, l = blockIdx.y, t = threadIdx.x;
     const RangeWs rws = range_ws<NW>(a, RAG);
@@ -696,12 +755,14 @@ __global__ __launch_bounds__(RFOLD_KEYS) void range_finish_kernel(const FusedArg
         const int g = h / G, hg = h - g * G;
         const size_t row = ((static_cast<size_t>(l) * NW + g) * a.R + r) * GMAX + hg;
         const float2* ps = rws.pstat + row;
-        const float2 st = parts_stats(ps, P);
+        const float2 st = table ? make_float2(0.f, 1.f) : parts_stats(ps, P);
         const float inv_S = 1.0f / st.y;
         const float* po = rws.pout + row * D + ch;
         float o = 0.f;
-        for (int p = 0; p < P; ++p)
-            o = fmaf(po[static_cast<size_t>(p) * GMAX * D], exp2f(ps[static_cast<size_t>(p) * GMAX].x - st.x) * inv_S, o);
+        for (int p = 0; p < P; ++p) {
+            const float x = ps[static_cast<size_t>(p) * GMAX].x;
+            o = fmaf(po[static_cast<size_t>(p) * GMAX * D], table ? x : exp2f(x - st.x) * inv_S, o);
+        }
         a.out[((static_cast<size_t>(it.s) * a.L + l) * Hq + h) * D + ch] = vz::f32_to_bf16(o);
         return;
     }
@@ -741,8 +802,11 @@ __global__ __launch_bounds__(RFOLD_KEYS) void range_finish_kernel(const FusedArg
             const float2* ps = rws.pstat + ((static_cast<size_t>(l) * NW + g) * a.R + r - it.p) * GMAX + hg;
             float f = 0.f;
             if (hg < G) {
-                const float2 st = parts_stats(ps, it.P);
-                f = exp2f(ps[static_cast<size_t>(it.p) * GMAX].x - st.x) * (1.0f / st.y);
+                f = ps[static_cast<size_t>(it.p) * GMAX].x;
+                if (!table) {
+                    const float2 st = parts_stats(ps, it.P);
+                    f = exp2f(f - st.x) * (1.0f / st.y);
+                }
             }
             s_f[t] = f;
         }
@@ -975,16 +1039,20 @@ hipError_t launch_range(const FusedArgs& a, hipStream_t stream) {
     if (a.rag.n > 0) {
         hipLaunchKernelGGL((range_order_kernel<NW>), dim3(1), dim3(ORDER_THREADS), 0, stream, a);
         hipLaunchKernelGGL((decode_range_kernel<NW, true, true>), dim3(NW * a.L * a.R), dim3(64 * RW), 0, stream, a);
+        const bool table = a.plane > static_cast<int64_t>(kOwnPartsRagged) * RPART;
+        if (table) hipLaunchKernelGGL((range_factors_kernel<NW, true>), dim3(a.MB, a.L), dim3(RFOLD_KEYS), 0, stream, a);
         hipLaunchKernelGGL((range_finish_kernel<NW, true>), dim3(a.FB + a.MB * merges, a.L), dim3(RFOLD_KEYS), 0, stream,
-                           a, a.FB);
+                           a, a.FB, table);
         return hipGetLastError();
     }
     if (a.n_parts > 1) {
         hipLaunchKernelGGL((decode_range_kernel<NW, false, true>), dim3(NW * a.L * a.n_parts), dim3(64 * RW), 0,
                            stream, a);
         const int folds = range_fold_blocks(a.len + 1, a.n_parts, a.part_keys);
+        const bool table = a.n_parts > kOwnParts;
+        if (table) hipLaunchKernelGGL((range_factors_kernel<NW, false>), dim3(1, a.L), dim3(RFOLD_KEYS), 0, stream, a);
         hipLaunchKernelGGL((range_finish_kernel<NW, false>), dim3(folds + merges, a.L), dim3(RFOLD_KEYS), 0, stream, a,
-                           folds);
+                           folds, table);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((decode_range_kernel<NW, false, false>), dim3(NW, a.L), dim3(64 * RW), 0, stream, a);
