@@ -50,7 +50,9 @@ constexpr size_t kHeaderBytes = 256;
 //   o  [L][nc_max][Hq][D]     bfloat16   O_c relative to m_c
 //   p  [L][nc_max][Hq][CHUNK] bfloat16   p~ = exp2(s - m_c) per key of the chunk
 //   layer [S][L][Hq]          float2     the layer's max M and 1 / sum S, per head
-//                                        (S = sequences of the call)
+//                                        (S = sequences of the call; calls of two
+//                                        finishing launches only: with one, a generation
+//                                        step's arrival counters, Hq apart)
 template <typename B>
 struct PartialsT {
     using F2 = typename std::conditional<std::is_const<B>::value, const float2, float2>::type;
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         // Lane (r16, q4) holds K channels 8 (q4 + 4 s) .. + 7 of its K rows and V
         // channels 8 r16 .. + 7 of its V rows (the tile layouts below).
         const int rr = len - kw0;
-        if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l] = 0;  // counted by the finishing launch
+        if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l * a.cnt_stride] = 0;  // counted by the finishing launch
         const bool writer = rr >= 0 && rr < VT;  // wave-uniform
         uint4 kn_row[KSTEPS], vn_row;
         if (writer) {
@@ -679,7 +681,7 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
     fold_finish(a, ld, s_f, sc, Hq, nk, j == it.len, evict);
     if constexpr (!RAG) {
         if (!evict) return;
-        const vz_sel::EvictOne e{a.cnt, a.ev, a.ev_budget, a.ev_sink, a.ev_M};
+        const vz_sel::EvictOne e{a.cnt, a.cnt_stride, a.ev, a.ev_budget, a.ev_sink, a.ev_M};
         if (!vz_sel::last_of_layer(e, l, a.n_chunks)) return;
         const size_t row = static_cast<size_t>(l) * a.plane;
         const int Hkv = a.Hkv;
@@ -689,9 +691,27 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
     }
 }
 
-// Slots of a cache whose single eviction the folding launch does itself: one
-// block of 128 or 256 threads then looks at every score of the layer.
+// Slots of a cache whose single eviction the folding launch does itself, where
+// one block looks at every score of the layer (256 threads; 128 on the general
+// path with several KV heads, whose sums its blocks also add up), against a
+// launch of its own with 1024 threads per layer.  In a graph, folding launch
+// and own launch, us:
+//   chunked path        1,025 slots: 1 layer 9.1 and 11.4, 28 layers 18.7 and
+//                       21.9; 8,193: 14.6 and 14.6, 16 layers 57.5 and 57.4,
+//                       28 layers 107.1 and 106.6 (eager, one layer 15.2 and
+//                       16.9: a launch less on the host)
+//   general, 1 KV head  257: 10.8 and 13.5; 8,193: 19.0 and 19.9
+//   2 and 4 KV heads    1,025: 14.0 and 16.3; 7,169: 20.5 and 20.9, 79.0 and
+//                       80.1; 8,193: 22.4 and 21.8, 95.0 and 94.9
+//   8                   5,121: 26.9 and 27.3, 84.6 and 85.6; 6,145: 27.7 and
+//                       26.6, 99.0 and 98.6
+//   16                  2,049: 48.1 and 48.9; 4,097: 202.6 and 201.6
+//   32                  1,025: 32.0 and 34.2; 2,049: 55.2 and 53.5
+// The chunked path takes it up to the whole-range path's length.
 constexpr int64_t kEvictOneSlots = 8224;
+int64_t evict_one_slots_general(int32_t Hkv) {
+    return Hkv == 1 ? kEvictOneSlots : std::min<int64_t>(7168, 40960 / Hkv);
+}
 
 // Whether a call's outputs and scores are finished in one launch.  `chunks`:
 // of a plane; `blocks`: fold and output blocks of a layer in that launch.
@@ -754,6 +774,11 @@ hipError_t launch_decode_fused(const VzDecodeArgs& v, hipStream_t stream) {
     }
     if (vz_decode_range_ok(a.L, NW, RAG ? v.rag.n : 0)) {
         return vz_launch_decode_range(a, NW, stream);
+    }
+    if (a.ev) {  // counted in the finishing launch, which leaves the layer statistics' array (the last one) free
+        const size_t end = vz_decode_fused_ws_bytes(a.L, a.Hq, a.plane, 0);
+        a.cnt = reinterpret_cast<uint64_t*>(a.ws + end) - static_cast<size_t>(a.L) * a.Hq;
+        a.cnt_stride = a.Hq;
     }
     hipLaunchKernelGGL((decode_attend_kernel<NW, RAG>), RAG ? dim3(a.n_chunks * NW, a.L) : dim3(a.L * a.n_chunks * NW),
                        dim3(64 * SPLIT_W), 0, stream, a);
@@ -838,7 +863,7 @@ bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget, bool kept) {
     const int64_t E = T > budget ? T - budget : 0;
     if (vz_decode_takes_range(a)) return a.Hkv <= 4 && E <= vz_sel::kInlineRows;
     if (E != 1 || kept || T > kEvictOneSlots) return false;
-    if (!vz_decode_fused_ok(a.dtype, a.d, a.Hq, a.Hkv, a.L, a.cap, 0)) return true;  // general path
+    if (!vz_decode_fused_ok(a.dtype, a.d, a.Hq, a.Hkv, a.L, a.cap, 0)) return T <= evict_one_slots_general(a.Hkv);
     return !vz_decode_range_ok(a.L, a.Hkv, 0) &&
            finish_in_one_launch((static_cast<int64_t>(a.cap) + CHUNK - 1) / CHUNK, 1, a.L, 0);
 }

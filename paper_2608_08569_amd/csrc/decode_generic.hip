@@ -64,7 +64,7 @@ struct GenericArgs {
     void* out;
     float* S;        // logits [L][nc_max][Hq][kChunk], then key sums and run outputs in their place
     float2* ml;      // max and sum of exp per (layer, head, chunk row) [L][Hq][nc_max]
-    float2* layer;   // the same per (sequence, layer, head), for planes of more than kStatChunks chunks
+    float2* layer;   // the same per (sequence, layer, head), for planes of more than kStatChunks chunks (else free)
     int32_t len, next_pos, n_chunks;  // single sequence
     int32_t nc_max;                   // chunk rows per layer
     int32_t Hq, Hkv, L;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
             T* dst = (tid < CH ? K : V) + static_cast<size_t>(len) * D + o;
             *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>((tid < CH ? kn : vn) + o);
         }
-        if (!RAG && a.ev.on && g == 0 && tid == 2 * CH) a.ev.cnt[l] = 0;  // counted by the launch that folds
+        if (!RAG && a.ev.on && g == 0 && tid == 2 * CH) a.ev.cnt[l * a.ev.stride] = 0;  // counted by the launch that folds
         if (g == 0 && tid == 2 * CH) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
     }
     if (r16 >= G) {  // unused head columns
@@ -587,7 +587,12 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
         a.next_pos = v.next_pos;
         a.n_chunks = chunks = v.len / kChunk + 1;  // of len + 1 keys
         runs = runs_of(chunks, G).n;
-        a.ev = vz_sel::EvictOne{vz_decode_counters(v.ws), v.ev, v.ev_budget, v.ev_sink, v.ev_M};
+        // arrival counters: in the layer statistics' place, or, where those are
+        // used, in a pair of each layer's head 0 past the sequence's chunks
+        const bool own_stats = (a.plane + kChunk - 1) / kChunk <= kStatChunks;
+        a.ev = vz_sel::EvictOne{reinterpret_cast<uint64_t*>(own_stats ? a.layer : a.ml + a.nc_max - 1),
+                                own_stats ? a.Hq : static_cast<int64_t>(a.Hq) * a.nc_max, v.ev, v.ev_budget, v.ev_sink,
+                                v.ev_M};
     }
     if (G <= 8)
         hipLaunchKernelGGL((logits_kernel<DT, D, RAG, true>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);

@@ -99,13 +99,17 @@ struct FusedArgs {
     int32_t n_parts, part_keys, R, FB;
     int32_t MB;   // a ragged call's bound on sequences in several parts
     int32_t cus;  // compute units of the device (the choice of parts)
-    // a single sequence: the last workgroup of each layer to finish (elected
-    // on the arrival counters cnt[L] with the call's tag) folds the scores
-    // (Eq. 6; whole-range path in one part) and, when ev != 0, runs the
-    // eviction of the len + 1 slots (Sec. 3.2.2 Eq. 7-9) with budget ev_budget,
-    // ev_sink sinks, an ev_M recent window, optional kept positions ev_kept
-    // [L][ev_budget] and the move counts ev_n [L] of the eviction workspace
+    // a single sequence: the last workgroup of each layer to finish is elected
+    // on the arrival counters, layer l's at cnt[l cnt_stride].  Whole-range path
+    // in one part: counters in the workspace header that carry the call's tag;
+    // it folds the scores (Eq. 6) and, when ev != 0, evicts.  Chunked path, only
+    // when ev != 0: plain counts, zeroed by the attend kernel; the finishing
+    // launch's last fold block evicts.  The eviction of the len + 1 slots (Sec.
+    // 3.2.2 Eq. 7-9) has budget ev_budget, ev_sink sinks, an ev_M recent window,
+    // optional kept positions ev_kept [L][ev_budget] and the move counts ev_n [L]
+    // of the eviction workspace
     uint64_t* cnt;
+    int64_t cnt_stride;
     uint32_t tag;
     int32_t ev, ev_budget, ev_sink, ev_M;
     int32_t* ev_kept;

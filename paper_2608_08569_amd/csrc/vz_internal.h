@@ -406,7 +406,8 @@ size_t vz_decode_range_ws_bytes(int32_t L, int32_t Hq, int32_t Hkv, int64_t plan
 // moved rows; on the other paths one eviction (T = budget + 1) with no kept
 // positions asked for.
 bool vz_decode_evicts(const VzDecodeArgs& a, int32_t budget, bool kept);
-// The layers' arrival counters of a decode workspace.
+// The layers' arrival counters of a decode workspace's header (whole-range
+// path).
 uint64_t* vz_decode_counters(void* ws);
 // A fresh nonzero tag per call (arrival counters of the whole-range path).
 uint32_t vz_call_tag();

@@ -22,9 +22,28 @@ pytestmark = pytest.mark.gpu
     (synth.DT_F32, 128, 16, 4, 2, 127, 4, -1),
     (synth.DT_F32, 128, 3, 3, 2, 300, 1, 5)])
 def test_step_equals_decode_then_evict(dtype, d, Hq, Hkv, L, budget, n_sink, n_recent):
+    compare_steps(dtype, d, Hq, Hkv, L, budget, n_sink, n_recent, budget + 2)
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,L,budget,cap", [
+    (synth.DT_F32, 64, 8, 2, 2, 7167, 7170),         # general path: the last length the folding launch takes
+    (synth.DT_F32, 64, 8, 2, 2, 7168, 7170),         # ... and the first it does not
+    (synth.DT_F32, 64, 2, 1, 2, 8223, 8225),         # ... with one KV head
+    (synth.DT_BF16, 64, 16, 16, 2, 2559, 2561),      # ... with sixteen
+    (synth.DT_BF16, 64, 16, 16, 2, 2560, 2562),
+    (synth.DT_F32, 64, 8, 2, 3, 300, 16384),         # planes of 128 chunks: the blocks' own statistics
+    (synth.DT_F32, 64, 8, 2, 3, 300, 16385),         # 129: statistics in a launch of their own, counters elsewhere
+    (synth.DT_F32, 64, 4, 1, 3, 7000, 16385),
+    (synth.DT_BF16, 128, 16, 2, 3, 300, 16384),      # chunked path: one finishing launch
+    (synth.DT_BF16, 128, 16, 2, 3, 300, 16385)])     # ... two, and the eviction after them
+def test_step_at_the_lines_of_its_dispatch(dtype, d, Hq, Hkv, L, budget, cap):
+    compare_steps(dtype, d, Hq, Hkv, L, budget, 4, -1, cap)
+
+
+def compare_steps(dtype, d, Hq, Hkv, L, budget, n_sink, n_recent, cap):
     import torch
     import paper_2608_08569_amd as vz
-    cap, nxt, steps = budget + 2, budget + 40, 3
+    nxt, steps = budget + 40, 3
     k, v, s, p = synth.random_state(budget, L, Hkv, d, cap, budget, dtype, next_pos=nxt)
     a, b = (GpuCache(L, Hq, Hkv, d, cap, dtype) for _ in range(2))
     for g in (a, b):
