@@ -66,18 +66,23 @@ __device__ int ragged_fuse_status(const FuseArgs& a, int s) {
 
 // Adds rows [b, e) of NC 16-byte columns (gap elements apart) to acc in row
 // order (col: row 0 of the first, stride elements per row), four rows' loads
-// at a time.  bfloat16: the last round's loads past the span read its last row
-// again (a cache hit) and add nothing, so no row waits for another's round
-// trip; a remainder of up to three rows, one load after the other, is most of
-// a span of mean length 4 (48 layers x 4 heads x 32,768 rows: 722 -> 704 us;
-// mean length 1.5: 278 -> 270, 8: 185.5 -> 187).  float32 rows are twice as
-// long and the repeated reads cost what they save (222 against 227 us at 12
-// layers x 20,000 rows): the remainder goes row by row.
+// at a time.  bfloat16: the loads of the remainder go out together too, those
+// past the span reading its last row again (a cache hit) and adding nothing, so
+// no row waits for another's round trip; a remainder of up to three rows, one
+// load after the other, is most of a span of mean length 4 (12 layers x 4 heads
+// x 32,768 rows: mean length 1.2: 305 -> 304 us, 1.5: 277 -> 260, 2: 242 ->
+// 224, 3: 196 -> 185, 5: 176 -> 177, 8: 186 -> 186, 12: 175 -> 175; every round
+// masked, full ones too, costs 4 % at 1.2 and 1 % at 8 and 12; 48 layers, mean
+// length 4.02: 706-724 either way, by where the buffers lie).  Two columns per thread: every round masked in
+// one loop (3584 elements, mean length 4.02: 74.9 -> 68.9 us, 70.2 with the
+// remainder by itself).  float32 rows are twice as long and the repeated reads
+// cost what they save (222 against 227 us at 12 layers x 20,000 rows): the
+// remainder goes row by row.
 template <int DT, int NC>
 __device__ __forceinline__ void add_rows(const typename vz::Elem<DT>::T* col, size_t stride, int gap, int32_t b,
                                          int32_t e, float (*acc)[vz::Elem<DT>::kPer16B]) {
     constexpr int PER = vz::Elem<DT>::kPer16B, ROWS = 4;
-    constexpr bool MASKED = DT == VZ_BF16;
+    constexpr bool MASKED = DT == VZ_BF16, ONE_LOOP = MASKED && NC > 1;
     auto add = [&](const uint4 (&x)[NC], bool on) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -93,14 +98,22 @@ __device__ __forceinline__ void add_rows(const typename vz::Elem<DT>::T* col, si
             x[c] = *reinterpret_cast<const uint4*>(col + static_cast<size_t>(r) * stride + c * gap);
     };
     int32_t r = b;
-    for (; MASKED ? r < e : r + ROWS <= e; r += ROWS) {
+    for (; ONE_LOOP ? r < e : r + ROWS <= e; r += ROWS) {
         uint4 x[ROWS][NC];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) load(MASKED ? min(r + u, e - 1) : r + u, x[u]);
+        for (int u = 0; u < ROWS; ++u) load(ONE_LOOP ? min(r + u, e - 1) : r + u, x[u]);
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) add(x[u], !MASKED || r + u < e);
+        for (int u = 0; u < ROWS; ++u) add(x[u], !ONE_LOOP || r + u < e);
     }
-    if constexpr (!MASKED) {
+    if constexpr (MASKED && !ONE_LOOP) {
+        if (r < e) {
+            uint4 x[ROWS - 1][NC];
+#pragma unroll
+            for (int u = 0; u < ROWS - 1; ++u) load(min(r + u, e - 1), x[u]);
+#pragma unroll
+            for (int u = 0; u < ROWS - 1; ++u) add(x[u], r + u < e);
+        }
+    } else if constexpr (!MASKED) {
         for (; r < e; ++r) {
             uint4 x[NC];
             load(r, x);
