@@ -73,11 +73,11 @@ __device__ int ragged_fuse_status(const FuseArgs& a, int s) {
 // x 32,768 rows: mean length 1.2: 305 -> 304 us, 1.5: 277 -> 260, 2: 242 ->
 // 224, 3: 196 -> 185, 5: 176 -> 177, 8: 186 -> 186, 12: 175 -> 175; every round
 // masked, full ones too, costs 4 % at 1.2 and 1 % at 8 and 12; 48 layers, mean
-// length 4.02: 706-724 either way, by where the buffers lie).  Two columns per thread: every round masked in
-// one loop (3584 elements, mean length 4.02: 74.9 -> 68.9 us, 70.2 with the
-// remainder by itself).  float32 rows are twice as long and the repeated reads
-// cost what they save (222 against 227 us at 12 layers x 20,000 rows): the
-// remainder goes row by row.
+// length 4.02: 706-724 either way, by where the buffers lie).  Two columns per
+// thread: every round masked in one loop (3584 elements, mean length 4.02: 74.9
+// -> 69.2 us, 70.2 with the remainder by itself).  float32 rows are twice as
+// long and the repeated reads cost what they save (222 against 227 us at 12
+// layers x 20,000 rows): the remainder goes row by row.
 template <int DT, int NC>
 __device__ __forceinline__ void add_rows(const typename vz::Elem<DT>::T* col, size_t stride, int gap, int32_t b,
                                          int32_t e, float (*acc)[vz::Elem<DT>::kPer16B]) {
@@ -193,12 +193,10 @@ __global__ __launch_bounds__(256) void fuse_spans_kernel(const FuseArgs a) {
 // block per (span, K-or-V, head, layer); thread t owns the 16-byte columns t,
 // t + threads, ... of the row, NC of them at a time, and sums them over the
 // span's rows in row order, as the lane-group kernel does, so the arithmetic
-// is the same.  Rows of more than WIDE_THREADS columns take two columns at a
-// time (32,768 rows of 3584 bfloat16, spans of mean length 4: 74.5 -> 68.3 us,
-// 5.15 TB/s, with eight loads in flight per thread instead of one to four);
-// narrower ones one, in a block of as many waves as the row needs (the second
-// column's registers would cost waves in flight: 1032 elements 22.6 us with
-// one column, 27.0 with two).
+// is the same.  Two columns at a time (two_columns) keep eight loads in flight
+// per thread instead of one to four, at 81 registers and five waves per SIMD
+// instead of 41 and eight; rows of up to WIDE_THREADS columns take a block of
+// as many waves as they need.
 constexpr int WIDE_THREADS = 256;
 template <int DT, bool RAG, int NC>
 __global__ __launch_bounds__(WIDE_THREADS) void fuse_wide_kernel(const FuseArgs a) {
@@ -261,8 +259,10 @@ __global__ __launch_bounds__(WIDE_THREADS) void fuse_wide_kernel(const FuseArgs 
         }
     };
     for (int c = threadIdx.x; c < nv; c += NC * threads) {
-        if (NC > 1 && c + WIDE_THREADS < nv) columns(std::integral_constant<int, NC>{}, c);
-        else columns(std::integral_constant<int, 1>{}, c);
+        // whole waves take NC columns: a wave whose lanes differ would run both forms
+        const int last = __builtin_amdgcn_readfirstlane((c | (vz::kWave - 1)) + (NC - 1) * WIDE_THREADS);
+        if (NC > 1 && last < nv) columns(std::integral_constant<int, NC>{}, c);
+        else for (int k = c; k < min(nv, c + NC * threads); k += threads) columns(std::integral_constant<int, 1>{}, k);
     }
     if (which == 0 && h == 0 && threadIdx.x == 0) {
         const size_t prow = static_cast<size_t>(l) * a.out_plane + out_row + j;
@@ -287,9 +287,29 @@ hipError_t launch_wide(const FuseArgs& a, int32_t L, hipStream_t stream) {
     hipLaunchKernelGGL((fuse_wide_kernel<DT, false, NC>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
+// Whether rows of nv columns in spans of mean length rows / spans take two
+// columns per thread.  32,768 rows of 3584 elements or as many bytes of others,
+// one and two columns, us: 8192 elements, mean length 1.0: 81.5 and 82.5, 1.2:
+// 73.0 and 71.9, 4.02: 56.1 and 53.6; 5120, 1.2: 70.8 and 75.5, 2.0: 57.2 and
+// 55.0; 3584, 1.0: 76.0 and 86.6, 1.5: 61.3 and 62.3, 1.75: 91.3 and 88.7 (all
+// 32,768 rows), 4.02: 47.9 and 44.6; 2560, 2.0: 54.6 and 56.3, 4.02: 48.9 and
+// 44.9.  Below 320 columns no wave has two.  float32 (remainders row by row)
+// gains a little or nothing at every mean length: 2048 elements, 1.0: 86.8 and
+// 86.1, 8.0: 50.9 and 49.0.  (A ragged call's spans are bounded by max_spans
+// per sequence.)
+template <int DT>
+bool two_columns(int32_t nv, int64_t rows, int64_t spans) {
+    if (nv < WIDE_THREADS + vz::kWave) return false;
+    if (DT == VZ_F32) return true;
+    if (nv >= 768) return 5 * rows >= 6 * spans;
+    return nv >= 448 ? 4 * rows >= 7 * spans : rows >= 3 * spans;
+}
 template <int DT>
 hipError_t launch_wide_any(const FuseArgs& a, int32_t L, hipStream_t stream) {
-    return a.d / vz::Elem<DT>::kPer16B > WIDE_THREADS ? launch_wide<DT, 2>(a, L, stream) : launch_wide<DT, 1>(a, L, stream);
+    const int64_t rows = a.n_seqs > 0 ? a.in_plane : a.T_in;
+    const int64_t spans = a.n_seqs > 0 ? static_cast<int64_t>(a.max_spans) * a.n_seqs : a.n_spans;
+    return two_columns<DT>(a.d / vz::Elem<DT>::kPer16B, rows, spans) ? launch_wide<DT, 2>(a, L, stream)
+                                                                    : launch_wide<DT, 1>(a, L, stream);
 }
 
 template <int DT, int D>

@@ -254,3 +254,25 @@ def test_fuse_wide_rows_at_the_column_rounds(dtype, d):
     for j in range(n):
         if j != 2:
             assert np.all(np.abs(inf[j] - ref[j]) <= RTOL[dtype] * (np.abs(ref[j]) + np.sqrt(np.mean(ref[j] ** 2)))), j
+
+
+@pytest.mark.parametrize("dtype,d", [(synth.DT_BF16, 2552), (synth.DT_BF16, 2560), (synth.DT_BF16, 2816),
+                                     (synth.DT_BF16, 3584), (synth.DT_BF16, 6144), (synth.DT_BF16, 8192),
+                                     (synth.DT_F32, 1276), (synth.DT_F32, 1280), (synth.DT_F32, 4096)])
+def test_fuse_wide_rows_one_and_two_columns_per_thread(dtype, d):
+    """319, 320, 352 (a wave with a second column in half its lanes), 448, 768
+    and 1024 vectors per row: spans of mean length 4 (from 320 vectors on two
+    columns per thread) and the same spans with single rows behind them, which
+    bring the mean below 1.2 (one column in bfloat16), give the same bits."""
+    lens = np.array([1, 2, 3, 4, 5, 7, 8, 9, 1, 6], dtype=np.int64)
+    n, tail = len(lens), 400
+    key = synth.stream_key(23, "fuse-columns", dtype, d)
+    T = int(lens.sum()) + tail
+    x = synth.as_storage(synth.normal_f32(key, T * d).reshape(1, 1, T, d), dtype)
+    short = x[:, :, : T - tail].copy()
+    _, k, v, s, p, sen = _run(short, short, synth.offsets_from_lengths(lens), dtype, n + 1)
+    _verify(short, short, synth.offsets_from_lengths(lens), dtype, k, v, s, p, sen)
+    off = synth.offsets_from_lengths(np.concatenate([lens, np.ones(tail, dtype=np.int64)]))
+    _, k1, v1, s, p, sen = _run(x, x, off, dtype, n + tail + 1)
+    assert np.array_equal(k1[:, :, :n], k[:, :, :n]) and np.array_equal(v1[:, :, :n], v[:, :, :n])
+    assert np.array_equal(k1[:, :, n: n + tail], x[:, :, T - tail:])
