@@ -169,16 +169,11 @@ __device__ __forceinline__ float2 merge_pairs(const float2 (&p)[kPairs], int nc,
     }
     return make_float2(m, row16_sum(z));
 }
+// The sum of a head's pairs relative to their max m.
 template <class Rel>
-__device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int i, Rel rel) {
+__device__ __forceinline__ float merge_sum(const float2* ml, int nc, int i, float m, Rel rel) {
     float2 p[kPairs];
-    float m = -INFINITY, z = 0.f;
-    for (int c0 = i; c0 - i < nc; c0 += kPairChunks) {
-        load_pairs(ml, nc, c0, p);
-#pragma unroll
-        for (int k = 0; k < kPairs; ++k) m = fmaxf(m, p[k].x);  // a clamped pair is one of the head's own
-    }
-    m = row16_max(m);
+    float z = 0.f;
     for (int c0 = i; c0 - i < nc; c0 += kPairChunks) {
         load_pairs(ml, nc, c0, p);
 #pragma unroll
@@ -187,7 +182,19 @@ __device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int i, Rel
             z = fmaf(c0 + 16 * k < nc ? p[k].y : 0.f, f, z);
         }
     }
-    return make_float2(m, row16_sum(z));
+    return row16_sum(z);
+}
+template <class Rel>
+__device__ __forceinline__ float2 merge_all(const float2* ml, int nc, int i, Rel rel) {
+    float2 p[kPairs];
+    float m = -INFINITY;
+    for (int c0 = i; c0 - i < nc; c0 += kPairChunks) {
+        load_pairs(ml, nc, c0, p);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) m = fmaxf(m, p[k].x);  // a clamped pair is one of the head's own
+    }
+    m = row16_max(m);
+    return make_float2(m, merge_sum(ml, nc, i, m, rel));
 }
 
 // Inclusive wave scan (DPP row shifts, then the row totals broadcast upwards).
