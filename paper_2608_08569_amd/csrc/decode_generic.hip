@@ -74,10 +74,62 @@ struct GenericArgs {
     vz_sel::EvictOne ev;              // a single sequence's eviction, by the launch that folds
 };
 
-// Flat chunk f of a layer: false when it holds no work; c = chunk inside the sequence.
-template <bool RAG>
+// The same search as vz::locate_ragged_chunk for batches of more than kManySeqs
+// sequences: kSeqRounds rounds of 64 sequences loaded at once.  With a block
+// per chunk and KV head, the rounds' load latencies one after another are most
+// of such a call's time when its sequences are short (16 heads and KV heads,
+// 2,000 sequences of 20 keys: one layer 856 -> 695 us, 8 layers 6,820 -> 5,430;
+// 14 / 2 heads, d = 64: one layer 177 -> 165, but 513 of 20 keys 30.1 -> 31.7 and
+// 8 layers, 300 of 10-1,500 keys 428 -> 448: not used there).
+constexpr int kManySeqs = 1024, kSeqRounds = 8;
+__device__ __forceinline__ bool locate_chunk_of_many(const VzRagged& r, int nc_max, int f, SeqItem& it, int& c) {
+    const int lane = threadIdx.x % vz::kWave;
+    int run = 0;
+    for (int s0 = 0; s0 < r.n; s0 += kSeqRounds * vz::kWave) {
+        int64_t b[kSeqRounds];
+        int cp[kSeqRounds], ln[kSeqRounds], np[kSeqRounds];
+#pragma unroll
+        for (int k = 0; k < kSeqRounds; ++k) {
+            const int su = min(s0 + k * vz::kWave + lane, r.n - 1);  // load for every lane, mask after
+            b[k] = r.base[su];
+            cp[k] = r.cap[su];
+            ln[k] = r.len[su];
+            np[k] = r.next_pos[su];
+        }
+#pragma unroll
+        for (int k = 0; k < kSeqRounds; ++k) {
+            const bool ok = (s0 + k * vz::kWave + lane < r.n) & vz::decode_served(b[k], cp[k], ln[k], np[k], r.total);
+            const int n = ok ? (ln[k] + kChunk) / kChunk : 0;
+            const int incl = vz::wave_incl_scan(n);
+            const unsigned long long hit = __ballot(run + incl > f);
+            if (hit) {
+                const int src = __builtin_ctzll(hit);
+                it.n_chunks = __builtin_amdgcn_readlane(n, src);
+                it.first = run + __builtin_amdgcn_readlane(incl, src) - it.n_chunks;
+                it.s = s0 + k * vz::kWave + src;
+                it.len = __builtin_amdgcn_readlane(ln[k], src);
+                it.next_pos = __builtin_amdgcn_readlane(np[k], src);
+                const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(b[k]), src);
+                const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(b[k] >> 32), src);
+                it.base = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+                c = f - it.first;
+                return it.first + it.n_chunks <= nc_max;
+            }
+            run += __builtin_amdgcn_readlane(incl, vz::kWave - 1);
+            if (run > nc_max) return false;
+        }
+    }
+    return false;
+}
+
+// Flat chunk f of a layer: false when it holds no work; c = chunk inside the
+// sequence.  RAG: 0 a single sequence, 1 a ragged batch, 2 one of many
+// sequences.
+template <int RAG>
 __device__ __forceinline__ bool resolve_chunk(const GenericArgs& a, int f, SeqItem& it, int& c) {
-    if constexpr (RAG) {
+    if constexpr (RAG == 2) {
+        return locate_chunk_of_many(a.rag, a.nc_max, f, it, c);
+    } else if constexpr (RAG == 1) {
         return vz::locate_ragged_chunk(a.rag, a.nc_max, f, it, c);
     } else {
         it = SeqItem{0, a.len, a.next_pos, a.n_chunks, 0, 0};
@@ -121,7 +173,7 @@ __device__ __forceinline__ float exp_rel(float x, float m) { return x == -INFINI
 
 // PACK: groups of at most 8 heads, whose second tile's logits are rotated into
 // head columns 8..15, so every exp serves a key and a head that exist.
-template <int DT, int D, bool RAG, bool PACK>
+template <int DT, int D, int RAG, bool PACK>
 __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
@@ -308,7 +360,7 @@ __device__ void evict_layer(const GenericArgs& a, int l) {
 // the second 16 keys of a wave's 32, so every exp serves a key and a head that
 // exist; a rotation by 8 lanes makes them the second tile's B operand (the
 // other columns of either product hold heads that are not read).
-template <int DT, int D, bool RAG, bool PACK>
+template <int DT, int D, int RAG, bool PACK>
 __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     using E = vz::Elem<DT>;
     using T = typename E::T;
@@ -330,12 +382,12 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     Runs rn;
     if constexpr (RAG) {
         // grid over chunk rows: the first chunk of each run works
-        if (!resolve_chunk<true>(a, blockIdx.x, it, c0)) return;
+        if (!resolve_chunk<RAG>(a, blockIdx.x, it, c0)) return;
         rn = runs_of(it.n_chunks, G);
         run = c0 / rn.step;
         if (run >= rn.n || c0 != run * rn.step) return;
     } else {
-        resolve_chunk<false>(a, 0, it, c0);
+        resolve_chunk<0>(a, 0, it, c0);
         rn = runs_of(it.n_chunks, G);
         run = blockIdx.x;
         c0 = run * rn.step;
@@ -510,10 +562,14 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
     }
 }
 
+// Blocks per sequence behind the fold blocks: one per head, or with one head
+// per KV head, where a sequence is always one run, one for the status alone.
+__host__ __device__ inline int out_heads(int Hq, int G) { return G == 1 ? 1 : Hq; }
+
 // Fold blocks [0, fold_blocks) of a layer: one chunk's scores, thread = key.
 // The blocks after them: one (head, sequence)'s output row from its runs, and
 // in a ragged call the sequence's status.
-template <int DT, int D, bool RAG>
+template <int DT, int D, int RAG>
 __global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int fold_blocks) {
     using E = vz::Elem<DT>;
     const int l = blockIdx.y, t = threadIdx.x;
@@ -537,7 +593,7 @@ __global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int
         }
         return;
     }
-    const int ob = static_cast<int>(blockIdx.x) - fold_blocks, h = ob % Hq, s = ob / Hq;
+    const int ob = static_cast<int>(blockIdx.x) - fold_blocks, heads = out_heads(Hq, G), h = ob % heads, s = ob / heads;
     int first = 0, nc = a.n_chunks;
     if constexpr (RAG) {
         const int st = vz::ragged_decode_status(a.rag, s);
@@ -557,7 +613,7 @@ __global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int
     static_cast<typename E::T*>(a.out)[((static_cast<size_t>(s) * a.L + l) * Hq + h) * D + t] = E::from_f32(o);
 }
 
-template <int DT, int D, bool RAG>
+template <int DT, int D, int RAG>
 hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
     GenericArgs a{};
     a.q = v.q;
@@ -601,7 +657,7 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if ((a.plane + kChunk - 1) / kChunk > kStatChunks) {
-        hipLaunchKernelGGL((stats_kernel<RAG>), dim3((a.Hq + 15) / 16, a.L, seqs), dim3(kThreads), 0, stream, a);
+        hipLaunchKernelGGL((stats_kernel<(RAG != 0)>), dim3((a.Hq + 15) / 16, a.L, seqs), dim3(kThreads), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -612,7 +668,7 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int folds = a.Hkv > 1 ? chunks : 0;  // one KV head: folded by the values kernel
-    const int outs = RAG || runs > 1 ? a.Hq * seqs : 0;
+    const int outs = RAG || runs > 1 ? out_heads(a.Hq, G) * seqs : 0;
     if (folds + outs == 0) return hipSuccess;
     hipLaunchKernelGGL((finish_kernel<DT, D, RAG>), dim3(folds + outs, a.L), dim3(kChunk), 0, stream, a, folds);
     return hipGetLastError();
@@ -620,7 +676,8 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
 
 template <int DT, int D>
 hipError_t launch_any(const VzDecodeArgs& v, hipStream_t stream) {
-    return v.rag.n > 0 ? launch<DT, D, true>(v, stream) : launch<DT, D, false>(v, stream);
+    if (v.rag.n > kManySeqs) return launch<DT, D, 2>(v, stream);
+    return v.rag.n > 0 ? launch<DT, D, 1>(v, stream) : launch<DT, D, 0>(v, stream);
 }
 
 }  // namespace

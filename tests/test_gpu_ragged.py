@@ -528,3 +528,44 @@ def test_ragged_many_sequences():
     budgets = np.maximum(lens // 2, 8)
     cases = [(int(x), int(b), int(x) + 3) for x, b in zip(lens, budgets)]
     _run_evict_case(synth.DT_BF16, 128, 4, cases, L=1, seed=42)
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,n", [(synth.DT_F32, 64, 4, 4, 1025), (synth.DT_BF16, 64, 6, 2, 2100)])
+def test_ragged_decode_of_many_sequences_on_the_general_path(dtype, d, Hq, Hkv, n):
+    """More than 1024 sequences (their search loads eight rounds of 64 at once)
+    in one call and as calls of at most 1024: the same bits and statuses, idle
+    slots and sequences without room among them."""
+    t = torch()
+    import paper_2608_08569_amd as vz
+    L, key = 2, synth.stream_key(67, dtype, n)
+    lens = synth.uniform_int(key, 0, n, 0, 200).astype(np.int64)
+    caps = lens + 2
+    pk = Packed(caps, gap=1, seed=n)
+    lens[::9] = caps[::9]  # no free slot
+    held = np.where(np.arange(n) % 7 == 3, 0, caps)  # idle slots
+    K, V, q, kn, vn = (_storage_noise(key + i, s, dtype) for i, s in enumerate((
+        (L, Hkv, pk.total, d), (L, Hkv, pk.total, d), (n, L, Hq, d), (n, L, Hkv, d), (n, L, Hkv, d))))
+    S = synth.uniform01(key, 0, L * pk.total).reshape(L, pk.total).astype(np.float32)
+    P = np.zeros((L, pk.total), dtype=np.int32)
+    base_d, _ = pk.dev()
+    cap_d, len_d, next_d, qd, knd, vnd = _i32(held), _i32(lens), _i32(lens + 5), to_dev(q), to_dev(kn), to_dev(vn)
+    got = []
+    for step in (n, 1024):
+        Kd, Vd, Sd, Pd = to_dev(K), to_dev(V), to_dev(S), to_dev(P)
+        out, status = t.zeros_like(qd), _i32(np.full(n, -99))
+        for a in range(0, n, step):
+            b = min(n, a + step)
+            vz.voxzip_decode_attend_score_ragged(
+                qd[a:b], knd[a:b], vnd[a:b], Kd, Vd, Sd, Pd, out[a:b], base_d[a:b], cap_d[a:b], len_d[a:b], next_d[a:b],
+                0.95, status=status[a:b], workspace=vz.workspace_ragged(vz.VZ_OP_DECODE, L, Hq, Hkv, d, pk.total, b - a))
+        got.append([from_dev(x) for x in (out, status, Sd, Pd, Kd, Vd)])
+    for x, y, what in zip(*got, ("outputs", "statuses", "scores", "positions", "K", "V")):
+        assert np.array_equal(x, y), what
+    want = np.where(held == 0, vz.VZ_IDLE, np.where(np.arange(n) % 9 == 0, vz.VZ_ERR_CAPACITY, vz.VZ_OK))
+    assert np.array_equal(got[0][1], want)
+    for i in np.flatnonzero(want == vz.VZ_OK)[:: n // 8]:
+        sl = pk.sl(i)
+        ref_o, ref_s, _, _ = oracle.decode_step(q[i], kn[i], vn[i], K[:, :, sl], V[:, :, sl], S[:, sl].astype(np.float64),
+                                                P[:, sl], int(lens[i]), int(lens[i]) + 5, 0.95, dtype)
+        check_close(widen(got[0][0][i], dtype), ref_o, RTOL[dtype], f"sequence {i} output")
+        check_rel(got[0][2][:, sl][:, : lens[i] + 1], ref_s, RTOL[dtype], f"sequence {i} score")
