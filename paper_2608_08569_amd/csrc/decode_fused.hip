@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * SPLIT_W, 4) void decode_attend_kernel(const Fu
         // Lane (r16, q4) holds K channels 8 (q4 + 4 s) .. + 7 of its K rows and V
         // channels 8 r16 .. + 7 of its V rows (the tile layouts below).
         const int rr = len - kw0;
-        if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l * a.cnt_stride] = 0;  // counted by the finishing launch
+        if (!RAG && a.ev != 0 && f == 0 && g == 0 && tid == 0) a.cnt[l * static_cast<size_t>(a.cnt_stride)] = 0;  // counted by the finishing launch
         const bool writer = rr >= 0 && rr < VT;  // wave-uniform
         uint4 kn_row[KSTEPS], vn_row;
         if (writer) {
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(OUT_THREADS) void decode_finish_kernel(const FusedA
     fold_finish(a, ld, s_f, sc, Hq, nk, j == it.len, evict);
     if constexpr (!RAG) {
         if (!evict) return;
-        const vz_sel::EvictOne e{a.cnt, a.cnt_stride, a.ev, a.ev_budget, a.ev_sink, a.ev_M};
+        const vz_sel::EvictOne e{a.cnt, a.cnt_stride, a.ev_budget, a.ev_sink, a.ev_M};
         if (!vz_sel::last_of_layer(e, l, a.n_chunks)) return;
         const size_t row = static_cast<size_t>(l) * a.plane;
         const int Hkv = a.Hkv;

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const GenericArgs a) {
             T* dst = (tid < CH ? K : V) + static_cast<size_t>(len) * D + o;
             *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>((tid < CH ? kn : vn) + o);
         }
-        if (!RAG && a.ev.on && g == 0 && tid == 2 * CH) a.ev.cnt[l * a.ev.stride] = 0;  // counted by the launch that folds
+        if (!RAG && a.ev.cnt && g == 0 && tid == 2 * CH) a.ev.cnt[l * static_cast<size_t>(a.ev.stride)] = 0;  // counted by the launch that folds
         if (g == 0 && tid == 2 * CH) a.pos[static_cast<size_t>(l) * a.plane + it.base + len] = it.next_pos;
     }
     if (r16 >= G) {  // unused head columns
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
         if (hc < 4) {
             if (fold) {
                 if (k0 + key_off <= len)
-                    vz_sel::store_score(sc + k0 + key_off, fmaf(a.gamma, p.old, sum), !RAG && a.ev.on);
+                    vz_sel::store_score(sc + k0 + key_off, fmaf(a.gamma, p.old, sum), !RAG && a.ev.cnt);
             } else {
                 // (the logits of these keys are in registers: only this wave reads them)
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), logits_of(x), 4 * (k0 % kChunk + key_off), 0, 0);
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(kThreads) void values_kernel(const GenericArgs a) {
             run_out(a, l, it.first + c0, g, G, h)[ch] = o;
     }
     if constexpr (!RAG) {
-        if (fold && a.ev.on && vz_sel::last_of_layer(a.ev, l, rn.n)) evict_layer<kThreads, T, D>(a, l);
+        if (fold && a.ev.cnt && vz_sel::last_of_layer(a.ev, l, rn.n)) evict_layer<kThreads, T, D>(a, l);
     }
 }
 
@@ -586,10 +586,10 @@ __global__ __launch_bounds__(kChunk) void finish_kernel(const GenericArgs a, int
     #pragma unroll 4
             for (int g = 0; g < Hkv; ++g) sum += a.S[ws_row(a, l, it.first + c, g * G) * kChunk + t];
             // (zero pad of Eq. (6) for the new slot)
-            vz_sel::store_score(sc, fmaf(a.gamma, key < it.len ? old : 0.f, sum), !RAG && a.ev.on);
+            vz_sel::store_score(sc, fmaf(a.gamma, key < it.len ? old : 0.f, sum), !RAG && a.ev.cnt);
         }
         if constexpr (!RAG) {
-            if (a.ev.on && vz_sel::last_of_layer(a.ev, l, fold_blocks)) evict_layer<kChunk, typename E::T, D>(a, l);
+            if (a.ev.cnt && vz_sel::last_of_layer(a.ev, l, fold_blocks)) evict_layer<kChunk, typename E::T, D>(a, l);
         }
         return;
     }
@@ -645,10 +645,11 @@ hipError_t launch(const VzDecodeArgs& v, hipStream_t stream) {
         runs = runs_of(chunks, G).n;
         // arrival counters: in the layer statistics' place, or, where those are
         // used, in a pair of each layer's head 0 past the sequence's chunks
+        // (whose distance, a layer's pairs, passes 2^31 at terabytes of cache)
         const bool own_stats = (a.plane + kChunk - 1) / kChunk <= kStatChunks;
-        a.ev = vz_sel::EvictOne{reinterpret_cast<uint64_t*>(own_stats ? a.layer : a.ml + a.nc_max - 1),
-                                own_stats ? a.Hq : static_cast<int64_t>(a.Hq) * a.nc_max, v.ev, v.ev_budget, v.ev_sink,
-                                v.ev_M};
+        if (v.ev)
+            a.ev = vz_sel::EvictOne{reinterpret_cast<uint64_t*>(own_stats ? a.layer : a.ml + a.nc_max - 1),
+                                    own_stats ? a.Hq : a.Hq * a.nc_max, v.ev_budget, v.ev_sink, v.ev_M};
     }
     if (G <= 8)
         hipLaunchKernelGGL((logits_kernel<DT, D, RAG, true>), dim3(chunks, a.L, a.Hkv), dim3(kThreads), 0, stream, a);

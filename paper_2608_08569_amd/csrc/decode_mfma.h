@@ -109,8 +109,8 @@ struct FusedArgs {
     // optional kept positions ev_kept [L][ev_budget] and the move counts ev_n [L]
     // of the eviction workspace
     uint64_t* cnt;
-    int64_t cnt_stride;
     uint32_t tag;
+    int32_t cnt_stride;
     int32_t ev, ev_budget, ev_sink, ev_M;
     int32_t* ev_kept;
     int32_t* ev_n;

@@ -494,9 +494,8 @@ __device__ void select_body(const SelJob<typename vz::Elem<DT>::T>& job, SH& sh,
 // calls leave free: side by side, the blocks of all layers queue for one or two
 // lines of memory (24 layers of 65 blocks 56.6 us, apart 46.6).
 struct EvictOne {
-    uint64_t* cnt;   // of layer 0; zeroed by the call's first launch, zero again after it
-    int64_t stride;  // from layer to layer
-    int32_t on, budget, n_sink, M;
+    uint64_t* cnt;  // of layer 0; zeroed by the call's first launch, zero again after it; null: no eviction
+    int32_t stride, budget, n_sink, M;  // stride: from one layer's counter to the next
 };
 __device__ __forceinline__ void store_score(float* p, float x, bool coherent) {
     if (coherent) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -512,7 +511,7 @@ __device__ __forceinline__ bool last_of_layer(const EvictOne& e, int l, int n) {
     // compare-and-swap of arrive_last is tried again and again -- 16 layers of
     // 17 blocks took 12 us longer)
     if (threadIdx.x == 0) {
-        uint64_t* const c = e.cnt + l * e.stride;
+        uint64_t* const c = e.cnt + l * static_cast<size_t>(e.stride);
         s_last = __hip_atomic_fetch_add(c, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                  static_cast<uint64_t>(n - 1);
         if (s_last) __hip_atomic_store(c, uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
