@@ -86,12 +86,6 @@ struct Exp2Weight {
     __device__ __forceinline__ float operator()(float x, float m) const { return __builtin_amdgcn_exp2f(x - m); }
 };
 
-// What the exp of keys with max m is relative to: m, or 0 when no key has a
-// finite logit (a key at -infinity, in a wave of its own or among others): the
-// keys' p and their weight beside others are then 0, where -inf - -inf would
-// make the head's output and scores not a number.
-__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
-
 // Flat chunk f of a call: false when it holds no work.
 template <bool RAG>
 __device__ __forceinline__ bool resolve_chunk(const FusedArgs& a, int f, SeqItem& it, int& c) {

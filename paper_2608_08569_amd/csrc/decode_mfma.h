@@ -72,6 +72,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+// What the exp of keys with max m is relative to: m, or 0 when no key has a
+// finite logit (a key at -infinity, in a wave of its own or among others): the
+// keys' p and their weight beside others are then 0, where -inf - -inf would
+// make the head's output and scores not a number.
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 // Kernel arguments shared by the decode launches.  A single-sequence call
 // has rag.n == 0 and takes len, next_pos and n_chunks from here; a ragged
 // call reads them per sequence, and n_chunks is then its grid extent per

@@ -332,15 +332,13 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
     const uint8_t* const kr = buf + r16 * KSTRIDE + 16 * q4;
     const uint8_t* const vr = buf + (4 * q4 + (r16 >> 2)) * VSTRIDE + 16 * ((r16 & 3) >> 1) + 8 * (r16 & 1);
 
-    uint4 qv[KSTEPS];  // B operand: Q^T, column r16 = query head (zero past G)
+    // B operand: Q^T, column r16 = query head (past the group head 0 again: its
+    // p~ there are finite whatever the keys hold, and weigh 0 in the key sums)
+    uint4 qv[KSTEPS];
     {
-        const int hq = r16 < G ? r16 : 0;
-        const uint16_t* qrow = a.q + (seq_row * Hq + g * G + hq) * D + 8 * q4;
+        const uint16_t* qrow = a.q + (seq_row * Hq + g * G + (r16 < G ? r16 : 0)) * D + 8 * q4;
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) {
-            const uint4 v = *reinterpret_cast<const uint4*>(qrow + 32 * s);
-            qv[s] = (r16 < G) ? v : make_uint4(0, 0, 0, 0);
-        }
+        for (int s = 0; s < KSTEPS; ++s) qv[s] = *reinterpret_cast<const uint4*>(qrow + 32 * s);
     }
 
     // Running state of head hh (columns r16 and r16 + 8 of the outputs hold
@@ -398,12 +396,13 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
         m_c = fmaxf(m_c, ror8(m_c));
         const float m_new = fmaxf(m_w, m_c);
         const float alpha = m_w == -INFINITY ? 0.f : exp2f(m_w - m_new);
+        const float ref = finite_ref(m_new);
         float l_c = 0.f;
 #pragma unroll
         for (int u = 0; u < PAIRS; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                sp[u][i] = exp2f(sp[u][i] - m_new);
+                sp[u][i] = exp2f(sp[u][i] - ref);
                 l_c += sp[u][i];
             }
         l_c += __shfl_xor(l_c, 16, 64);
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(64 * RW, 1) void decode_range_kernel(const FusedArg
     // a part of a longer sequence keeps its output and p~ relative to its own
     // max; the finishing launch applies the sequence's statistics
     const float inv_S = split ? 1.f : 1.0f / S;
-    if (w == 0 && q4 == 0 && hi == 0) s_MS[hh] = make_float2(M, inv_S);  // read after the next barrier
+    if (w == 0 && q4 == 0 && hi == 0) s_MS[hh] = make_float2(finite_ref(M), inv_S);  // read after the next barrier
     const size_t part_row = (static_cast<size_t>(l) * NW + g) * a.R + r;  // (layer, KV head, item) of pstat, pout
     if (split && w == 0 && q4 == 0 && hi == 0 && hh < G) rws.pstat[part_row * GMAX + hh] = make_float2(M, S);
 

@@ -64,3 +64,50 @@ def test_keys_without_a_finite_logit(dtype, d, Hq, Hkv, L, length, first, last):
         torch.cuda.synchronize()
         assert np.array_equal(from_dev(o[n - 1]), out)
         assert np.array_equal(from_dev(A)[:, at: at + length + 1], S[:, : length + 1])
+
+
+@pytest.mark.parametrize("Hq,Hkv,L", [(32, 4, 32), (6, 2, 64)])
+@pytest.mark.parametrize("T,first,last", [
+    (300, 0, 130),       # the first chunk of a wave and keys of the next
+    (300, 256, 300),     # the partial chunk
+    (1500, 128, 1500),   # all chunks but the first
+    (8224, 0, 8000),     # whole waves
+    (9001, 0, 4608),     # the first of two parts
+    (9001, 4000, 9001)]) # the second, and the end of the first
+def test_keys_without_a_finite_logit_on_the_whole_range_path(Hq, Hkv, L, T, first, last):
+    import math
+
+    import torch
+    import paper_2608_08569_amd as vz
+    g = torch.Generator(device="cuda").manual_seed(T + first)
+    n, d, gamma, bf, base = T - 1, 128, 0.95, torch.bfloat16, 9
+    mk = lambda *shape: torch.randn(*shape, generator=g, device="cuda", dtype=bf)
+    K, V, q, kn, vn = mk(L, Hkv, base + T, d), mk(L, Hkv, base + T, d), mk(2, L, Hq, d), mk(2, L, Hkv, d), mk(2, L, Hkv, d)
+    q[..., 5] = 1.0  # every head's query: positive on the channel that is infinite
+    K[:, :, base + first: base + min(last, n), 5] = -math.inf
+    if last == T:
+        kn[1, ..., 5] = -math.inf
+    S = torch.rand(L, base + T, generator=g, device="cuda")
+    P = torch.arange(base + T, dtype=torch.int32, device="cuda").repeat(L, 1)
+    k1, v1, s1, p1 = (x[:, :, base:].contiguous() if x.dim() == 4 else x[:, base:].contiguous() for x in (K, V, S, P))
+    out = torch.zeros(L, Hq, d, dtype=bf, device="cuda")
+    vz.voxzip_decode_attend_score(q[1], kn[1], vn[1], k1, v1, s1, p1, out, n, n, gamma,
+                                  workspace=vz.workspace(vz.VZ_OP_DECODE, L, Hq, Hkv, d, T))
+    for l in (0, L - 1):
+        ref_o, ref_s = [], gamma * S[l, base:].double()
+        ref_s[n] = 0
+        for h in range(Hkv):
+            kd, vd = k1[l, h].double(), v1[l, h].double()
+            s = (q[1, l].view(Hkv, -1, d)[h].double()[:, None] * kd[None]).sum(-1) / math.sqrt(d)
+            a = torch.softmax(s, -1)
+            ref_o.append(a @ vd)
+            ref_s += a.sum(0)
+        check_close(out[l].double().cpu().numpy(), torch.cat(ref_o).cpu().numpy(), RTOL[synth.DT_BF16], f"layer {l} output")
+        check_rel(s1[l].double().cpu().numpy(), ref_s.cpu().numpy(), RTOL[synth.DT_BF16], f"layer {l} score")
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    o = torch.zeros(2, L, Hq, d, dtype=bf, device="cuda")
+    vz.voxzip_decode_attend_score_ragged(q, kn, vn, K, V, S, P, o, torch.tensor([0, base], device="cuda"),
+                                         i32([base, T]), i32([base - 1, n]), i32([base - 1, n]), gamma,
+                                         workspace=vz.workspace_ragged(vz.VZ_OP_DECODE, L, Hq, Hkv, d, base + T, 2))
+    torch.cuda.synchronize()
+    assert torch.equal(o[1], out) and torch.equal(S[:, base:], s1)
