@@ -143,14 +143,14 @@ def test_gamma_edges_and_explicit_scale():
         assert abs(S.sum() - expect) <= 1e-4 * expect
 
 
-@pytest.mark.parametrize("length", [16383, 16384])
-def test_single_and_ragged_calls_agree_on_long_sequences(length):
-    """T = 16,384 and 16,385 keys (128 and 129 chunks): the single-sequence call
-    against the oracle and bit for bit against the ragged call on the same data."""
+@pytest.mark.parametrize("length,cap", [(16383, 16384), (16383, 16385), (16384, 16386)])
+def test_single_and_ragged_calls_agree_on_long_sequences(length, cap):
+    """T = 16,384 and 16,385 keys (128 and 129 chunks) in planes of 128 chunks
+    (one finishing launch) and of 129 (two): the single-sequence call against
+    the oracle and bit for bit against the ragged call on the same data."""
     import torch
     import paper_2608_08569_amd as vz
     dtype, L, Hq, Hkv, d = synth.DT_BF16, 1, 32, 4, 128
-    cap = length + 2
     k, v, s, p = synth.random_state(31, L, Hkv, d, cap, length, dtype, next_pos=length + 5)
     w = synth.workload("layer")
     q, kn, vn = synth.decode_inputs(w, 1)

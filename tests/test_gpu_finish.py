@@ -19,21 +19,23 @@ def _i32(a):
     return torch.tensor(np.asarray(a), dtype=torch.int32, device="cuda")
 
 
-@pytest.mark.parametrize("Hq,Hkv,L,lens", [
-    (32, 4, 1, [130, 1700, 1, 5, 260, 2047]),       # one launch, several sequences
-    (64, 8, 1, [900, 127]),                         # 64 heads: four rounds of 16
-    (6, 2, 2, [300, 31]),                           # heads that do not fill a wave's quarter
-    (8, 1, 1, [17000, 40, 90, 1000]),               # 133 chunks in a batch of one launch
-    (32, 4, 1, [300] * 70),                         # too many blocks for one launch
-    (16, 4, 1, [16383]), (16, 4, 1, [16384])])      # 128 and 129 chunks of one sequence
-def test_ragged_calls_match_single_calls_and_the_oracle(Hq, Hkv, L, lens):
+@pytest.mark.parametrize("Hq,Hkv,L,lens,slots", [
+    (32, 4, 1, [130, 1700, 1, 5, 260, 2047], 2),       # one launch, several sequences
+    (64, 8, 1, [900, 127], 2),                         # 64 heads: four rounds of 16
+    (6, 2, 2, [300, 31], 2),                           # heads that do not fill a wave's quarter
+    (8, 1, 1, [17000, 40, 90, 1000], 2),               # 133 chunks in a batch of one launch
+    (32, 4, 1, [300] * 70, 2),                         # too many blocks for one launch
+    (16, 4, 1, [16383], 1),                            # 128 chunks of one sequence in planes of 128: one launch
+    (16, 4, 1, [16383], 2), (16, 4, 1, [16384], 1),    # 128 and 129 chunks in planes of 129: two launches
+    (16, 4, 1, [16384], 2)])
+def test_ragged_calls_match_single_calls_and_the_oracle(Hq, Hkv, L, lens, slots):
     import torch
     import paper_2608_08569_amd as vz
     n, gamma, dt = len(lens), 0.95, synth.DT_BF16
     key = synth.stream_key(41, Hq, Hkv, L, n, lens[0])
     noise = lambda tag, shape: synth.as_storage(
         synth.normal_f32(synth.stream_key(key, tag), int(np.prod(shape))).reshape(shape), dt)
-    caps = np.asarray(lens) + 2
+    caps = np.asarray(lens) + slots  # at least one free slot
     base = np.concatenate([[0], np.cumsum(caps)[:-1]])
     total = int(caps.sum())
     K, V = noise("K", (L, Hkv, total, D)), noise("V", (L, Hkv, total, D))

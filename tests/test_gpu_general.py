@@ -26,13 +26,17 @@ CASES = [  # dtype, d, Hq, Hkv, resident keys before the step
     (synth.DT_BF16, 128, 9, 1, 260), (synth.DT_BF16, 128, 32, 2, 1023), (synth.DT_BF16, 128, 5, 5, 300),
     (synth.DT_F32, 64, 4, 2, 16899), (synth.DT_BF16, 64, 16, 1, 17100),
 ]
+# 128 chunks in planes of 128, whose workgroups merge the statistics themselves
+# (the ragged twin's planes have 129: a launch of its own), and of 129
+EDGES = [(synth.DT_F32, 64, 4, 2, 16383, 1), (synth.DT_F32, 64, 4, 2, 16383, 2), (synth.DT_F32, 64, 4, 2, 16384, 1),
+         (synth.DT_BF16, 64, 14, 2, 16383, 1), (synth.DT_BF16, 64, 4, 1, 16383, 1)]
 
 
-@pytest.mark.parametrize("dtype,d,Hq,Hkv,length", CASES)
-def test_general_path_against_oracle_and_ragged_twin(dtype, d, Hq, Hkv, length):
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,length,slots", [c + (3,) for c in CASES] + EDGES)
+def test_general_path_against_oracle_and_ragged_twin(dtype, d, Hq, Hkv, length, slots):
     import torch
     import paper_2608_08569_amd as vz
-    L, cap, gamma, nxt = 2, length + 3, 0.95, length + 9
+    L, cap, gamma, nxt = 2, length + slots, 0.95, length + 9
     k, v, s, p = synth.random_state(31, L, Hkv, d, cap, length, dtype, next_pos=nxt)
     key = synth.stream_key(31, dtype, d, Hq, Hkv, length)
     mk = lambda tag, shape: synth.as_storage(
