@@ -514,7 +514,8 @@ __device__ void output_block(const FusedArgs& a, int h, int l, int s, bool store
 // A[j] = gamma A[j] + sum_h p~_hj f_h with f_h = exp2(m_c,h - M_h) / S_h (the
 // new slot starts from 0).  Wave w adds its quarter of the heads for every key
 // of the chunk, two keys per lane, and the four waves' sums meet in LDS.  The
-// p~ loads (rows are complete, CHUNK entries each) and the old score's are
+// p~ loads (rows of CHUNK entries; those past the chunk's keys hold anything, a
+// lane's two keys stay apart and the store is masked) and the old score's are
 // issued before the factors are known.
 constexpr int FOLD_HEADS = 16;  // heads per wave: Hq <= Hkv * GMAX with Hkv <= 8
 struct FoldLoads {

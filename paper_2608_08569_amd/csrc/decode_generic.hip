@@ -24,12 +24,14 @@
 // bfloat16 are exact in float32); bfloat16 values are widened first, so that p
 // keeps its 24 bits.  At 16 heads the float32 instruction needs about a
 // quarter of its rate to keep up with HBM, so large calls are bound by memory
-// and small ones by the launches and the round trips inside each.  Measured
-// (kernel times, before: one thread per key for the logits, one workgroup per
+// and small ones by the launches and the round trips inside each.  Measured,
+// whole passes (before: one thread per key for the logits, one workgroup per
 // (layer, head) for softmax and P V, one thread per key for the scores):
-//   16 layers, 16Q/4KV, d = 128, float32, 2049 keys   365 -> 38 us (3.6 TB/s)
-//   24 layers, 14Q/2KV, d = 64, bfloat16, 4001 keys   345 -> 25 us (2.0 TB/s)
-//   1 layer, 4Q/1KV, d = 64, float32, 129 keys        22.4 -> 10.5 us (with the eviction)
+//   16 layers, 16Q/4KV, d = 128, float32, 2049 keys, with the eviction
+//                                                     499 -> 44.4 us (3.0 TB/s)
+//   24 layers, 14Q/2KV, d = 64, bfloat16, 4001 keys   343 -> 22.0 us (2.2 TB/s)
+//   1 layer, 4Q/1KV, d = 64, float32, 129 keys, with the eviction
+//                                                     26.7 -> 14.4 us, of which 10.6 kernels
 #include <math.h>
 
 #include <type_traits>

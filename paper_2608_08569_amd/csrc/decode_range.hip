@@ -729,7 +729,7 @@ __global__ __launch_bounds__(RFOLD_KEYS) void range_factors_kernel(const FusedAr
 // (One launch: as two, the merge of a few rows -- of none, in a batch of
 // sequences in one part whose planes could hold longer ones -- was 4.7 us and
 // a gap of its own beside 9.5 us of folding: 48 layers at 13,181 keys 269.5 ->
-// 267.1 us, eight sequences of 1k-8k keys 519.3 -> 517.5.)
+// 266.5 us, eight sequences of 1k-8k keys 520.7 -> 518.7.)
 constexpr int RMERGE_HEADS = RFOLD_KEYS / D;
 __host__ __device__ inline int merge_blocks(int Hq) { return (Hq + RMERGE_HEADS - 1) / RMERGE_HEADS; }
 template <int NW, bool RAG>

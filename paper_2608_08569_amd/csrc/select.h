@@ -12,7 +12,7 @@
 //      minimum over keys above the previous one (small E, the steady state of
 //      one eviction per step), or by an MSB-first radix select with 11-bit
 //      digits and an LDS histogram (large E, e.g. the first eviction): the
-//      first digit then holds a score's exponent and three bits of its
+//      first digit then holds a score's sign, exponent and two bits of its
 //      mantissa, so scores of any spread reach many bins (8-bit digits put
 //      most of a layer into a handful of bins, whose LDS atomics serialise),
 //      and two or three digits settle the threshold.
