@@ -664,10 +664,11 @@ __device__ __forceinline__ float2 parts_stats(const float2* ps, int P) {
 // and with it: 13,181 keys (2 parts) 162.6 and 164 us, 32,768 (4) 407 and 407,
 // 65,536 (8) 825-833 and 820-823, 131,072 (17) 1,700 and 1,660, 524,288 (65)
 // 7,400 and 6,766.  The host does not know the parts of a ragged call's
-// sequences, only what its planes can hold, and a batch of short sequences
-// would pay for an empty launch (eight of 1k-8k keys 519.1 -> 520.7 us): its
-// planes decide, at twice as many.
-constexpr int kOwnParts = 4, kOwnPartsRagged = 8;
+// sequences, only what its planes can hold, and a batch of shorter sequences
+// would pay for a launch it does not need (16 sequences of up to 8k keys in
+// planes of 80k slots: 4.6 of 1,420 us): there the planes' slots per sequence
+// decide, or planes so long that the launch does not count.
+constexpr int kOwnParts = 4, kManyParts = 64;
 
 // For a sequence in parts of a call with more of them, one block per (sequence
 // in parts, layer): every pair's max becomes its part's factor exp2(m_part -
@@ -1038,7 +1039,8 @@ hipError_t launch_range(const FusedArgs& a, hipStream_t stream) {
     if (a.rag.n > 0) {
         hipLaunchKernelGGL((range_order_kernel<NW>), dim3(1), dim3(ORDER_THREADS), 0, stream, a);
         hipLaunchKernelGGL((decode_range_kernel<NW, true, true>), dim3(NW * a.L * a.R), dim3(64 * RW), 0, stream, a);
-        const bool table = a.plane > static_cast<int64_t>(kOwnPartsRagged) * RPART;
+        const int64_t parts = a.plane / RPART;
+        const bool table = parts >= kManyParts || parts >= static_cast<int64_t>(kOwnParts) * a.rag.n;
         if (table) hipLaunchKernelGGL((range_factors_kernel<NW, true>), dim3(a.MB, a.L), dim3(RFOLD_KEYS), 0, stream, a);
         hipLaunchKernelGGL((range_finish_kernel<NW, true>), dim3(a.FB + a.MB * merges, a.L), dim3(RFOLD_KEYS), 0, stream,
                            a, a.FB, table);
